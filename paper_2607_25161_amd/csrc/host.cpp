@@ -133,6 +133,41 @@ struct SmoothPart {
   }
 };
 
+// Coefficients of the smooth part on [0, rcut] in the layout of RealPoly<R>: per interval the
+// interpolation at the Chebyshev nodes, solved for the powers of the centred offset (at most
+// degree 6 on an offset of at most 1/2, well conditioned).
+template <typename R>
+std::vector<double> smooth_poly(const SmoothPart& sp, double rcut) {
+  using P = RealPoly<R>;
+  constexpr int n = P::kCoef;
+  double x[n];
+  for (int m = 0; m < n; ++m) x[m] = 0.5 * std::cos(M_PI * (m + 0.5) / n);
+  std::vector<double> out(size_t(P::kIntervals) * P::kStride, 0.0);
+  for (int q = 0; q < P::kIntervals; ++q) {
+    double v[n][5];
+    for (int m = 0; m < n; ++m) {
+      const double r = (q + 0.5 + x[m]) * rcut / P::kIntervals;
+      sp.eval(r, v[m]);
+      v[m][1] /= r * r;
+      v[m][3] /= r * r;
+      v[m][4] /= r;
+    }
+    for (int k = 0; k < 5; ++k) {
+      // Newton's divided differences, then the product form expanded to powers of the offset
+      double d[n], c[n] = {0};
+      for (int m = 0; m < n; ++m) d[m] = v[m][k];
+      for (int o = 1; o < n; ++o)
+        for (int m = n - 1; m >= o; --m) d[m] = (d[m] - d[m - 1]) / (x[m] - x[m - o]);
+      for (int m = n - 1; m >= 0; --m) {  // c <- c (x - x_m) + d_m, c[i] the power i
+        for (int i = n - 1; i > 0; --i) c[i] = c[i - 1] - x[m] * c[i];
+        c[0] = d[m] - x[m] * c[0];
+      }
+      for (int i = 0; i < n; ++i) out[size_t(q) * P::kStride + k * n + i] = c[n - 1 - i];
+    }
+  }
+  return out;
+}
+
 void rpy_free(double r, double a, double eta, double* o) {
   const double c8 = 1.0 / (8.0 * M_PI * eta);
   const double mt = 1.0 / (6.0 * M_PI * eta * a), mr = 1.0 / (8.0 * M_PI * eta * a * a * a);
@@ -294,7 +329,7 @@ struct fsd_system {
   double *d_ub = nullptr, *d_fb = nullptr, *d_lan = nullptr, *d_lc = nullptr, *d_u6 = nullptr;
   double *d_lh = nullptr, *d_lpart = nullptr;  // Lanczos reorthogonalisation coefficients and partials
   SpreadPlan* spread = nullptr;  // gather spreading (nullptr: atomic scatter)
-  std::vector<double> h_tab;  // host copy of the smooth-part table (5 per node, 8 stride)
+  std::vector<double> h_tab, h_tab32;  // the smooth part's coefficients (RealPoly), before rounding to R
 
   // per-kernel-class event timing (fsd_set_timing)
   struct Pending {
@@ -576,13 +611,10 @@ void choose_parameters(fsd_system* s) {
   const double reach = rcut * (s->le ? std::sqrt(1.25) : 1.0);
   if (reach >= 3.0 * L) throw ApiError(FSD_EINVAL, "real-space cutoff exceeds three box lengths; raise xi");
   r.r_cut = rcut;
-  const int ntab = 4096;
-  const double ht = rcut / ntab;
-  r.inv_ht = 1.0 / ht;
-  r.ntab = ntab;
-  SmoothPart sp(a, p.eta, xi, rcut + 4 * ht);
-  s->h_tab.assign(size_t(ntab + 4) * 8, 0.0);
-  for (int t = 0; t < ntab + 4; ++t) sp.eval((t - 1) * ht, &s->h_tab[8 * size_t(t)]);
+  r.inv_w = 1.0 / rcut;
+  SmoothPart sp(a, p.eta, xi, rcut);
+  s->h_tab = smooth_poly<double>(sp, rcut);
+  s->h_tab32 = smooth_poly<float>(sp, rcut);
   double s0[5];
   sp.eval(0.0, s0);
   r.self_t = mt - s0[0];
@@ -593,12 +625,11 @@ void choose_parameters(fsd_system* s) {
 
 void upload_tables(fsd_system* s) {
   const size_t nt = s->h_tab.size();
+  std::vector<float> f(s->h_tab32.begin(), s->h_tab32.end());
   s->d_tab64 = dalloc<double>(s->owned, nt);
-  s->d_tab32 = dalloc<float>(s->owned, nt);
-  std::vector<float> f(nt);
-  for (size_t i = 0; i < nt; ++i) f[i] = float(s->h_tab[i]);
+  s->d_tab32 = dalloc<float>(s->owned, f.size());
   HIPCHK(hipMemcpy(s->d_tab64, s->h_tab.data(), nt * sizeof(double), hipMemcpyHostToDevice));
-  HIPCHK(hipMemcpy(s->d_tab32, f.data(), nt * sizeof(float), hipMemcpyHostToDevice));
+  HIPCHK(hipMemcpy(s->d_tab32, f.data(), f.size() * sizeof(float), hipMemcpyHostToDevice));
   const int N = s->wp.n;
   std::vector<double> tw(2 * N);
   std::vector<float> twf(2 * N);
@@ -1936,7 +1967,7 @@ size_t fsd_estimate_bytes(const fsd_params* p, int32_t nb, int32_t na, double L)
   const double n = 6.0 * (nb + na);
   const int m = p->gmres_restart;
   double bytes = 48.0 * double(N) * N * N + 4.0 * nnz + 44.0 * nl + 8.0 * n * (m + 9) + 200.0 * nb + 400.0 * na +
-                 8.0 * (m + 2) * 1024 + 8.0 * 8 * 4100 + (1 << 20);
+                 8.0 * (m + 2) * 1024 + 8.0 * 64 * 36 + 4.0 * 128 * 20 + (1 << 20);
   if (p->kT > 0) {  // Lanczos basis and partials, Brownian vectors
     const double lm = p->lanczos_maxit > 0 ? p->lanczos_maxit : 100;
     bytes += 8.0 * nb * (6.0 * (lm + 1) + 24) + 8.0 * (lm + 2) * 1024;
@@ -2020,20 +2051,20 @@ fsd_status fsd_real_functions(fsd_system* s, int n, const double* r, double* out
   fsd_status c = check_ready(s);
   if (c) return c;
   if (n < 0 || (n > 0 && (!r || !out))) return fail(s, FSD_EINVAL, "bad arguments");
-  // the same interpolation as the real-space kernel, evaluated on the host table
+  // the same interpolation as the real-space kernel, evaluated on the host's coefficients
   for (int q = 0; q < n; ++q) {
     if (!(r[q] > 0) || r[q] >= s->rp.r_cut) return fail(s, FSD_EINVAL, "r outside (0, r_cut)");
     double o[5];
     rpy_free(r[q], s->p.radius, s->p.eta, o);
-    const double t = r[q] * s->rp.inv_ht;
-    const int it = int(t);
-    const double f = t - it;
-    const double w[4] = {-f * (f - 1) * (f - 2) / 6.0, (f + 1) * (f - 1) * (f - 2) / 2.0,
-                         -(f + 1) * f * (f - 2) / 2.0, (f + 1) * f * (f - 1) / 6.0};
+    using P = RealPoly<double>;
+    const double u = r[q] * s->rp.inv_w * P::kIntervals;
+    const int it = std::min(int(u), P::kIntervals - 1);
+    const double scale[5] = {1.0, r[q] * r[q], 1.0, r[q] * r[q], r[q]};
     for (int k = 0; k < 5; ++k) {
-      double sv = 0;
-      for (int m = 0; m < 4; ++m) sv += w[m] * s->h_tab[8 * size_t(it + m) + k];
-      out[5 * q + k] = o[k] - sv;
+      const double* cf = &s->h_tab[size_t(it) * P::kStride + k * P::kCoef];
+      double sv = cf[0];
+      for (int m = 1; m < P::kCoef; ++m) sv = sv * (u - it - 0.5) + cf[m];
+      out[5 * q + k] = o[k] - scale[k] * sv;
     }
   }
   return FSD_OK;

@@ -80,103 +80,145 @@ struct SpreadPlan {
 // real-space pair sum: one group of LPR lanes per bead row
 // ------------------------------------------------------------------------------------------
 
+// The smooth part of a pair, five scalars as piecewise polynomials of the distance (RealPoly):
+// interval q = int(r inv_w), x = r inv_w - q - 1/2, Horner from the highest coefficient.  T points
+// at the coefficients in LDS.  Rows of a multiple of 16 bytes read in 16-byte pieces.
+template <typename R>
+__device__ __forceinline__ void smooth_part(const R* T, R r, R inv_w, R (&f)[5]) {
+  using P = RealPoly<R>;
+  const R u = r * inv_w;
+  const int q = min(int(u), P::kIntervals - 1);  // r < r_cut up to rounding
+  const R x = u - R(q) - R(0.5);
+  typedef R V __attribute__((ext_vector_type(16 / sizeof(R))));
+  constexpr int L = 16 / sizeof(R);
+  const V* row = reinterpret_cast<const V*>(T + q * P::kStride);
+  V c[P::kStride / L];
+#pragma unroll
+  for (int k = 0; k < P::kStride / L; ++k) c[k] = row[k];
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+    R v = c[(k * P::kCoef) / L][(k * P::kCoef) % L];
+#pragma unroll
+    for (int m = 1; m < P::kCoef; ++m) v = v * x + c[(k * P::kCoef + m) / L][(k * P::kCoef + m) % L];
+    f[k] = v;
+  }
+}
+
+// Out of the pair's separation vector d itself, with no unit vector and no division:
+//   u += (tI + ..) f + B (d.f) d + C d x t,   w += rI t + rB (d.t) d + C d x f.
+// What bounds it: per pair the position (32 B) and the force moments (48 B) are gathered, one
+// cache line a lane.  The smooth part was gathered as well, four rows of a 262 KB table in L2,
+// 12 of the 17 loads of a pair: at 15.5 million pairs (81,920 beads) 367 us in FP64 and 230 in
+// FP32, the rate at which a CU looks up cache lines.  As 64 intervals of degree 6 (FP64) or 128
+// of degree 3 (FP32) it is 18 or 10 KB that every workgroup copies to LDS, and is closer to the
+// quadrature than the table was (4e-14 of the self mobility against 1e-13): 163 us in FP64, 114
+// in FP32.  A workgroup takes a contiguous chunk of rows, in the plan's spatial order where there
+// is one, so that the copy is paid once per many rows.
 template <typename R, int LPR>
 __device__ __forceinline__ void real_sum_body(int nb, const double4* __restrict__ pos,
-                                                  const double* __restrict__ lam, const int* __restrict__ rowptr,
-                                                  const uint32_t* __restrict__ col, const R* __restrict__ tab,
-                                                  RealParams rp, double* __restrict__ out, int accumulate,
-                                                  const int* __restrict__ order, const int* __restrict__ skip, int bx_, int by_, int gx_) {
+                                              const double* __restrict__ lam, const int* __restrict__ rowptr,
+                                              const uint32_t* __restrict__ col, const R* __restrict__ tab,
+                                              const RealParams& rp, double* __restrict__ out, int accumulate,
+                                              const int* __restrict__ order, const int* __restrict__ skip,
+                                              unsigned char* smem, int bx, int nblk) {
   if (skip && *skip) return;
-  // with order (beads in spatially sorted order), rows are visited in that order and
-  // each XCD takes one contiguous range of them
-  const int nblk = gx_ > 0 ? gx_ : int((size_t(nb) * LPR + blockDim.x - 1) / blockDim.x);
-  const int gt = (order ? xcd_remap(bx_, nblk) : bx_) * blockDim.x + threadIdx.x;
-  const int rl = gt / LPR;
-  const int lane = gt % LPR;
-  if (rl >= nb) return;  // LPR divides the wavefront, so whole groups leave together
-  const int row = order ? order[rl] : rl;
-  const double4 pi = pos[row];
-  const R a = R(rp.a);
+  using P = RealPoly<R>;
+  R* T = reinterpret_cast<R*>(smem);
+  {
+    typedef R V __attribute__((ext_vector_type(16 / sizeof(R))));
+    constexpr int NV = P::kIntervals * P::kStride * int(sizeof(R)) / 16;
+    for (int k = threadIdx.x; k < NV; k += kThreads)
+      reinterpret_cast<V*>(T)[k] = reinterpret_cast<const V*>(tab)[k];
+  }
+  __syncthreads();
+  constexpr int kGroups = kThreads / LPR;
+  int chunk = (nb + nblk - 1) / nblk;
+  if (chunk > kGroups) chunk = (chunk + kGroups - 1) / kGroups * kGroups;  // whole passes
+  const int lb = order ? xcd_remap(bx, nblk) : bx;  // with an order, each XCD takes one contiguous range
+  const int r_end = min(nb, (lb + 1) * chunk), lane = threadIdx.x % LPR;
+  const R a = R(rp.a), a2 = a * a;
   const R c8 = R(1.0 / (8.0 * M_PI * rp.eta));
-  const R mt = R(1.0 / (6.0 * M_PI * rp.eta * rp.a));
-  const R mr = R(1.0 / (8.0 * M_PI * rp.eta * rp.a * rp.a * rp.a));
-  const R inv_ht = R(rp.inv_ht);
+  const R inv_w = R(rp.inv_w) * R(P::kIntervals);
+  const R touch = R(4) * a2;
   const double gam = rp.gam ? *rp.gam : 0.0;
-  R u0 = 0, u1 = 0, u2 = 0, w0 = 0, w1 = 0, w2 = 0;
-  const int e1 = rowptr[row + 1];
-  for (int e = rowptr[row] + lane; e < e1; e += LPR) {
-    const uint32_t c = col[e];
-    const int j = int(c & 0x3FFFFFu);
-    const double4 pj = pos[j];
-    const double dyd = pi.y - pj.y + (int((c >> 25) & 7u) - 3) * rp.L;  // Cartesian from sheared
-    const R dx = R(pi.x - pj.x + (int((c >> 22) & 7u) - 3) * rp.L + gam * dyd);
-    const R dy = R(dyd);
-    const R dz = R(pi.z - pj.z + (int((c >> 28) & 7u) - 3) * rp.L);
-    const R r = sqrt(dx * dx + dy * dy + dz * dz);
-    const R ir = R(1) / r;
-    const R ex = dx * ir, ey = dy * ir, ez = dz * ir;
-    // free-space force-torque RPY (non-overlapping and overlapping branches)
-    R tI, tR, rI, rR, cc;
-    if (r >= R(2) * a) {
-      const R ir2 = ir * ir, a2 = a * a;
-      tI = c8 * ir * (R(1) + R(2.0 / 3.0) * a2 * ir2);
-      tR = c8 * ir * (R(1) - R(2) * a2 * ir2);
-      rI = R(-0.5) * c8 * ir * ir2;
-      rR = R(1.5) * c8 * ir * ir2;
-      cc = -c8 * ir2;
-    } else {
-      const R s = r / a;
-      tI = mt * (R(1) - R(9.0 / 32.0) * s);
-      tR = mt * R(3.0 / 32.0) * s;
-      rI = mr * (R(1) - R(27.0 / 32.0) * s + R(5.0 / 64.0) * s * s * s);
-      rR = mr * (R(9.0 / 32.0) * s - R(3.0 / 64.0) * s * s * s);
-      cc = -R(0.5) * c8 / (a * a) * s * (R(1) - R(3.0 / 8.0) * s);
+  for (int rl = lb * chunk + int(threadIdx.x) / LPR; rl < r_end; rl += kGroups) {
+    const int row = order ? order[rl] : rl;
+    const double4 pi = pos[row];
+    R u0 = 0, u1 = 0, u2 = 0, w0 = 0, w1 = 0, w2 = 0;
+    const int e1 = rowptr[row + 1];
+    for (int e = rowptr[row] + lane; e < e1; e += LPR) {
+      const uint32_t c = col[e];
+      const int j = int(c & 0x3FFFFFu);
+      const double4 pj = pos[j];
+      const double* lj = lam + 6 * size_t(j);
+      const R fx = R(lj[0]), fy = R(lj[1]), fz = R(lj[2]);
+      const R tx = R(lj[3]), ty = R(lj[4]), tz = R(lj[5]);
+      const double dyd = pi.y - pj.y + (int((c >> 25) & 7u) - 3) * rp.L;  // Cartesian from sheared
+      const R dx = R(pi.x - pj.x + (int((c >> 22) & 7u) - 3) * rp.L + gam * dyd);
+      const R dy = R(dyd);
+      const R dz = R(pi.z - pj.z + (int((c >> 28) & 7u) - 3) * rp.L);
+      const R r2 = dx * dx + dy * dy + dz * dz;
+      const R ir = rsqrt(r2), ir2 = ir * ir, ir3 = ir * ir2, r = r2 * ir;
+      // free-space force-torque RPY; C, tB and rB are the rt, tt and rr functions over r, r^2, r^2
+      R tI, tB, rI, rB, cc;
+      if (r2 >= touch) {
+        tI = c8 * ir * (R(1) + R(2.0 / 3.0) * a2 * ir2);
+        tB = c8 * ir3 * (R(1) - R(2) * a2 * ir2);
+        rI = R(-0.5) * c8 * ir3;
+        rB = R(1.5) * c8 * ir3 * ir2;
+        cc = -c8 * ir3;
+      } else {  // overlapping spheres
+        const R s = r / a, mt = c8 / a * R(4.0 / 3.0), mr = c8 / (a * a2);
+        tI = mt * (R(1) - R(9.0 / 32.0) * s);
+        tB = mt * R(3.0 / 32.0) * s * ir2;
+        rI = mr * (R(1) - R(27.0 / 32.0) * s + R(5.0 / 64.0) * s * s * s);
+        rB = mr * (R(9.0 / 32.0) * s - R(3.0 / 64.0) * s * s * s) * ir2;
+        cc = -R(0.5) * mr * (R(1) - R(3.0 / 8.0) * s);
+      }
+      R f[5];
+      smooth_part<R>(T, r, inv_w, f);
+      tI -= f[0];
+      tB -= f[1];
+      rI -= f[2];
+      rB -= f[3];
+      cc -= f[4];
+      const R fd = tB * (dx * fx + dy * fy + dz * fz), td = rB * (dx * tx + dy * ty + dz * tz);
+      u0 += tI * fx + fd * dx + cc * (dy * tz - dz * ty);
+      u1 += tI * fy + fd * dy + cc * (dz * tx - dx * tz);
+      u2 += tI * fz + fd * dz + cc * (dx * ty - dy * tx);
+      w0 += rI * tx + td * dx + cc * (dy * fz - dz * fy);
+      w1 += rI * ty + td * dy + cc * (dz * fx - dx * fz);
+      w2 += rI * tz + td * dz + cc * (dx * fy - dy * fx);
     }
-    // minus the smooth part (cubic Lagrange on nodes it-1 .. it+2; table row 0 is r = -h)
-    const R t = r * inv_ht;
-    const int it = int(t);
-    const R f = t - R(it);
-    const R wa = -f * (f - 1) * (f - 2) * R(1.0 / 6.0);
-    const R wb = (f + 1) * (f - 1) * (f - 2) * R(0.5);
-    const R wc = -(f + 1) * f * (f - 2) * R(0.5);
-    const R wd = (f + 1) * f * (f - 1) * R(1.0 / 6.0);
-    const R* T0 = tab + 8 * it;
-    tI -= wa * T0[0] + wb * T0[8] + wc * T0[16] + wd * T0[24];
-    tR -= wa * T0[1] + wb * T0[9] + wc * T0[17] + wd * T0[25];
-    rI -= wa * T0[2] + wb * T0[10] + wc * T0[18] + wd * T0[26];
-    rR -= wa * T0[3] + wb * T0[11] + wc * T0[19] + wd * T0[27];
-    cc -= wa * T0[4] + wb * T0[12] + wc * T0[20] + wd * T0[28];
-    const double* lj = lam + 6 * j;
-    const R fx = R(lj[0]), fy = R(lj[1]), fz = R(lj[2]);
-    const R tx = R(lj[3]), ty = R(lj[4]), tz = R(lj[5]);
-    const R fd = ex * fx + ey * fy + ez * fz;
-    const R td = ex * tx + ey * ty + ez * tz;
-    u0 += tI * fx + tR * fd * ex + cc * (ey * tz - ez * ty);
-    u1 += tI * fy + tR * fd * ey + cc * (ez * tx - ex * tz);
-    u2 += tI * fz + tR * fd * ez + cc * (ex * ty - ey * tx);
-    w0 += rI * tx + rR * td * ex + cc * (ey * fz - ez * fy);
-    w1 += rI * ty + rR * td * ey + cc * (ez * fx - ex * fz);
-    w2 += rI * tz + rR * td * ez + cc * (ex * fy - ey * fx);
-  }
+    // the first exchange leaves the velocity with the lower half of the lanes and the angular
+    // velocity with the upper one, so the others move three values instead of six
+    bool up = false;
+    if (LPR > 1) {
+      up = lane & (LPR / 2);
+      const R s0 = up ? u0 : w0, s1 = up ? u1 : w1, s2 = up ? u2 : w2;
+      u0 = (up ? w0 : u0) + __shfl_xor(s0, LPR / 2, LPR);
+      u1 = (up ? w1 : u1) + __shfl_xor(s1, LPR / 2, LPR);
+      u2 = (up ? w2 : u2) + __shfl_xor(s2, LPR / 2, LPR);
 #pragma unroll
-  for (int o = LPR / 2; o >= 1; o >>= 1) {
-    u0 += __shfl_xor(u0, o, LPR);
-    u1 += __shfl_xor(u1, o, LPR);
-    u2 += __shfl_xor(u2, o, LPR);
-    w0 += __shfl_xor(w0, o, LPR);
-    w1 += __shfl_xor(w1, o, LPR);
-    w2 += __shfl_xor(w2, o, LPR);
-  }
-  if (lane == 0) {
-    const double* li = lam + 6 * row;
-    double* o = out + 6 * row;
-    const double v[6] = {double(u0) + rp.self_t * li[0], double(u1) + rp.self_t * li[1],
-                         double(u2) + rp.self_t * li[2], double(w0) + rp.self_r * li[3],
-                         double(w1) + rp.self_r * li[4], double(w2) + rp.self_r * li[5]};
-    if (accumulate)
-      for (int k = 0; k < 6; ++k) o[k] += v[k];
-    else
-      for (int k = 0; k < 6; ++k) o[k] = v[k];
+      for (int o = LPR / 4; o >= 1; o >>= 1) {
+        u0 += __shfl_xor(u0, o, LPR);
+        u1 += __shfl_xor(u1, o, LPR);
+        u2 += __shfl_xor(u2, o, LPR);
+      }
+    }
+    if (LPR == 1 || (lane & (LPR / 2 - 1)) == 0) {
+      const int h = up ? 3 : 0;
+      const double* li = lam + 6 * size_t(row) + h;
+      double* o = out + 6 * size_t(row) + h;
+      const double self = up ? rp.self_r : rp.self_t;
+      double v[6] = {double(u0) + self * li[0], double(u1) + self * li[1], double(u2) + self * li[2], 0, 0, 0};
+      if (LPR == 1) {
+        v[3] = double(w0) + rp.self_r * li[3];
+        v[4] = double(w1) + rp.self_r * li[4];
+        v[5] = double(w2) + rp.self_r * li[5];
+      }
+      for (int k = 0; k < (LPR == 1 ? 6 : 3); ++k) o[k] = accumulate ? o[k] + v[k] : v[k];
+    }
   }
 }
 
@@ -186,18 +228,29 @@ __global__ __launch_bounds__(256) void k_real_sum(int nb, const double4* __restr
                                                   const uint32_t* __restrict__ col, const R* __restrict__ tab,
                                                   RealParams rp, double* __restrict__ out, int accumulate,
                                                   const int* __restrict__ order, const int* __restrict__ skip) {
-  real_sum_body<R, LPR>(nb, pos, lam, rowptr, col, tab, rp, out, accumulate, order, skip, blockIdx.x, blockIdx.y, gridDim.x);
+  extern __shared__ unsigned char smem_raw[];
+  real_sum_body<R, LPR>(nb, pos, lam, rowptr, col, tab, rp, out, accumulate, order, skip, smem_raw, blockIdx.x,
+                        gridDim.x);
 }
+
+namespace {
+// Workgroups of a real-space sum over nb rows: one pass of 256 / LPR rows each up to
+// kRealBlocks, so that small systems spread over the CUs; beyond it each takes more rows
+// (twelve workgroups a CU hide the gathers, and the copy of the coefficients is paid 3,072 times)
+constexpr int kRealBlocks = 3072;
+inline int real_blocks(long long nb, int lpr) {
+  return int(std::min<long long>((nb * lpr + kThreads - 1) / kThreads, kRealBlocks));
+}
+}  // namespace
 
 template <typename R>
 void launch_real_sum(int nb, const double* pos4, const double* lam, const int* rowptr, const uint32_t* col,
                      const R* table, const RealParams& rp, double* out, bool accumulate, int lpr, hipStream_t st,
                      const int* skip, const int* order) {
-  const long long threads = (long long)nb * lpr;
   const int acc = accumulate ? 1 : 0;
   const double4* p = (const double4*)pos4;
 #define FSD_REAL(L_)                                                                                    \
-  launch_k(k_real_sum<R, L_>, nblocks(threads), kThreads, 0, st, nb, p, lam, rowptr, col, table, rp, out, acc, order, skip)
+  launch_k(k_real_sum<R, L_>, real_blocks(nb, L_), kThreads, RealPoly<R>::kBytes, st, nb, p, lam, rowptr, col, table, rp, out, acc, order, skip)
   switch (lpr) {
     case 1: FSD_REAL(1); break;
     case 2: FSD_REAL(2); break;
@@ -1141,7 +1194,9 @@ __global__ __launch_bounds__(256) void k_spread_fused(const int* __restrict__ bl
   }
   b -= na_blk;
   if (b < nr_blk) {
-    real_sum_body<R, LPR>(ra.nb, ra.pos, lam, ra.rowptr, ra.col, tab, ra.rp, ra.out, 0, ra.order, skip, b, 0, nr_blk);
+    extern __shared__ unsigned char smem_raw[];
+    real_sum_body<R, LPR>(ra.nb, ra.pos, lam, ra.rowptr, ra.col, tab, ra.rp, ra.out, 0, ra.order, skip, smem_raw, b,
+                          nr_blk);
     return;
   }
   spread_split_body<R>(blk_start, blk_end, cand, perm, starts, weights, lam, wp, nbin, C, grid, cs, skip, b - nr_blk, 0,
@@ -1157,9 +1212,9 @@ void launch_spread_fused(const SpreadPlan* sp, const double* lam, const WavePara
   const int nblk = sp->nbin * sp->nbin * sp->nbin;
   const size_t per = sizeof(R) * (3 * size_t(wp.support) + 6) + sizeof(int4) + sizeof(int);
   const int C = int(std::min<size_t>(128, (size_t(60) << 10) / per)) & ~3;  // as launch_spread_gather
-  const size_t shm = std::max(per * C, size_t(kSplitRedBytes64) / sizeof(double) * sizeof(R));
+  const size_t shm = std::max({per * C, size_t(kSplitRedBytes64) / sizeof(double) * sizeof(R), RealPoly<R>::kBytes});
   auto pad8 = [](long long n) { return int((n + 7) / 8 * 8); };
-  const int na_blk = pad8((ga.na + 3) / 4), nr_blk = pad8(((long long)ra.nb * lpr + 255) / 256);
+  const int na_blk = pad8((ga.na + 3) / 4), nr_blk = pad8(real_blocks(ra.nb, lpr));
   const int total = na_blk + nr_blk + nblk;
 #define FSD_FUSED(L_)                                                                                       \
   launch_k(k_spread_fused<R, L_>, total, 256, shm, st, sp->blk_start, sp->blk_end, sp->cand, sp->perm,        \
@@ -1996,6 +2051,7 @@ __device__ inline const float* pick<float>(const double*, const float* b) {
 }
 
 constexpr int kBatchLpr = 16;  // lanes per bead row of the batched real-space sum
+constexpr int kBatchRealPasses = 4;  // row passes per workgroup there: the other systems fill the chip
 }  // namespace
 
 template <typename R>
@@ -2003,8 +2059,9 @@ __global__ __launch_bounds__(256) void kb_real(const BatchDesc* __restrict__ D, 
                                               int nsys) {
   const int s = batch_sys(off, nsys, blockIdx.x);
   const BatchDesc& d = D[s];
+  extern __shared__ unsigned char smem_raw[];
   real_sum_body<R, kBatchLpr>(d.nb, (const double4*)d.pos4, d.z, d.nrow, d.ncol, pick<R>(d.tab64, d.tab32), d.rp,
-                              d.w, 0, d.perm, &d.ctl->stop, blockIdx.x - off[s], 0, 0);
+                              d.w, 0, d.perm, &d.ctl->stop, smem_raw, blockIdx.x - off[s], off[s + 1] - off[s]);
 }
 
 template <typename R>
@@ -2084,7 +2141,7 @@ int batch_blocks(const BatchDesc& d, int kind) {
     case BK_AGG:
       return (d.na + 3) / 4;
     case BK_REAL:
-      return int((size_t(d.nb) * kBatchLpr + kThreads - 1) / kThreads);
+      return std::max(1, real_blocks(d.nb, kBatchLpr) / kBatchRealPasses);
     case BK_SPREAD:
       return d.bin_start ? d.nbin * d.nbin * d.nbin : 0;
     case BK_FFT_OUTER:
@@ -2105,6 +2162,8 @@ size_t batch_shm(const BatchDesc& d, int kind, int prec) {
   const size_t rb = prec ? sizeof(float) : sizeof(double), tb = 2 * rb;
   const size_t N = d.plan.n;
   switch (kind) {
+    case BK_REAL:
+      return prec ? RealPoly<float>::kBytes : RealPoly<double>::kBytes;
     case BK_SPREAD:
       return std::max((rb * (3 * size_t(d.wp.support) + 6) + sizeof(int4) + sizeof(int)) * d.C,
                       size_t(kSplitRedBytes64) / sizeof(double) * rb);
@@ -2124,7 +2183,7 @@ void batch_mobility(int kind, int stage, const BatchDesc* D, const int* off, int
                     hipStream_t st) {
   switch (kind) {
     case BK_REAL:
-      kb_real<R><<<total, kThreads, 0, st>>>(D, off, nsys);
+      kb_real<R><<<total, kThreads, shm, st>>>(D, off, nsys);
       break;
     case BK_SPREAD:
       kb_spread<R><<<total, 256, shm, st>>>(D, off, nsys);
