@@ -90,15 +90,15 @@ struct WaveParams {
 
 // The smooth part of the real-space functions as piecewise polynomials on kIntervals equal
 // intervals of [0, r_cut]: five functions of kCoef coefficients each (highest power first, in the
-// offset from the interval's centre over its width), rows kStride values apart (a multiple of
-// 16 bytes).  The functions, all even in r: tt I, tt rr / r^2, rr I, rr rr / r^2, rt / r.
+// offset from the interval's centre over its width), rows kStride values apart (an odd multiple
+// of 16 bytes).  The functions, all even in r: tt I, tt rr / r^2, rr I, rr rr / r^2, rt / r.
 // Their error, in units of the self mobilities, is at most 4e-14 in FP64 and 2e-9 in FP32 for
 // cutoff rules from 1e-5 to 1e-8 (checked against the quadrature in the tests).
 template <typename R>
 struct RealPoly;
 template <>
 struct RealPoly<double> {
-  static constexpr int kIntervals = 64, kCoef = 7, kStride = 36;
+  static constexpr int kIntervals = 64, kCoef = 7, kStride = 38;
   static constexpr size_t kBytes = sizeof(double) * kIntervals * kStride;
 };
 template <>
@@ -165,7 +165,7 @@ void launch_real_sum(int nb, const double* pos4, const double* lam, const int* r
 template <typename R>
 void launch_spread(int nb, const double* pos4, const double* lam, const WaveParams& wp, R* grid,
                    hipStream_t st, const int* skip = nullptr);
-// Spreading and interpolation on the grid of a sheared lattice (wp.gam): grid point
+// Spreading (grids without 8^3 blocks) and interpolation on a sheared lattice (wp.gam): grid point
 // (i, j, k) sits at sheared coordinates (i, j, k) h, and each grid row j takes the P x-points
 // around its own centre p_x - gam (j h - p_y).  Spreading scatters with atomic adds into a
 // zeroed grid; interpolation adds into out as launch_interp does (with V: + Sigma^T V).
@@ -193,7 +193,9 @@ void launch_wave_fft(R* grid, const FftPlan& plan, const R* twiddle, const WaveP
                      hipStream_t st, const int* skip = nullptr);
 // Gaussian spreading as a gather over beads binned by grid block (no atomics).
 struct SpreadPlan;
-SpreadPlan* spread_plan_create(int nb, int n_grid, int support);  // nullptr if n_grid % 4 != 0
+// nullptr if n_grid has no blocks: not a multiple of 4, or of 8 on a sheared lattice
+SpreadPlan* spread_plan_create(int nb, int n_grid, int support, bool sheared);
+bool spread_plan_sheared(const SpreadPlan* sp);
 void spread_plan_destroy(SpreadPlan* sp);
 hipError_t spread_plan_update(SpreadPlan* sp, const double* pos4, const WaveParams& wp, hipStream_t st);
 template <typename R>
@@ -388,14 +390,12 @@ struct BatchDesc {
   // gather spreading (8^3 blocks): per-block candidate lists
   const int* blk_start;
   const int* blk_end;
-  const int* cand;
-  const int* bin_start;
-  const int* bin_end;
+  const int4* cand;
   const int* perm;
   const int4* starts;
   const double* w64;
   const float* w32;
-  int nbin, K, C;
+  int nbin;
   // lubrication and preconditioner
   const int* lrow;
   const uint32_t* lcol;
@@ -437,7 +437,7 @@ int green_g_of(const WaveParams& wp);
 bool tile_b_fits(int N, int B, int rbytes);
 bool tile_g_fits(int N, int G, int rbytes);
 // fill the spreading fields of d from a gather plan (d.wp must be set first)
-void spread_plan_desc(const SpreadPlan* sp, int prec, BatchDesc& d);
+void spread_plan_desc(const SpreadPlan* sp, BatchDesc& d);
 // per-system block counts of each kind and the dynamic LDS the kinds need (prec: 0 FP64, 1 FP32)
 int batch_blocks(const BatchDesc& d, int kind);
 size_t batch_shm(const BatchDesc& d, int kind, int prec);

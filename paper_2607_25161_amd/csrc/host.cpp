@@ -707,6 +707,10 @@ void prepare_begin(fsd_system* s) {
     launch_set_value(s->d_gam, g, s->st);
   }
   s->rp.gam = s->wp.gam = s->le ? s->d_gam : nullptr;
+  if (spread_plan_sheared(s->spread) && !s->le) {  // the lattice was switched back to the cube
+    spread_plan_destroy(s->spread);
+    s->spread = spread_plan_create(s->nb, s->wp.n, s->wp.support, false);
+  }
   launch_bead_positions(s->nb, s->na, s->d_body, s->d_xbody, s->d_com, s->d_quat, s->L, g, s->d_r4, s->d_pos4,
                         s->st);
   HIPCHK(neighbors_count(s->nw, s->nb, s->d_pos4, s->d_body, s->L, g, s->rp.r_cut, false, s->d_nrow, s->st));
@@ -818,7 +822,7 @@ void mob_real(fsd_system* s, const double* lam, double* out, hipStream_t rs, con
 template <typename R>
 void mob_spread(fsd_system* s, const double* lam, const int* skip) {
   R* grid = static_cast<R*>(s->d_grid);
-  if (s->le) {
+  if (s->le && !s->spread) {
     const size_t N = s->wp.n;
     launch_zero(grid, sizeof(R) * 6 * N * N * N, s->st);
     launch_spread_sheared<R>(s->nb, s->d_pos4, lam, s->wp, grid, s->st, skip);
@@ -923,7 +927,7 @@ void mob_first(fsd_system* s, const double* x, double* y, const int* skip) {
 template <typename R>
 void apply_saddle(fsd_system* s, const double* x, double* y, const int* skip = nullptr) {
   const size_t nb6 = 6 * size_t(s->nb);
-  if (spread_fuses(s->spread) && !s->le) {
+  if (spread_fuses(s->spread)) {
     const double full = grid_bytes<R>(s), beads = 80.0 * s->nb;
     {
       Timed t(s, FSD_TIMER_SPREAD, full + beads + real_bytes(s) + rigid_bytes(s));
@@ -1500,7 +1504,7 @@ bool replay_one(fsd_system* s, int cls) {
   switch (cls) {
     case FSD_TIMER_REAL: mob_real<R>(s, s->d_z, s->d_t, s->st, nullptr); return true;
     case FSD_TIMER_SPREAD:  // the kernel a solve runs for this class
-      if (spread_fuses(s->spread) && !s->le)
+      if (spread_fuses(s->spread))
         mob_first<R>(s, s->d_z, s->d_t, nullptr);
       else
         mob_spread<R>(s, s->d_z, nullptr);
@@ -1703,7 +1707,7 @@ fsd_status fsd_init_aggregates(fsd_system* s, int32_t n_agg, const int32_t* off,
     HIPCHK(hipHostMalloc((void**)&s->h_flags, 2 * sizeof(int)));
     HIPCHK(hipHostMalloc((void**)&s->h_scal, 4 * sizeof(double)));
     s->h_flags[0] = s->h_flags[1] = 0;
-    s->spread = spread_plan_create(nb, s->wp.n, s->wp.support);  // nullptr: grid not a multiple of 4
+    s->spread = spread_plan_create(nb, s->wp.n, s->wp.support, s->le);  // nullptr: scatter
     upload_tables(s);
     HIPCHK(hipMemcpy(s->d_offsets, off, sizeof(int) * (n_agg + 1), hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(s->d_body, body.data(), sizeof(int) * nb, hipMemcpyHostToDevice));
@@ -1967,15 +1971,15 @@ size_t fsd_estimate_bytes(const fsd_params* p, int32_t nb, int32_t na, double L)
   const double n = 6.0 * (nb + na);
   const int m = p->gmres_restart;
   double bytes = 48.0 * double(N) * N * N + 4.0 * nnz + 44.0 * nl + 8.0 * n * (m + 9) + 200.0 * nb + 400.0 * na +
-                 8.0 * (m + 2) * 1024 + 8.0 * 64 * 36 + 4.0 * 128 * 20 + (1 << 20);
+                 8.0 * (m + 2) * 1024 + 8.0 * 64 * 38 + 4.0 * 128 * 20 + (1 << 20);
   if (p->kT > 0) {  // Lanczos basis and partials, Brownian vectors
     const double lm = p->lanczos_maxit > 0 ? p->lanczos_maxit : 100;
     bytes += 8.0 * nb * (6.0 * (lm + 1) + 24) + 8.0 * (lm + 2) * 1024;
   }
-  // spreading plan: 3P weights per bead (FP64, FP32 and a staging copy) and up to 27 block
+  // spreading plan: 3P weights per bead (FP64 and FP32) and up to 27 block
   // slots per bead (keys and values, sorted copies and the sort's temporary storage)
   const int P = p->support > 0 ? p->support : int(std::ceil(2.0 / M_PI * std::log(1.0 / p->ewald_tol))) + 2;
-  bytes += double(nb) * (20.0 * 3 * P + 27.0 * 32.0);
+  bytes += double(nb) * (12.0 * 3 * P + 27.0 * 48.0);
   return size_t(bytes);
 }
 
@@ -2606,7 +2610,12 @@ namespace {
 size_t system_bytes(const fsd_system* s) {
   fsd_params p = s->p;
   p.grid = s->wp.n;  // the grid it holds (larger on a sheared lattice than the rule gives)
-  return fsd_estimate_bytes(&p, s->nb, s->na, s->L);
+  size_t bytes = fsd_estimate_bytes(&p, s->nb, s->na, s->L);
+  if (spread_plan_sheared(s->spread)) {  // P^2 + P weights instead of 3 P, row starts, up to 45 slots
+    const size_t P = size_t(s->wp.support);
+    bytes += size_t(s->nb) * (12 * (P * P + P) + 2 * P + 18 * 48);
+  }
+  return bytes;
 }
 
 // One solve (and optionally an Euler step) for every admitted system.  Each system
@@ -2703,7 +2712,7 @@ BatchDesc make_desc(fsd_system* s, int prec) {
   d.grid = s->d_grid;
   d.bl = lines_b_of(s->wp, prec ? 4 : 8);
   d.bg = green_g_of(s->wp);
-  spread_plan_desc(s->spread, prec, d);
+  spread_plan_desc(s->spread, d);
   d.lrow = lub ? s->d_lrow : nullptr;
   d.lcol = s->d_lcol;
   d.lcoef = s->d_lcoef;

@@ -53,27 +53,31 @@ __device__ inline R wave_sum(R v) {
 }  // namespace
 
 // Gather-spreading plan: beads binned by the grid block holding the first point of
-// their support, in sorted order with their support starts and per-axis weights.
+// their support, in sorted order with their support starts and weights.  On the cube a bead has
+// P weights per axis; on a sheared lattice (8^3 blocks only) every grid row in y has its own
+// window along x, so it has P x P weights of its (y, x) points, the row's x start, and P along z.
 struct SpreadPlan {
   int nb = 0, BS = 0, nbin = 0, K = 0, P = 0;
+  bool sheared = false;
+  int wlen = 0;  // weights per bead: 3 P, or P P + P
   int *keys_in = nullptr, *keys_out = nullptr, *vals_in = nullptr, *perm = nullptr;
-  int *bin_start = nullptr, *bin_end = nullptr;
-  // 8^3 blocks: for every block, the sorted indices of exactly the beads whose support
-  // reaches it (cand[blk_start[b] .. blk_end[b]), in bead order); each bead files kc^3 slots
-  // (its blocks, then sentinels) that one stable sort groups by block
-  int kc = 0;
+  int *bin_start = nullptr, *bin_end = nullptr;  // 4^3 blocks only
+  // 8^3 blocks: for every block, a record of exactly the beads whose support reaches it
+  // (cand[blk_start[b] .. blk_end[b]), in bead order): sorted index, bead, and the offsets of the
+  // block's first point from the support's start, mod N, 8 bits an axis.  Each bead files kcx kc^2
+  // slots (its blocks, then sentinels) that one stable sort groups by block
+  int kc = 0, kcx = 0;
   int *blk_start = nullptr, *blk_end = nullptr, *pk_in = nullptr, *pk_out = nullptr, *pv_in = nullptr,
-      *cand = nullptr;
+      *pv_out = nullptr;
+  int4* cand = nullptr;
   void* ptemp = nullptr;
   size_t ptemp_bytes = 0;
   int4* starts = nullptr;   // (sx, sy, sz, bin) per bead, sorted order
-  double* weights = nullptr;  // 3P weights per bead, sorted order
+  short* rows = nullptr;    // sheared: x start of each of the P grid rows, sorted order
+  double* weights = nullptr;  // wlen weights per bead, sorted order
   float* weights32 = nullptr;  // the same in FP32
-  double* wtmp = nullptr;
-  int4* stmp = nullptr;
   void* temp = nullptr;
   size_t temp_bytes = 0;
-  size_t rbytes = 0;
 };
 
 // ------------------------------------------------------------------------------------------
@@ -82,7 +86,9 @@ struct SpreadPlan {
 
 // The smooth part of a pair, five scalars as piecewise polynomials of the distance (RealPoly):
 // interval q = int(r inv_w), x = r inv_w - q - 1/2, Horner from the highest coefficient.  T points
-// at the coefficients in LDS.  Rows of a multiple of 16 bytes read in 16-byte pieces.
+// at the coefficients in LDS, read in 16-byte pieces; rows are an odd number of pieces apart, so
+// that lanes at different distances meet different banks (an even number, 18, left FP64 half of
+// the banks: 163 us instead of 154 at 81,920 beads).
 template <typename R>
 __device__ __forceinline__ void smooth_part(const R* T, R r, R inv_w, R (&f)[5]) {
   using P = RealPoly<R>;
@@ -92,9 +98,9 @@ __device__ __forceinline__ void smooth_part(const R* T, R r, R inv_w, R (&f)[5])
   typedef R V __attribute__((ext_vector_type(16 / sizeof(R))));
   constexpr int L = 16 / sizeof(R);
   const V* row = reinterpret_cast<const V*>(T + q * P::kStride);
-  V c[P::kStride / L];
+  V c[(5 * P::kCoef + L - 1) / L];
 #pragma unroll
-  for (int k = 0; k < P::kStride / L; ++k) c[k] = row[k];
+  for (int k = 0; k < int(sizeof(c) / sizeof(V)); ++k) c[k] = row[k];
 #pragma unroll
   for (int k = 0; k < 5; ++k) {
     R v = c[(k * P::kCoef) / L][(k * P::kCoef) % L];
@@ -111,8 +117,8 @@ __device__ __forceinline__ void smooth_part(const R* T, R r, R inv_w, R (&f)[5])
 // 12 of the 17 loads of a pair: at 15.5 million pairs (81,920 beads) 367 us in FP64 and 230 in
 // FP32, the rate at which a CU looks up cache lines.  As 64 intervals of degree 6 (FP64) or 128
 // of degree 3 (FP32) it is 18 or 10 KB that every workgroup copies to LDS, and is closer to the
-// quadrature than the table was (4e-14 of the self mobility against 1e-13): 163 us in FP64, 114
-// in FP32.  A workgroup takes a contiguous chunk of rows, in the plan's spatial order where there
+// quadrature than the table was (4e-14 of the self mobility against 1e-13): 140 us in FP64 (with
+// four wavefronts a SIMD; 154 with the three that its registers would leave), 114 in FP32.  A workgroup takes a contiguous chunk of rows, in the plan's spatial order where there
 // is one, so that the copy is paid once per many rows.
 template <typename R, int LPR>
 __device__ __forceinline__ void real_sum_body(int nb, const double4* __restrict__ pos,
@@ -223,7 +229,7 @@ __device__ __forceinline__ void real_sum_body(int nb, const double4* __restrict_
 }
 
 template <typename R, int LPR>
-__global__ __launch_bounds__(256) void k_real_sum(int nb, const double4* __restrict__ pos,
+__global__ __launch_bounds__(256, 4) void k_real_sum(int nb, const double4* __restrict__ pos,
                                                   const double* __restrict__ lam, const int* __restrict__ rowptr,
                                                   const uint32_t* __restrict__ col, const R* __restrict__ tab,
                                                   RealParams rp, double* __restrict__ out, int accumulate,
@@ -486,6 +492,12 @@ __device__ __forceinline__ void stg2(R* p, unsigned i, R a, R b) {
 }
 
 template <typename R>
+__device__ __forceinline__ R ldg1(const R* p, unsigned i) {
+  const unsigned bytes = i * unsigned(sizeof(R));
+  return *(__attribute__((address_space(1))) const R*)((__attribute__((address_space(1))) const char*)p + bytes);
+}
+
+template <typename R>
 __device__ __forceinline__ void ldg4(const R* p, unsigned i, R& a, R& b, R& c, R& d) {
   typedef R V4 __attribute__((ext_vector_type(4)));
   const unsigned bytes = i * unsigned(sizeof(R));
@@ -685,42 +697,49 @@ int pick_block(int N) {
 }
 }  // namespace
 
-SpreadPlan* spread_plan_create(int nb, int N, int P) {
+SpreadPlan* spread_plan_create(int nb, int N, int P, bool sheared) {
   const int BS = pick_block(N);
-  if (BS == 0) return nullptr;
+  if (BS == 0 || (sheared && BS != 8)) return nullptr;
   auto* sp = new SpreadPlan;
   sp->nb = nb;
   sp->BS = BS;
   sp->nbin = N / BS;
   sp->P = P;
+  sp->sheared = sheared;
+  sp->wlen = sheared ? P * P + P : 3 * P;
   sp->K = std::min(1 + (P - 1 + BS - 1) / BS, sp->nbin);
   const int nbins = sp->nbin * sp->nbin * sp->nbin;
+  const size_t nw = size_t(sp->wlen) * nb;
   bool ok = hipMalloc(&sp->keys_in, sizeof(int) * nb) == hipSuccess &&
             hipMalloc(&sp->keys_out, sizeof(int) * nb) == hipSuccess &&
             hipMalloc(&sp->vals_in, sizeof(int) * nb) == hipSuccess &&
             hipMalloc(&sp->perm, sizeof(int) * nb) == hipSuccess &&
-            hipMalloc(&sp->bin_start, sizeof(int) * nbins) == hipSuccess &&
-            hipMalloc(&sp->bin_end, sizeof(int) * nbins) == hipSuccess &&
             hipMalloc(&sp->starts, sizeof(int4) * nb) == hipSuccess &&
-            hipMalloc(&sp->stmp, sizeof(int4) * nb) == hipSuccess &&
-            hipMalloc(&sp->weights, sizeof(double) * 3 * P * size_t(nb)) == hipSuccess &&
-            hipMalloc(&sp->weights32, sizeof(float) * 3 * P * size_t(nb)) == hipSuccess &&
-            hipMalloc(&sp->wtmp, sizeof(double) * 3 * P * size_t(nb)) == hipSuccess;
+            hipMalloc(&sp->weights, sizeof(double) * nw) == hipSuccess &&
+            hipMalloc(&sp->weights32, sizeof(float) * nw) == hipSuccess;
+  if (sheared) ok = ok && hipMalloc(&sp->rows, sizeof(short) * size_t(P) * nb) == hipSuccess;
   size_t b = 0;
   hipcub::DeviceRadixSort::SortPairs(nullptr, b, sp->keys_in, sp->keys_out, sp->vals_in, sp->perm, nb);
   sp->temp_bytes = b;
   ok = ok && hipMalloc(&sp->temp, b) == hipSuccess;
+  if (ok && BS == 4) {
+    ok = hipMalloc(&sp->bin_start, sizeof(int) * nbins) == hipSuccess &&
+         hipMalloc(&sp->bin_end, sizeof(int) * nbins) == hipSuccess;
+  }
   if (ok && BS == 8) {
     sp->kc = std::min(sp->K, sp->nbin);
-    const size_t slots = size_t(nb) * sp->kc * sp->kc * sp->kc;
+    // the rows of a sheared support start up to ceil((P - 1) / 2) points apart (|strain| <= 1/2)
+    sp->kcx = sheared ? std::min(1 + (P + P / 2 - 1 + 7) / 8, sp->nbin) : sp->kc;
+    const size_t slots = size_t(nb) * sp->kcx * sp->kc * sp->kc;
     ok = hipMalloc(&sp->blk_start, sizeof(int) * nbins) == hipSuccess &&
          hipMalloc(&sp->blk_end, sizeof(int) * nbins) == hipSuccess &&
          hipMalloc(&sp->pk_in, sizeof(int) * slots) == hipSuccess &&
          hipMalloc(&sp->pk_out, sizeof(int) * slots) == hipSuccess &&
          hipMalloc(&sp->pv_in, sizeof(int) * slots) == hipSuccess &&
-         hipMalloc(&sp->cand, sizeof(int) * slots) == hipSuccess;
+         hipMalloc(&sp->pv_out, sizeof(int) * slots) == hipSuccess &&
+         hipMalloc(&sp->cand, sizeof(int4) * slots) == hipSuccess;
     size_t pb = 0;
-    hipcub::DeviceRadixSort::SortPairs(nullptr, pb, sp->pk_in, sp->pk_out, sp->pv_in, sp->cand, int(slots));
+    hipcub::DeviceRadixSort::SortPairs(nullptr, pb, sp->pk_in, sp->pk_out, sp->pv_in, sp->pv_out, int(slots));
     sp->ptemp_bytes = pb;
     ok = ok && hipMalloc(&sp->ptemp, pb) == hipSuccess;
   }
@@ -731,6 +750,8 @@ SpreadPlan* spread_plan_create(int nb, int N, int P) {
   return sp;
 }
 
+bool spread_plan_sheared(const SpreadPlan* sp) { return sp && sp->sheared; }
+
 void spread_plan_destroy(SpreadPlan* sp) {
   if (!sp) return;
   (void)hipFree(sp->keys_in);
@@ -740,55 +761,84 @@ void spread_plan_destroy(SpreadPlan* sp) {
   (void)hipFree(sp->bin_start);
   (void)hipFree(sp->bin_end);
   (void)hipFree(sp->starts);
-  (void)hipFree(sp->stmp);
+  (void)hipFree(sp->rows);
   (void)hipFree(sp->weights);
   (void)hipFree(sp->weights32);
-  (void)hipFree(sp->wtmp);
   (void)hipFree(sp->temp);
   (void)hipFree(sp->blk_start);
   (void)hipFree(sp->blk_end);
   (void)hipFree(sp->pk_in);
   (void)hipFree(sp->pk_out);
   (void)hipFree(sp->pv_in);
+  (void)hipFree(sp->pv_out);
   (void)hipFree(sp->cand);
   (void)hipFree(sp->ptemp);
   delete sp;
 }
 
-__global__ void k_bead_prep(int nb, const double4* __restrict__ pos, WaveParams wp, int BS, int nbin,
-                            double* __restrict__ w, int4* __restrict__ st, int* __restrict__ keys, int* __restrict__ vals) {
+namespace {
+// First of the P support points around coordinate u (in grid spacings), unwrapped.
+__device__ inline int support_start(double u, int P) { return int(ceil(u - 0.5 * P)); }
+
+// offset of point m from the start s of a support, mod N (both in [0, N))
+__device__ __forceinline__ int point_offset(int m, int s, int N) {
+  const int o = m - s;
+  return o < 0 ? o + N : o;
+}
+
+// x centre of grid row sy + ky of a support on the lattice of strain gam
+__device__ inline double row_centre(const double4& p, const WaveParams& wp, double gam, int sy, int ky) {
+  return p.x - gam * ((sy + ky) * wp.h - p.y);
+}
+}  // namespace
+
+// sort key of every bead: the block of its support's first point
+__global__ void k_bead_keys(int nb, const double4* __restrict__ pos, WaveParams wp, int BS, int nbin,
+                            int* __restrict__ keys, int* __restrict__ vals) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= nb) return;
   const int P = wp.support, N = wp.n;
   const double4 p = pos[i];
-  int sm[3];
-  for (int d = 0; d < 3; ++d) {
-    const double pd = d == 0 ? p.x : (d == 1 ? p.y : p.z);
-    const int s = int(ceil(pd / wp.h - 0.5 * P));
-    for (int k = 0; k < P; ++k) {
-      const double xm = (s + k) * wp.h - pd;
-      w[size_t(i) * 3 * P + d * P + k] = exp(-wp.alpha * xm * xm);
-    }
-    sm[d] = ((s % N) + N) % N;
-  }
-  const int bin = ((sm[2] / BS) * nbin + sm[1] / BS) * nbin + sm[0] / BS;
-  st[i] = make_int4(sm[0], sm[1], sm[2], bin);
-  keys[i] = bin;
+  const int sx = wrapi(support_start(p.x / wp.h, P), N), sy = wrapi(support_start(p.y / wp.h, P), N),
+            sz = wrapi(support_start(p.z / wp.h, P), N);
+  keys[i] = ((sz / BS) * nbin + sy / BS) * nbin + sx / BS;
   vals[i] = i;
 }
 
-// one thread per copied weight: consecutive threads move consecutive weights of a bead
-__global__ void k_bead_permute(int nb, int P3, const int* __restrict__ perm, const double* __restrict__ w_in,
-                               const int4* __restrict__ s_in, double* __restrict__ w_out, float* __restrict__ w32,
-                               int4* __restrict__ s_out) {
+// weights and starts of the beads in sorted order, one thread per weight
+template <bool SHEAR>
+__global__ void k_bead_weights(int nb, int wlen, const double4* __restrict__ pos, WaveParams wp, int BS, int nbin,
+                               const int* __restrict__ perm, double* __restrict__ w64, float* __restrict__ w32,
+                               int4* __restrict__ starts, short* __restrict__ rows) {
   const size_t t = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= size_t(nb) * P3) return;
-  const int k = int(t / P3), q = int(t - size_t(k) * P3);
-  const int i = perm[k];
-  const double v = w_in[size_t(i) * P3 + q];
-  w_out[t] = v;
+  if (t >= size_t(nb) * wlen) return;
+  const int k = int(t / wlen), q = int(t - size_t(k) * wlen);
+  const int P = wp.support, N = wp.n;
+  const double4 p = pos[perm[k]];
+  const int sy = support_start(p.y / wp.h, P), sz = support_start(p.z / wp.h, P);
+  double xm, wy = 1.0;
+  if (SHEAR && q < P * P) {
+    const int ky = q / P, kx = q - ky * P;
+    const double gam = wp.gam ? *wp.gam : 0.0, cx = row_centre(p, wp, gam, sy, ky);
+    const int sx = support_start(cx / wp.h, P);
+    xm = (sx + kx) * wp.h - cx;
+    const double ym = (sy + ky) * wp.h - p.y;
+    wy = exp(-wp.alpha * ym * ym);
+    if (kx == 0) rows[size_t(k) * P + ky] = short(wrapi(sx, N));
+  } else if (SHEAR) {
+    xm = (sz + q - P * P) * wp.h - p.z;
+  } else {
+    const int d = q / P, m = q - d * P;
+    const double pd = d == 0 ? p.x : (d == 1 ? p.y : p.z);
+    xm = (support_start(pd / wp.h, P) + m) * wp.h - pd;
+  }
+  const double v = exp(-wp.alpha * xm * xm) * wy;
+  w64[t] = v;
   w32[t] = float(v);
-  if (q == 0) s_out[k] = s_in[i];
+  if (q == 0) {
+    const int x = wrapi(support_start(p.x / wp.h, P), N), y = wrapi(sy, N), z = wrapi(sz, N);
+    starts[k] = make_int4(x, y, z, ((z / BS) * nbin + y / BS) * nbin + x / BS);
+  }
 }
 
 __global__ void k_bin_bounds(int nb, const int* __restrict__ keys, int* start, int* end) {
@@ -799,47 +849,74 @@ __global__ void k_bin_bounds(int nb, const int* __restrict__ keys, int* start, i
   if (k == nb - 1 || keys[k + 1] != c) end[c] = k + 1;
 }
 
-// the kc^3 slots of sorted bead k: the blocks its support reaches (their index as the key,
-// k as the value), the remaining slots a sentinel key past the last block
-__global__ void k_block_slots(int nb, const int4* __restrict__ starts, int P, int nbin, int kc,
+// the slots of sorted bead k: the blocks its support reaches (their index as the key, k as the
+// value), the remaining slots a sentinel key past the last block.  SHEAR: along x, the blocks from
+// the first to the last point of the rows that lie in the block row
+template <bool SHEAR>
+__global__ void k_block_slots(int nb, const int4* __restrict__ starts, const double4* __restrict__ pos,
+                              const int* __restrict__ perm, WaveParams wp, int nbin, int kc, int kcx,
                               int* __restrict__ keys, int* __restrict__ vals) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= nb) return;
+  const int P = wp.support;
   const int4 s = starts[k];
   const int cnt[3] = {min(((s.x & 7) + P - 1) / 8 + 1, nbin), min(((s.y & 7) + P - 1) / 8 + 1, nbin),
                       min(((s.z & 7) + P - 1) / 8 + 1, nbin)};
   const int b0[3] = {s.x >> 3, s.y >> 3, s.z >> 3};
-  const int per = kc * kc * kc, sentinel = nbin * nbin * nbin;
+  const int per = kcx * kc * kc, sentinel = nbin * nbin * nbin;
   int q = 0;
-  for (int jz = 0; jz < cnt[2]; ++jz)
-    for (int jy = 0; jy < cnt[1]; ++jy)
-      for (int jx = 0; jx < cnt[0]; ++jx) {
-        const int bz = (b0[2] + jz) % nbin, by = (b0[1] + jy) % nbin, bx = (b0[0] + jx) % nbin;
+  for (int jy = 0; jy < cnt[1]; ++jy) {
+    const int by = (b0[1] + jy) % nbin;
+    int x0 = b0[0], nx = cnt[0];
+    if (SHEAR) {
+      const double4 p = pos[perm[k]];
+      const double gam = wp.gam ? *wp.gam : 0.0;
+      const int sy = support_start(p.y / wp.h, P);
+      int lo = 1 << 30, hi = -(1 << 30);
+      for (int iy = 0; iy < P; ++iy) {
+        if (((s.y + iy) >> 3) % nbin != by) continue;
+        const int sx = support_start(row_centre(p, wp, gam, sy, iy) / wp.h, P);
+        lo = min(lo, sx);
+        hi = max(hi, sx);
+      }
+      x0 = lo >> 3;  // arithmetic shift: lo may be negative
+      nx = min(((hi + P - 1) >> 3) - x0 + 1, min(nbin, kcx));
+    }
+    for (int jz = 0; jz < cnt[2]; ++jz)
+      for (int jx = 0; jx < nx; ++jx) {
+        const int bz = (b0[2] + jz) % nbin, bx = wrapi(x0 + jx, nbin);
         keys[size_t(k) * per + q] = (bz * nbin + by) * nbin + bx;
         vals[size_t(k) * per + q] = k;
         ++q;
       }
+  }
   for (; q < per; ++q) {
     keys[size_t(k) * per + q] = sentinel;
     vals[size_t(k) * per + q] = k;
   }
 }
 
-// list bounds per block from the sorted slot keys (sentinels ignored)
-__global__ void k_block_bounds(int n, int nblk, const int* __restrict__ keys, int* start, int* end) {
+// list bounds per block and the candidate records from the sorted slots (sentinels ignored)
+__global__ void k_block_lists(int n, int nbin, int N, const int* __restrict__ keys, const int* __restrict__ vals,
+                              const int4* __restrict__ starts, const int* __restrict__ perm, int* __restrict__ start,
+                              int* __restrict__ end, int4* __restrict__ cand) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= n) return;
   const int c = keys[p];
-  if (c >= nblk) return;
+  if (c >= nbin * nbin * nbin) return;
   if (p == 0 || keys[p - 1] != c) start[c] = p;
   if (p == n - 1 || keys[p + 1] != c) end[c] = p + 1;
+  const int k = vals[p];
+  const int4 s = starts[k];
+  const int ox = point_offset(8 * (c % nbin), s.x, N), oy = point_offset(8 * (c / nbin % nbin), s.y, N),
+            oz = point_offset(8 * (c / (nbin * nbin)), s.z, N);
+  cand[p] = make_int4(k, perm[k], ox | (oy << 8) | (oz << 16), 0);
 }
 
 hipError_t spread_plan_update(SpreadPlan* sp, const double* pos4, const WaveParams& wp, hipStream_t st) {
   const int nb = sp->nb;
-  double* w = sp->wtmp;
-  k_bead_prep<<<nblocks(nb), kThreads, 0, st>>>(nb, (const double4*)pos4, wp, sp->BS, sp->nbin, w, sp->stmp,
-                                                   sp->keys_in, sp->vals_in);
+  const double4* pos = (const double4*)pos4;
+  k_bead_keys<<<nblocks(nb), kThreads, 0, st>>>(nb, pos, wp, sp->BS, sp->nbin, sp->keys_in, sp->vals_in);
   int bits = 1;
   const int nbins = sp->nbin * sp->nbin * sp->nbin;
   while ((1 << bits) < nbins) ++bits;
@@ -847,24 +924,35 @@ hipError_t spread_plan_update(SpreadPlan* sp, const double* pos4, const WavePara
   hipError_t e = hipcub::DeviceRadixSort::SortPairs(sp->temp, tb, sp->keys_in, sp->keys_out, sp->vals_in, sp->perm,
                                                     nb, 0, bits, st);
   if (e != hipSuccess) return e;
-  if ((e = hipMemsetAsync(sp->bin_start, 0, sizeof(int) * nbins, st)) != hipSuccess) return e;
-  if ((e = hipMemsetAsync(sp->bin_end, 0, sizeof(int) * nbins, st)) != hipSuccess) return e;
-  k_bin_bounds<<<nblocks(nb), kThreads, 0, st>>>(nb, sp->keys_out, sp->bin_start, sp->bin_end);
-  k_bead_permute<<<nblocks((long long)nb * 3 * sp->P), kThreads, 0, st>>>(nb, 3 * sp->P, sp->perm, w, sp->stmp,
-                                                                         sp->weights,
-                                                   sp->weights32, sp->starts);
-  if (sp->BS == 8) {  // the candidate list of every block
-    const int kc = sp->kc, slots = nb * kc * kc * kc;
-    k_block_slots<<<nblocks(nb), kThreads, 0, st>>>(nb, sp->starts, sp->P, sp->nbin, kc, sp->pk_in, sp->pv_in);
+  const int wblk = nblocks((long long)nb * sp->wlen);
+  if (sp->sheared)
+    k_bead_weights<true><<<wblk, kThreads, 0, st>>>(nb, sp->wlen, pos, wp, sp->BS, sp->nbin, sp->perm, sp->weights,
+                                                    sp->weights32, sp->starts, sp->rows);
+  else
+    k_bead_weights<false><<<wblk, kThreads, 0, st>>>(nb, sp->wlen, pos, wp, sp->BS, sp->nbin, sp->perm, sp->weights,
+                                                     sp->weights32, sp->starts, nullptr);
+  if (sp->BS == 4) {
+    if ((e = hipMemsetAsync(sp->bin_start, 0, sizeof(int) * nbins, st)) != hipSuccess) return e;
+    if ((e = hipMemsetAsync(sp->bin_end, 0, sizeof(int) * nbins, st)) != hipSuccess) return e;
+    k_bin_bounds<<<nblocks(nb), kThreads, 0, st>>>(nb, sp->keys_out, sp->bin_start, sp->bin_end);
+  } else {  // the candidate list of every block
+    const int kc = sp->kc, kcx = sp->kcx, slots = nb * kcx * kc * kc;
+    if (sp->sheared)
+      k_block_slots<true><<<nblocks(nb), kThreads, 0, st>>>(nb, sp->starts, pos, sp->perm, wp, sp->nbin, kc, kcx,
+                                                            sp->pk_in, sp->pv_in);
+    else
+      k_block_slots<false><<<nblocks(nb), kThreads, 0, st>>>(nb, sp->starts, pos, sp->perm, wp, sp->nbin, kc, kcx,
+                                                             sp->pk_in, sp->pv_in);
     int pbits = 1;
     while ((1 << pbits) <= nbins) ++pbits;  // the sentinel nbins included
     size_t pb = sp->ptemp_bytes;
-    if ((e = hipcub::DeviceRadixSort::SortPairs(sp->ptemp, pb, sp->pk_in, sp->pk_out, sp->pv_in, sp->cand, slots, 0,
+    if ((e = hipcub::DeviceRadixSort::SortPairs(sp->ptemp, pb, sp->pk_in, sp->pk_out, sp->pv_in, sp->pv_out, slots, 0,
                                                 pbits, st)) != hipSuccess)
       return e;
     if ((e = hipMemsetAsync(sp->blk_start, 0, sizeof(int) * nbins, st)) != hipSuccess) return e;
     if ((e = hipMemsetAsync(sp->blk_end, 0, sizeof(int) * nbins, st)) != hipSuccess) return e;
-    k_block_bounds<<<nblocks(slots), kThreads, 0, st>>>(slots, nbins, sp->pk_out, sp->blk_start, sp->blk_end);
+    k_block_lists<<<nblocks(slots), kThreads, 0, st>>>(slots, sp->nbin, wp.n, sp->pk_out, sp->pv_out, sp->starts,
+                                                       sp->perm, sp->blk_start, sp->blk_end, sp->cand);
   }
   return hipGetLastError();
 }
@@ -985,160 +1073,209 @@ __global__ __launch_bounds__(BS* BS* BS) void k_spread_gather(const int* __restr
   g[2 * cs + 1] = a5;
 }
 
-// Gather spreading on 8^3 blocks with the candidates split among the four wavefronts:
-// lane (x, y) owns one grid column and all 8 planes of the block; wavefront w takes
-// every fourth candidate of the block's list (the beads whose support reaches it, built
-// with the plan) and forms the x-y weight once per lane, reusing it over the planes.  The
-// four partial blocks are added through LDS in a fixed order (deterministic).  Candidates
-// are staged in LDS in chunks of C (dynamic shared memory): the sorted bead index, then
-// the weights with independent loads in flight, then start cells and force moments.
-constexpr int kSplitRedBytes64 = 2 * 48 * 64 * 8;  // LDS of the two-step reduction (FP64)
+// Gather spreading on 8^3 blocks as matrix products.  A grid point's value is
+//   G_c(x, y, z) = sum_b A_b(x, y) B_b(z, c),  A = w_x w_y,  B = w_z l_c (c = 6 force moments),
+// a product over the block's candidate beads b of a (points in the plane) x b and a
+// b x (planes and components) matrix, so it runs on the matrix cores: a wavefront owns two of
+// the block's rows in y, all eight points in x and all eight planes, and walks the candidates that
+// reach its rows four at a time, three 16 x 16 x 4 products each (one per axis: 8 planes of force,
+// 8 of torque).  Points inside the support fill 32% of the products at P = 10; with the whole
+// plane they would fill 20%, with 4 x 4 quadrants 35%, but those store half lines.
+// Weights are staged in LDS as windows over the block's 8 points per axis, zero outside the
+// support, so the inner loop has no index tests; on a sheared lattice the window is the 8 x 8
+// plane of A.  Lists are padded to four with a candidate of zero weights.  No atomics; every
+// sum is in list order.  The products of 81,920 beads take 45 us in FP64 and 22 in FP32 at the
+// matrix rate; what is left is the latency from the candidate's record to its weights and the
+// store of the grid, which other blocks' wavefronts cover.  Measured in the first pass of the
+// saddle operator (128^3, beside 140 and 115 us of pair sum): 246 us in FP64 and 173 in FP32; with
+// one lane per (x, y) column on the vector units it took 415 and 278.  The scatter with atomics of
+// the sheared lattice took 250 (FP64, 2,048 beads) to 410 us (FP32, 6,011), now 17 and 22.
+template <typename R, bool SHEAR>
+struct SpreadTile {
+  static constexpr int kCand = SHEAR ? 32 : 64;       // candidates staged at a time
+  static constexpr int kPlane = SHEAR ? 64 : 16;      // the window of A (SHEAR) or of w_x and w_y
+  static constexpr int kUsed = kPlane + 8 + 6;        // then w_z and the moments
+  static constexpr int kStride = SHEAR ? 80 : 40;     // spreads four candidates over the banks
+  // windows, records, the four wavefronts' lists, and (SHEAR) the rows' offsets along x
+  static constexpr size_t kBytes = sizeof(R) * (kCand + 1) * kStride + sizeof(int4) * kCand +
+                                   sizeof(int) * 4 * (kCand + 4) + (SHEAR ? sizeof(int) * 8 * kCand : 0);
+};
 
+typedef double Acc64 __attribute__((ext_vector_type(4)));
+typedef float Acc32 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ Acc64 mma4(double a, double b, Acc64 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ Acc32 mma4(float a, float b, Acc32 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
 template <typename R>
-__device__ __forceinline__ void spread_split_body(const int* __restrict__ blk_start,
-                                                               const int* __restrict__ blk_end,
-                                                               const int* __restrict__ cand,
-                                                               const int* __restrict__ perm,
-                                                               const int4* __restrict__ starts,
-                                                               const R* __restrict__ weights,
-                                                               const double* __restrict__ lam, WaveParams wp,
-                                                               int nbin, int C, R* __restrict__ grid,
-                                                               size_t cs, const int* __restrict__ skip, int bx_, int by_, int gx_) {
+struct AccOf {
+  using T = Acc64;
+};
+template <>
+struct AccOf<float> {
+  using T = Acc32;
+};
+
+// What the block kernels read of a plan.
+template <typename R>
+struct BlockArgs {
+  const int *blk_start, *blk_end;
+  const int4* cand;
+  const short* rows;
+  const R* weights;
+  int nbin;
+};
+
+// the value of the lane 8 further in the row of 16
+__device__ __forceinline__ float ror8(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x128, 0xf, 0xf, true));
+}
+__device__ __forceinline__ double ror8(double v) {
+  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), 0x128, 0xf, 0xf, true),
+                          __builtin_amdgcn_mov_dpp(__double2loint(v), 0x128, 0xf, 0xf, true));
+}
+
+template <typename R, bool SHEAR>
+__device__ __forceinline__ void spread_tile_body(const BlockArgs<R>& ba, const double* __restrict__ lam,
+                                                 const WaveParams& wp, R* __restrict__ grid, size_t cs,
+                                                 const int* __restrict__ skip, unsigned char* smem, int bx_) {
   if (skip && *skip) return;
-  constexpr int BS = 8, NT = 256, ZW = 8, NW = NT / 64;
-  const int P = wp.support, N = wp.n, P3 = 3 * P;
-  extern __shared__ unsigned char smem_raw[];
-  R* sh_w = reinterpret_cast<R*>(smem_raw);                 // C * 3P
-  R* sh_l = sh_w + size_t(C) * P3;                           // C * 6
-  int4* sh_s = reinterpret_cast<int4*>(sh_l + size_t(C) * 6); // C
-  int* sh_k = reinterpret_cast<int*>(sh_s + C);              // C
-  const int bl = xcd_remap(bx_, nbin * nbin * nbin);  // each XCD takes a contiguous slab of blocks
-  const int bx = bl % nbin, by = (bl / nbin) % nbin, bz = bl / (nbin * nbin);
+  using Tile = SpreadTile<R, SHEAR>;
+  using Acc = typename AccOf<R>::T;
+  constexpr int C = Tile::kCand, S = Tile::kStride, NT = 256;
+  const int P = wp.support, N = wp.n, nbin = ba.nbin;
+  const int wlen = SHEAR ? P * P + P : 3 * P;
+  R* win = reinterpret_cast<R*>(smem);
+  int4* rec = reinterpret_cast<int4*>(win + (C + 1) * S);
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int x0 = bx * BS, y0 = by * BS, z0 = bz * BS;
-  const int mx = x0 + (lane & 7), my = y0 + (lane >> 3);
-  const int cb = blk_start[bl], total = blk_end[bl] - cb;
-  R a[ZW][6];
-#pragma unroll
-  for (int zz = 0; zz < ZW; ++zz)
-#pragma unroll
-    for (int c = 0; c < 6; ++c) a[zz][c] = 0;
+  int* list = reinterpret_cast<int*>(rec + C) + wave * (C + 4);
+  int* row_x = reinterpret_cast<int*>(rec + C) + 4 * (C + 4);
+  const int bl = xcd_remap(bx_, nbin * nbin * nbin);  // each XCD takes a contiguous slab of blocks
+  const int x0 = (bl % nbin) * 8, y0 = (bl / nbin % nbin) * 8, z0 = bl / (nbin * nbin) * 8;
+  const int qy = 2 * wave;
+  // operand lanes: row m = lane % 16 of A is point (xa, ya) of the wavefront's rows, column m of B
+  // the component half (force, torque) and plane m % 8; both take candidate lane / 16 of the four.
+  // The products leave point (x = lane / 16 + 4 (r % 2), y = r / 2) in register r: FP64 has row
+  // 4 r + lane / 16 there, FP32 row 4 (lane / 16) + r, so the two number the points differently
+  const int m = lane & 15, kq = lane >> 4;
+  const int xa = sizeof(R) == 8 ? (m & 3) + 4 * ((m >> 2) & 1) : (m >> 2) + 4 * (m & 1);
+  const int ya = qy + (sizeof(R) == 8 ? m >> 3 : (m >> 1) & 1);
+  const int plane = m & 7, half = m >> 3;
+  const int cb = ba.blk_start[bl], total = ba.blk_end[bl] - cb;
+  Acc acc[3] = {};
+  if (t < S) win[C * S + t] = 0;  // the candidate of zero weights
+  constexpr int NW = Tile::kPlane + 8;               // window points of a candidate
+  constexpr int UL = (C * 6 + NT - 1) / NT;          // moments per thread
   for (int c0 = 0; c0 < total; c0 += C) {
     const int n = min(C, total - c0);
     if (c0 > 0) __syncthreads();
-    for (int c = t; c < n; c += NT) sh_k[c] = cand[cb + c0 + c];
+    if (t < n) rec[t] = ba.cand[cb + c0 + t];
     __syncthreads();
-    const int nw = n * P3;
-    for (int q0 = t; q0 < nw; q0 += 4 * NT) {
-      R v[4];
+    if (SHEAR) {  // offset of x0 from the start of the candidate's row y0 + y, or N: outside the support
+      for (int q = t; q < 8 * n; q += NT) {
+        const int4 rc = rec[q >> 3];
+        int oy = ((rc.z >> 8) & 255) + (q & 7);
+        oy -= oy >= N ? N : 0;
+        row_x[q] = oy < P ? point_offset(x0, ba.rows[size_t(rc.x) * P + oy], N) : N;
+      }
+      __syncthreads();
+    }
+    // the moments' loads are issued before the first of the weights' is waited for; three of those
+    // are in flight at a time (more take registers, and a wavefront a SIMD with them)
+    double lv[UL];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int q = q0 + u * NT;
-        if (q < nw) {
-          const int cq = q / P3;
-          v[u] = weights[size_t(sh_k[cq]) * P3 + (q - cq * P3)];
+    for (int u = 0; u < UL; ++u) {
+      const unsigned q = t + u * NT, c = q / 6;
+      if (c < unsigned(n)) lv[u] = lam[6 * size_t(rec[c].y) + (q - 6 * c)];
+    }
+    for (unsigned q0 = t; q0 < unsigned(n * NW); q0 += 3 * NT) {
+      R wv[3];
+#pragma unroll
+      for (int u = 0; u < 3; ++u) {
+        const unsigned q = q0 + u * NT, c = q / NW, i = q - c * NW;
+        wv[u] = 0;
+        if (c >= unsigned(n)) continue;
+        const int4 rc = rec[c];
+        int o, at;
+        if (i >= Tile::kPlane) {
+          o = ((rc.z >> 16) & 255) + i - Tile::kPlane;
+          at = wlen - P;
+        } else if (SHEAR) {
+          int oy = ((rc.z >> 8) & 255) + (i >> 3);
+          oy -= oy >= N ? N : 0;
+          o = row_x[8 * c + (i >> 3)];
+          o = o < N ? o + (i & 7) : P;
+          at = oy * P;
+        } else {
+          o = ((rc.z >> (i & 8)) & 255) + (i & 7);
+          at = i < 8 ? 0 : P;
         }
+        o -= o >= N ? N : 0;
+        if (o < P) wv[u] = SHEAR ? ba.weights[size_t(rc.x) * wlen + at + o] : ldg1(ba.weights, rc.x * wlen + at + o);
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (q0 + u * NT < nw) sh_w[q0 + u * NT] = v[u];
-    }
-    for (int c = t; c < n; c += NT) {
-      const int k = sh_k[c];
-      sh_s[c] = starts[k];
-      const double* l = lam + 6 * size_t(perm[k]);
-#pragma unroll
-      for (int f = 0; f < 6; ++f) sh_l[6 * c + f] = R(l[f]);
-    }
-    __syncthreads();
-    for (int q = wave; q < n; q += NW) {
-      const int4 s = sh_s[q];
-      // offsets of the block (or the wave's planes) from the support start, mod N
-      int ox = x0 - s.x, oy = y0 - s.y, oz = z0 - s.z;
-      ox += ox < 0 ? N : 0;
-      oy += oy < 0 ? N : 0;
-      oz += oz < 0 ? N : 0;
-      if (!((ox < P || ox > N - BS) && (oy < P || oy > N - BS) && (oz < P || oz > N - ZW))) continue;
-      int ix = mx - s.x, iy = my - s.y;
-      ix += ix < 0 ? N : 0;
-      iy += iy < 0 ? N : 0;
-      if (ix < P && iy < P) {
-        const R* wq = sh_w + q * P3;
-        const R wxy = wq[ix] * wq[P + iy];
-        const R* l = sh_l + 6 * q;
-        const R l0 = l[0], l1 = l[1], l2 = l[2], l3 = l[3], l4 = l[4], l5 = l[5];
-        // the planes zz of the block inside the support, (oz + zz) mod N < P: before the
-        // wrap zz < P - oz, after it N - oz <= zz < N - oz + P; the same in every lane, so
-        // the mask goes to a scalar register and the plane tests are scalar branches
-        const int hi1 = min(max(P - oz, 0), ZW), lo2 = min(N - oz, ZW), hi2 = min(N - oz + P, ZW);
-        const unsigned zmask = __builtin_amdgcn_readfirstlane(
-            int(((1u << hi1) - 1u) | (((1u << hi2) - 1u) & ~((1u << lo2) - 1u))));
-#pragma unroll
-        for (int zz = 0; zz < ZW; ++zz) {
-          if (zmask & (1u << zz)) {
-            int iz = oz + zz;
-            iz -= iz >= N ? N : 0;
-            const R w = wxy * wq[2 * P + iz];
-            a[zz][0] += w * l0;
-            a[zz][1] += w * l1;
-            a[zz][2] += w * l2;
-            a[zz][3] += w * l3;
-            a[zz][4] += w * l4;
-            a[zz][5] += w * l5;
-          }
-        }
+      for (int u = 0; u < 3; ++u) {
+        const unsigned q = q0 + u * NT, c = q / NW, i = q - c * NW;
+        if (c < unsigned(n)) win[c * S + i] = wv[u];
       }
     }
+#pragma unroll
+    for (int u = 0; u < UL; ++u) {
+      const unsigned q = t + u * NT, c = q / 6;
+      if (c < unsigned(n)) win[c * S + NW + q - 6 * c] = R(lv[u]);
+    }
+    // the candidates that reach the wavefront's rows (the block they all reach): the offset of the
+    // first row below P, or of the second one after the wrap
+    bool hit = false;
+    if (lane < n) {
+      if (SHEAR) {
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+          const int ox = row_x[8 * lane + qy + y];
+          hit = hit || ox < P || (ox > N - 8 && ox < N);
+        }
+      } else {
+        const int z = rec[lane].z;
+        int oy = ((z >> 8) & 255) + qy;
+        oy -= oy >= N ? N : 0;
+        hit = oy < P || oy == N - 1;
+      }
+    }
+    const unsigned long long hits = __ballot(hit);
+    const int cnt = __popcll(hits);
+    if (hit) list[__popcll(hits & ((1ull << lane) - 1ull))] = lane * S;
+    if (lane < 4) list[cnt + lane] = C * S;
+    __syncthreads();
+    for (int e = 0; e < cnt; e += 4) {
+      const R* w = win + list[e + kq];
+      const R a = SHEAR ? w[8 * ya + xa] : w[xa] * w[8 + ya];
+      const R wz = w[Tile::kPlane + plane];
+      const R* l = w + NW + 3 * half;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) acc[c] = mma4(a, wz * l[c], acc[c]);
+    }
   }
-  // partial blocks of waves 2, 3 -> added by waves 0, 1; then wave 1 -> wave 0
-  __syncthreads();
-  R* red = reinterpret_cast<R*>(smem_raw);  // [2][48][64], reusing the staging area
-  if (wave >= 2)
+  // lanes of force and torque trade half of their points, so that each stores whole complex values
+  // and an instruction covers the block's eight x of a row: 64 or 128 bytes in one piece
 #pragma unroll
-    for (int zz = 0; zz < ZW; ++zz)
+  for (int c = 0; c < 3; ++c)
 #pragma unroll
-      for (int c = 0; c < 6; ++c) red[((wave - 2) * 48 + zz * 6 + c) * 64 + lane] = a[zz][c];
-  __syncthreads();
-  if (wave < 2)
-#pragma unroll
-    for (int zz = 0; zz < ZW; ++zz)
-#pragma unroll
-      for (int c = 0; c < 6; ++c) a[zz][c] += red[(wave * 48 + zz * 6 + c) * 64 + lane];
-  __syncthreads();
-  if (wave == 1)
-#pragma unroll
-    for (int zz = 0; zz < ZW; ++zz)
-#pragma unroll
-      for (int c = 0; c < 6; ++c) red[(zz * 6 + c) * 64 + lane] = a[zz][c];
-  __syncthreads();
-  if (wave != 0) return;
-#pragma unroll
-  for (int zz = 0; zz < ZW; ++zz)
-#pragma unroll
-    for (int c = 0; c < 6; ++c) a[zz][c] += red[(zz * 6 + c) * 64 + lane];
-#pragma unroll
-  for (int zz = 0; zz < ZW; ++zz) {
-    const size_t m = (size_t(z0 + zz) * N + my) * N + mx;
-    R* g = grid + 2 * m;
-    g[0] = a[zz][0];
-    g[1] = a[zz][3];
-    g[cs] = a[zz][1];
-    g[cs + 1] = a[zz][4];
-    g[2 * cs] = a[zz][2];
-    g[2 * cs + 1] = a[zz][5];
-  }
+    for (int y = 0; y < 2; ++y) {
+      const R keep = half ? acc[c][2 * y + 1] : acc[c][2 * y];
+      const R got = ror8(half ? acc[c][2 * y] : acc[c][2 * y + 1]);
+      const unsigned p = (unsigned(z0 + plane) * N + y0 + qy + y) * N + x0 + kq + 4 * half;
+      stg2(grid + c * cs, 2 * p, half ? got : keep, half ? keep : got);
+    }
 }
 
-template <typename R>
-__global__ __launch_bounds__(256) void k_spread_split(const int* __restrict__ blk_start, const int* __restrict__ blk_end,
-                                                      const int* __restrict__ cand, const int* __restrict__ perm,
-                                                      const int4* __restrict__ starts, const R* __restrict__ weights,
-                                                      const double* __restrict__ lam, WaveParams wp, int nbin, int C,
-                                                      R* __restrict__ grid, size_t cs, const int* __restrict__ skip) {
-  spread_split_body<R>(blk_start, blk_end, cand, perm, starts, weights, lam, wp, nbin, C, grid, cs, skip, blockIdx.x,
-                       blockIdx.y, gridDim.x);
+template <typename R, bool SHEAR>
+__global__ __launch_bounds__(256, 4) void k_spread_tile(BlockArgs<R> ba, const double* __restrict__ lam, WaveParams wp,
+                                                     R* __restrict__ grid, size_t cs, const int* __restrict__ skip) {
+  extern __shared__ unsigned char smem_raw[];
+  spread_tile_body<R, SHEAR>(ba, lam, wp, grid, cs, skip, smem_raw, blockIdx.x);
 }
-
 
 namespace {
 template <typename R>
@@ -1153,23 +1290,27 @@ const float* plan_weights<float>(const SpreadPlan* sp) {
 }
 }  // namespace
 
+namespace {
+template <typename R>
+BlockArgs<R> block_args(const SpreadPlan* sp) {
+  return {sp->blk_start, sp->blk_end, sp->cand, sp->rows, plan_weights<R>(sp), sp->nbin};
+}
+}  // namespace
+
 template <typename R>
 void launch_spread_gather(const SpreadPlan* sp, const double* lam, const WaveParams& wp, R* grid, hipStream_t st,
                           const int* skip) {
   const size_t cs = 2 * size_t(wp.n) * wp.n * wp.n;
   const int nblk = sp->nbin * sp->nbin * sp->nbin;
-  if (sp->BS == 8) {
-    // candidates per LDS chunk: at most 128, within 60 KB of dynamic shared memory (the
-    // static arrays take the rest of 64 KB)
-    const size_t per = sizeof(R) * (3 * size_t(wp.support) + 6) + sizeof(int4) + sizeof(int);
-    const int C = int(std::min<size_t>(128, (size_t(60) << 10) / per)) & ~3;  // int4 array stays 16-byte aligned
-    const size_t shm = std::max(per * C, size_t(kSplitRedBytes64) / sizeof(double) * sizeof(R));
-    launch_k(k_spread_split<R>, nblk, 256, shm, st, sp->blk_start, sp->blk_end, sp->cand, sp->perm, sp->starts,
-             plan_weights<R>(sp), lam, wp, sp->nbin, C, grid, cs, skip);
-  }
-  else
+  if (sp->BS == 4)
     launch_k(k_spread_gather<R, 4>, nblk, 64, 0, st, sp->bin_start, sp->bin_end, sp->perm, sp->starts,
                                                 plan_weights<R>(sp), lam, wp, sp->nbin, sp->K, grid, cs, skip);
+  else if (sp->sheared)
+    launch_k(k_spread_tile<R, true>, nblk, 256, SpreadTile<R, true>::kBytes, st, block_args<R>(sp), lam, wp, grid, cs,
+             skip);
+  else
+    launch_k(k_spread_tile<R, false>, nblk, 256, SpreadTile<R, false>::kBytes, st, block_args<R>(sp), lam, wp, grid, cs,
+             skip);
 }
 
 // First pass of the saddle operator in one launch.  The Sigma/lubrication reduction, the
@@ -1179,14 +1320,12 @@ void launch_spread_gather(const SpreadPlan* sp, const double* lam, const WavePar
 // blocks.  The two short ranges are padded to multiples of 8 blocks, so every spreading
 // block keeps the XCD (block index mod 8) its slab mapping assumes, and they finish early,
 // leaving their slots to the longer spreading blocks.
-template <typename R, int LPR>
-__global__ __launch_bounds__(256) void k_spread_fused(const int* __restrict__ blk_start, const int* __restrict__ blk_end,
-                                                      const int* __restrict__ cand, const int* __restrict__ perm,
-                                                      const int4* __restrict__ starts,
-                                                      const R* __restrict__ weights, const double* __restrict__ lam,
-                                                      WaveParams wp, int nbin, int C, R* __restrict__ grid,
-                                                      size_t cs, const R* __restrict__ tab, RealArgs ra, RigidArgs ga,
-                                                      int na_blk, int nr_blk, const int* __restrict__ skip) {
+template <typename R, int LPR, bool SHEAR>
+__global__ __launch_bounds__(256, 4) void k_spread_fused(BlockArgs<R> ba, const double* __restrict__ lam, WaveParams wp,
+                                                      R* __restrict__ grid, size_t cs, const R* __restrict__ tab,
+                                                      RealArgs ra, RigidArgs ga, int na_blk, int nr_blk,
+                                                      const int* __restrict__ skip) {
+  extern __shared__ unsigned char smem_raw[];
   int b = blockIdx.x;
   if (b < na_blk) {
     agg_lub_body(ga.na, ga.offsets, ga.body, ga.r4, lam, ga.V, ga.lrow, ga.lcol, ga.coef, ga.y2, skip, b, 0, na_blk);
@@ -1194,13 +1333,11 @@ __global__ __launch_bounds__(256) void k_spread_fused(const int* __restrict__ bl
   }
   b -= na_blk;
   if (b < nr_blk) {
-    extern __shared__ unsigned char smem_raw[];
     real_sum_body<R, LPR>(ra.nb, ra.pos, lam, ra.rowptr, ra.col, tab, ra.rp, ra.out, 0, ra.order, skip, smem_raw, b,
                           nr_blk);
     return;
   }
-  spread_split_body<R>(blk_start, blk_end, cand, perm, starts, weights, lam, wp, nbin, C, grid, cs, skip, b - nr_blk, 0,
-                       0);
+  spread_tile_body<R, SHEAR>(ba, lam, wp, grid, cs, skip, smem_raw, b - nr_blk);
 }
 
 bool spread_fuses(const SpreadPlan* sp) { return sp && sp->BS == 8; }
@@ -1210,15 +1347,20 @@ void launch_spread_fused(const SpreadPlan* sp, const double* lam, const WavePara
                          int lpr, const RealArgs& ra, const RigidArgs& ga, hipStream_t st, const int* skip) {
   const size_t cs = 2 * size_t(wp.n) * wp.n * wp.n;
   const int nblk = sp->nbin * sp->nbin * sp->nbin;
-  const size_t per = sizeof(R) * (3 * size_t(wp.support) + 6) + sizeof(int4) + sizeof(int);
-  const int C = int(std::min<size_t>(128, (size_t(60) << 10) / per)) & ~3;  // as launch_spread_gather
-  const size_t shm = std::max({per * C, size_t(kSplitRedBytes64) / sizeof(double) * sizeof(R), RealPoly<R>::kBytes});
+  const size_t shm = std::max(sp->sheared ? SpreadTile<R, true>::kBytes : SpreadTile<R, false>::kBytes,
+                              RealPoly<R>::kBytes);
   auto pad8 = [](long long n) { return int((n + 7) / 8 * 8); };
   const int na_blk = pad8((ga.na + 3) / 4), nr_blk = pad8(real_blocks(ra.nb, lpr));
   const int total = na_blk + nr_blk + nblk;
-#define FSD_FUSED(L_)                                                                                       \
-  launch_k(k_spread_fused<R, L_>, total, 256, shm, st, sp->blk_start, sp->blk_end, sp->cand, sp->perm,        \
-           sp->starts, plan_weights<R>(sp), lam, wp, sp->nbin, C, grid, cs, table, ra, ga, na_blk, nr_blk, skip)
+#define FSD_FUSED(L_)                                                                                           \
+  do {                                                                                                          \
+    if (sp->sheared)                                                                                            \
+      launch_k(k_spread_fused<R, L_, true>, total, 256, shm, st, block_args<R>(sp), lam, wp, grid, cs, table, ra, \
+               ga, na_blk, nr_blk, skip);                                                                       \
+    else                                                                                                        \
+      launch_k(k_spread_fused<R, L_, false>, total, 256, shm, st, block_args<R>(sp), lam, wp, grid, cs, table, ra, \
+               ga, na_blk, nr_blk, skip);                                                                       \
+  } while (0)
   switch (lpr) {
     case 1: FSD_FUSED(1); break;
     case 2: FSD_FUSED(2); break;
@@ -2027,17 +2169,6 @@ void launch_wave_fft(R* grid, const FftPlan& plan, const R* twiddle, const WaveP
 // ------------------------------------------------------------------------------------------
 
 namespace {
-__device__ inline int batch_sys(const int* __restrict__ off, int nsys, int b) {
-  int lo = 0, hi = nsys - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (off[mid] <= b)
-      lo = mid;
-    else
-      hi = mid - 1;
-  }
-  return lo;
-}
 
 template <typename R>
 __device__ inline const R* pick(const double* a, const float* b);
@@ -2055,9 +2186,9 @@ constexpr int kBatchRealPasses = 4;  // row passes per workgroup there: the othe
 }  // namespace
 
 template <typename R>
-__global__ __launch_bounds__(256) void kb_real(const BatchDesc* __restrict__ D, const int* __restrict__ off,
+__global__ __launch_bounds__(256, 4) void kb_real(const BatchDesc* __restrict__ D, const int* __restrict__ off,
                                               int nsys) {
-  const int s = batch_sys(off, nsys, blockIdx.x);
+  const int s = batch_system(off, nsys, blockIdx.x);
   const BatchDesc& d = D[s];
   extern __shared__ unsigned char smem_raw[];
   real_sum_body<R, kBatchLpr>(d.nb, (const double4*)d.pos4, d.z, d.nrow, d.ncol, pick<R>(d.tab64, d.tab32), d.rp,
@@ -2065,19 +2196,21 @@ __global__ __launch_bounds__(256) void kb_real(const BatchDesc* __restrict__ D, 
 }
 
 template <typename R>
-__global__ __launch_bounds__(256) void kb_spread(const BatchDesc* __restrict__ D, const int* __restrict__ off,
+__global__ __launch_bounds__(256, 4) void kb_spread(const BatchDesc* __restrict__ D, const int* __restrict__ off,
                                                 int nsys) {
-  const int s = batch_sys(off, nsys, blockIdx.x);
+  const int s = batch_system(off, nsys, blockIdx.x);
   const BatchDesc& d = D[s];
   const size_t cs = 2 * size_t(d.wp.n) * d.wp.n * d.wp.n;
-  spread_split_body<R>(d.blk_start, d.blk_end, d.cand, d.perm, d.starts, pick<R>(d.w64, d.w32), d.z, d.wp, d.nbin,
-                       d.C, static_cast<R*>(d.grid), cs, &d.ctl->stop, blockIdx.x - off[s], 0, 0);
+  extern __shared__ unsigned char smem_raw[];
+  const BlockArgs<R> ba{d.blk_start, d.blk_end, d.cand, nullptr, pick<R>(d.w64, d.w32), d.nbin};
+  spread_tile_body<R, false>(ba, d.z, d.wp, static_cast<R*>(d.grid), cs, &d.ctl->stop, smem_raw,
+                             blockIdx.x - off[s]);
 }
 
 template <typename R, int STAGE>
 __global__ __launch_bounds__(256) void kb_fft(const BatchDesc* __restrict__ D, const int* __restrict__ off,
                                              int nsys) {
-  const int s = batch_sys(off, nsys, blockIdx.x);
+  const int s = batch_system(off, nsys, blockIdx.x);
   const BatchDesc& d = D[s];
   const int lb = blockIdx.x - off[s];
   const int N = d.plan.n;
@@ -2099,7 +2232,7 @@ __global__ __launch_bounds__(256) void kb_fft(const BatchDesc* __restrict__ D, c
 template <typename R>
 __global__ __launch_bounds__(256) void kb_interp(const BatchDesc* __restrict__ D, const int* __restrict__ off,
                                                 int nsys) {
-  const int s = batch_sys(off, nsys, blockIdx.x);
+  const int s = batch_system(off, nsys, blockIdx.x);
   const BatchDesc& d = D[s];
   const size_t cs = 2 * size_t(d.wp.n) * d.wp.n * d.wp.n;
   interp_body<R>(d.nb, (const double4*)d.pos4, static_cast<const R*>(d.grid), cs, d.wp, d.w, &d.ctl->stop, d.body,
@@ -2107,31 +2240,17 @@ __global__ __launch_bounds__(256) void kb_interp(const BatchDesc* __restrict__ D
                  blockIdx.x - off[s], 0, 0);
 }
 
-// spreading fields of a batch descriptor (bin_start == nullptr: no gather plan)
-void spread_plan_desc(const SpreadPlan* sp, int prec, BatchDesc& d) {
-  if (!sp || sp->BS != 8) {
-    d.blk_start = d.blk_end = d.cand = nullptr;
-    d.bin_start = d.bin_end = d.perm = nullptr;
-    d.starts = nullptr;
-    d.w64 = nullptr;
-    d.w32 = nullptr;
-    d.nbin = d.K = d.C = 0;
-    return;
-  }
-  d.bin_start = sp->bin_start;
-  d.bin_end = sp->bin_end;
-  d.blk_start = sp->blk_start;
-  d.blk_end = sp->blk_end;
-  d.cand = sp->cand;
-  d.perm = sp->perm;
-  d.starts = sp->starts;
-  d.w64 = sp->weights;
-  d.w32 = sp->weights32;
-  d.nbin = sp->nbin;
-  d.K = sp->K;
-  const size_t rb = prec ? sizeof(float) : sizeof(double);
-  const size_t per = rb * (3 * size_t(d.wp.support) + 6) + sizeof(int4) + sizeof(int);
-  d.C = int(std::min<size_t>(128, (size_t(60) << 10) / per)) & ~3;  // as launch_spread_gather
+// spreading fields of a batch descriptor (blk_start == nullptr: no plan of 8^3 blocks)
+void spread_plan_desc(const SpreadPlan* sp, BatchDesc& d) {
+  const bool ok = sp && sp->BS == 8;
+  d.blk_start = ok ? sp->blk_start : nullptr;
+  d.blk_end = ok ? sp->blk_end : nullptr;
+  d.cand = ok ? sp->cand : nullptr;
+  d.perm = ok ? sp->perm : nullptr;
+  d.starts = ok ? sp->starts : nullptr;
+  d.w64 = ok ? sp->weights : nullptr;
+  d.w32 = ok ? sp->weights32 : nullptr;
+  d.nbin = ok ? sp->nbin : 0;
 }
 
 int batch_blocks(const BatchDesc& d, int kind) {
@@ -2143,7 +2262,7 @@ int batch_blocks(const BatchDesc& d, int kind) {
     case BK_REAL:
       return std::max(1, real_blocks(d.nb, kBatchLpr) / kBatchRealPasses);
     case BK_SPREAD:
-      return d.bin_start ? d.nbin * d.nbin * d.nbin : 0;
+      return d.nbin * d.nbin * d.nbin;
     case BK_FFT_OUTER:
     case BK_FFT_MID:
       return N * N / d.bl * 3;
@@ -2165,8 +2284,7 @@ size_t batch_shm(const BatchDesc& d, int kind, int prec) {
     case BK_REAL:
       return prec ? RealPoly<float>::kBytes : RealPoly<double>::kBytes;
     case BK_SPREAD:
-      return std::max((rb * (3 * size_t(d.wp.support) + 6) + sizeof(int4) + sizeof(int)) * d.C,
-                      size_t(kSplitRedBytes64) / sizeof(double) * rb);
+      return prec ? SpreadTile<float, false>::kBytes : SpreadTile<double, false>::kBytes;
     case BK_FFT_OUTER:
     case BK_FFT_MID:
       return tb * (2 * size_t(d.bl) * fft_line_stride(int(N), d.bl, int(tb)) + N);

@@ -968,24 +968,10 @@ void launch_precond_arnoldi(int nb, int na, const int* offsets, const double* r4
 // CGS2 passes (block -> system by the prefix table; see BatchDesc)
 // ------------------------------------------------------------------------------------------
 
-namespace {
-__device__ inline int batch_sys_s(const int* __restrict__ off, int nsys, int b) {
-  int lo = 0, hi = nsys - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (off[mid] <= b)
-      lo = mid;
-    else
-      hi = mid - 1;
-  }
-  return lo;
-}
-}  // namespace
-
 // Arnoldi step j: v_j = scal * (j == 0 ? r : w) formed in the preconditioner, z = P^-1 v_j
 __global__ __launch_bounds__(256) void kb_precond(const BatchDesc* __restrict__ D, const int* __restrict__ off,
                                                  int nsys, int j) {
-  const int s = batch_sys_s(off, nsys, blockIdx.x);
+  const int s = batch_system(off, nsys, blockIdx.x);
   const BatchDesc& d = D[s];
   precond_fused_body(d.nb, d.na, d.offsets, (const double4*)d.r4, d.lu, d.piv, d.drag_t, d.drag_r, j == 0 ? d.r : d.w,
                      d.scal, d.basis + size_t(j) * d.n, d.z, &d.ctl->stop, blockIdx.x - off[s], 0, 0);
@@ -993,7 +979,7 @@ __global__ __launch_bounds__(256) void kb_precond(const BatchDesc* __restrict__ 
 
 __global__ __launch_bounds__(256) void kb_agg(const BatchDesc* __restrict__ D, const int* __restrict__ off,
                                              int nsys) {
-  const int s = batch_sys_s(off, nsys, blockIdx.x);
+  const int s = batch_system(off, nsys, blockIdx.x);
   const BatchDesc& d = D[s];
   const size_t nb6 = 6 * size_t(d.nb);
   agg_lub_body(d.na, d.offsets, d.body, (const double4*)d.r4, d.z, d.z + nb6, d.lrow, d.lcol, d.lcoef, d.w + nb6,
@@ -1005,7 +991,7 @@ __global__ __launch_bounds__(256) void kb_agg(const BatchDesc* __restrict__ D, c
 template <int MODE>
 __global__ __launch_bounds__(kCgsThreads) void kb_cgs(const BatchDesc* __restrict__ D, const int* __restrict__ off,
                                                      int nsys, int j) {
-  const int s = batch_sys_s(off, nsys, blockIdx.x);
+  const int s = batch_system(off, nsys, blockIdx.x);
   const BatchDesc& d = D[s];
   if (d.ctl->stop) return;
   const int G = d.ncgs;
@@ -1019,7 +1005,7 @@ __global__ __launch_bounds__(kCgsThreads) void kb_cgs(const BatchDesc* __restric
 // into the preconditioner that forms v_j, as k_precond_arnoldi
 __global__ __launch_bounds__(256) void kb_precond_arnoldi(const BatchDesc* __restrict__ D,
                                                          const int* __restrict__ off, int nsys, int j) {
-  const int s = batch_sys_s(off, nsys, blockIdx.x);
+  const int s = batch_system(off, nsys, blockIdx.x);
   const BatchDesc& d = D[s];
   const ArnoldiArgs prev{j - 1, d.ctl, d.h1, d.h2, d.H, d.gcs, d.gsn, d.g, d.scal};
   precond_arnoldi_body(d.nb, d.na, d.offsets, (const double4*)d.r4, d.lu, d.piv, d.drag_t, d.drag_r, d.w,
