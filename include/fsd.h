@@ -434,8 +434,8 @@ fsd_status fsd_batch_set_timing(fsd_batch* b, int enable);
 fsd_status fsd_batch_get_timers(fsd_batch* b, double* total_ms, long long* launches, double* bytes);
 
 /* Average duration (ms) of one multi-system launch of class timer (FSD_TIMER_REAL ..
- * FSD_TIMER_PRECOND) over every admitted system, replayed reps times back to back on the
- * batch stream between one pair of HIP events; bytes_per_launch (may be NULL) gets the
+ * FSD_TIMER_PRECOND) over every admitted system (summed over the groups of systems that share a
+ * launch), replayed reps times back to back on the batch stream between one pair of HIP events; bytes_per_launch (may be NULL) gets the
  * algorithmic bytes of that launch.  Needs systems that share multi-system launches
  * (FSD_ESTATE otherwise).  Builds lists and factors for moved positions first; leaves the
  * grids and scratch vectors undefined and the systems ready for their next solve. */

@@ -2550,10 +2550,10 @@ struct fsd_batch {
   // multi-system launches (fused mode): descriptor and block tables on the device and
   // a stream of their own
   bool fused = true;
-  // captured lock-step segments (j0, cnt) of the current tables; recaptured whenever the
+  // captured lock-step segments (group, j0, cnt) of the current tables; recaptured whenever the
   // tables are uploaded again (another set of systems, other block counts or LDS)
   struct SegGraph {
-    int j0, cnt;
+    int group, j0, cnt;
     hipGraphExec_t exec;
   };
   bool use_graphs = true;
@@ -2573,10 +2573,20 @@ struct fsd_batch {
   int* d_off = nullptr;
   int cap = 0;
   std::vector<BatchDesc> h_desc;
-  std::vector<int> h_off;  // BK_COUNT x (cap + 1)
+  std::vector<int> h_off;  // the groups' block tables
+  int off_cap = 0;
   int nsys = 0, prec = 0;
-  int total[BK_COUNT] = {0};
-  size_t shm[BK_COUNT] = {0};
+  // Consecutive systems of the tables that share a launch: block totals and LDS of each kind, and
+  // where the group's block tables start in d_off (one prefix table of ns + 1 entries per kind)
+  struct Group {
+    int first, ns;
+    int total[BK_COUNT];
+    size_t shm[BK_COUNT];
+    size_t off;
+  };
+  std::vector<Group> groups;
+  const BatchDesc* desc_of(const Group& g) const { return d_desc + g.first; }
+  const int* off_of(const Group& g, int kind) const { return d_off + g.off + size_t(kind) * (g.ns + 1); }
   std::vector<fsd_system*> cyc;  // the systems of the tables, in table order
   std::vector<char> active;      // cyc[k] still iterating in the current cycle (timing only)
   // LDS per workgroup allowed to the z/y line passes and to the x+Green pass (0: no cap).
@@ -2751,6 +2761,18 @@ bool fusable(const std::vector<fsd_system*>& act) {
   return true;
 }
 
+// The wave-space kernels of an Arnoldi step sweep the systems' grids twelve times.  One launch over
+// all systems of a large batch streams every sweep from HBM; a group whose grids stay in the
+// 256 MB last-level cache does not.  64 systems, 594 MB of FP32 grids, all groups replayed: line
+// passes 396 -> 329 us each, spreading 298 -> 270, interpolation 391 -> 337, the step 171.2 ->
+// 166.5 ms.  (100 MB: 180 ms, the small kernels' launches show; 240 MB: 165.1 ms.)
+constexpr double kGroupBytes = 170e6;
+
+double grid_bytes_of(const BatchDesc& d, int prec) {
+  const double N = d.plan.n;
+  return 6.0 * N * N * N * (prec ? 4 : 8);
+}
+
 // upload descriptors and block tables for the systems in cyc (skipped when unchanged)
 void set_tables(fsd_batch* b, const std::vector<fsd_system*>& cyc, int prec) {
   const int ns = int(cyc.size());
@@ -2764,20 +2786,30 @@ void set_tables(fsd_batch* b, const std::vector<fsd_system*>& cyc, int prec) {
     if (b->lds_cap[1])
       while (d.bg > 1 && batch_shm(d, BK_FFT_GREEN, prec) > b->lds_cap[1]) --d.bg;
   }
-  std::vector<int> off(size_t(BK_COUNT) * (ns + 1), 0);
-  int total[BK_COUNT];
-  size_t shm[BK_COUNT];
-  for (int kind = 0; kind < BK_COUNT; ++kind) {
-    int acc = 0;
-    size_t mx = 0;
-    for (int k = 0; k < ns; ++k) {
-      off[size_t(kind) * (ns + 1) + k] = acc;
-      acc += batch_blocks(desc[k], kind);
-      mx = std::max(mx, batch_shm(desc[k], kind, prec));
+  std::vector<fsd_batch::Group> groups;
+  std::vector<int> off;
+  double all = 0;
+  for (const BatchDesc& d : desc) all += grid_bytes_of(d, prec);
+  const double per_group = all / std::ceil(std::max(all, 1.0) / kGroupBytes);
+  for (int first = 0; first < ns;) {
+    fsd_batch::Group g{};
+    g.first = first;
+    double held = 0;  // the group closes at the system that brings it to its share of the bytes
+    do held += grid_bytes_of(desc[first++], prec);
+    while (first < ns && held + 0.5 * grid_bytes_of(desc[first], prec) <= per_group);
+    g.ns = first - g.first;
+    g.off = off.size();
+    for (int kind = 0; kind < BK_COUNT; ++kind) {
+      int acc = 0;
+      for (int k = g.first; k < first; ++k) {
+        off.push_back(acc);
+        acc += batch_blocks(desc[k], kind);
+        g.shm[kind] = std::max(g.shm[kind], batch_shm(desc[k], kind, prec));
+      }
+      off.push_back(acc);
+      g.total[kind] = acc;
     }
-    off[size_t(kind) * (ns + 1) + ns] = acc;
-    total[kind] = acc;
-    shm[kind] = mx;
+    groups.push_back(g);
   }
   b->cyc = cyc;
   b->active.assign(ns, 1);
@@ -2787,22 +2819,26 @@ void set_tables(fsd_batch* b, const std::vector<fsd_system*>& cyc, int prec) {
   ++b->table_version;  // captured segments hold the old block counts and LDS sizes
   if (ns > b->cap) {
     if (b->d_desc) HIPCHK(hipFree(b->d_desc));
-    if (b->d_off) HIPCHK(hipFree(b->d_off));
     b->d_desc = nullptr;
-    b->d_off = nullptr;
+    b->cap = 0;
     HIPCHK(hipMalloc(&b->d_desc, sizeof(BatchDesc) * ns));
-    HIPCHK(hipMalloc(&b->d_off, sizeof(int) * BK_COUNT * (ns + 1)));
     b->cap = ns;
+  }
+  if (int(off.size()) > b->off_cap) {
+    if (b->d_off) HIPCHK(hipFree(b->d_off));
+    b->d_off = nullptr;
+    b->off_cap = 0;
+    HIPCHK(hipMalloc(&b->d_off, sizeof(int) * off.size()));
+    b->off_cap = int(off.size());
   }
   HIPCHK(hipMemcpyAsync(b->d_desc, desc.data(), sizeof(BatchDesc) * ns, hipMemcpyHostToDevice, b->st));
   HIPCHK(hipMemcpyAsync(b->d_off, off.data(), sizeof(int) * off.size(), hipMemcpyHostToDevice, b->st));
   HIPCHK(hipStreamSynchronize(b->st));
   b->h_desc.swap(desc);
   b->h_off.swap(off);
+  b->groups.swap(groups);
   b->nsys = ns;
   b->prec = prec;
-  std::copy(total, total + BK_COUNT, b->total);
-  std::copy(shm, shm + BK_COUNT, b->shm);
 }
 
 // algorithmic HBM bytes of one system's share of a multi-system launch of timer class cls
@@ -2851,10 +2887,10 @@ void batch_harvest(fsd_batch* b) {
   b->ev_next = 0;
 }
 
-// one multi-system launch; with timing on it is bracketed by events on the batch stream and
-// counts the bytes of the systems still iterating
+// one multi-system launch over a group; with timing on it is bracketed by events on the batch
+// stream and counts the bytes of the group's systems still iterating
 template <typename L>
-void batch_launch(fsd_batch* b, int cls, int nq, L&& launch) {
+void batch_launch(fsd_batch* b, const fsd_batch::Group& g, int cls, int nq, L&& launch) {
   if (!b->timing) {
     launch();
     return;
@@ -2864,27 +2900,28 @@ void batch_launch(fsd_batch* b, int cls, int nq, L&& launch) {
   launch();
   HIPCHK(hipEventRecord(eb, b->st));
   double by = 0;
-  for (size_t k = 0; k < b->cyc.size(); ++k)
+  for (int k = g.first; k < g.first + g.ns; ++k)
     if (b->active[k]) by += batch_share_bytes(b->cyc[k], cls, b->prec, nq);
   b->pending.push_back({cls, by, ea, eb});
 }
 
-// Arnoldi steps j0 .. j0 + cnt - 1 of every system in the tables, one launch per kernel
-void batch_segment_body(fsd_batch* b, int j0, int cnt) {
-  const int ns = b->nsys, prec = b->prec;
-  auto off = [&](int kind) { return b->d_off + size_t(kind) * (ns + 1); };
+// Arnoldi steps j0 .. j0 + cnt - 1 of a group's systems, one launch per kernel
+void batch_segment_body(fsd_batch* b, const fsd_batch::Group& g, int j0, int cnt) {
+  const int ns = g.ns, prec = b->prec;
+  const BatchDesc* D = b->desc_of(g);
+  auto off = [&](int kind) { return b->off_of(g, kind); };
   auto mob = [&](int cls, int kind, int stage) {
-    batch_launch(b, cls, 0, [&] {
-      launch_batch_mobility(kind, prec, stage, b->d_desc, off(kind), ns, b->total[kind], b->shm[kind], b->st);
+    batch_launch(b, g, cls, 0, [&] {
+      launch_batch_mobility(kind, prec, stage, D, off(kind), ns, g.total[kind], g.shm[kind], b->st);
     });
   };
   for (int j = j0; j < j0 + cnt; ++j) {
     // inside a segment the Arnoldi update of step j-1 rides in the preconditioner of step j;
     // the segment's last step makes its update alone (kb_arnoldi_reduce), so the host reads
     // current stop flags after every segment
-    batch_launch(b, FSD_TIMER_PRECOND, 0, [&] {
-      launch_batch_solver(j > j0 ? BK_PRECOND_ARNOLDI : BK_PRECOND, j, 0, b->d_desc, off(BK_PRECOND), ns,
-                          b->total[BK_PRECOND], b->st);
+    batch_launch(b, g, FSD_TIMER_PRECOND, 0, [&] {
+      launch_batch_solver(j > j0 ? BK_PRECOND_ARNOLDI : BK_PRECOND, j, 0, D, off(BK_PRECOND), ns,
+                          g.total[BK_PRECOND], b->st);
     });
     mob(FSD_TIMER_REAL, BK_REAL, 0);
     mob(FSD_TIMER_SPREAD, BK_SPREAD, 0);
@@ -2895,24 +2932,25 @@ void batch_segment_body(fsd_batch* b, int j0, int cnt) {
       mob(cls_of[stage], kind, stage);
     }
     mob(FSD_TIMER_INTERP, BK_INTERP, 0);
-    batch_launch(b, FSD_TIMER_RIGID, 0, [&] {
-      launch_batch_solver(BK_AGG, j, 0, b->d_desc, off(BK_AGG), ns, b->total[BK_AGG], b->st);
+    batch_launch(b, g, FSD_TIMER_RIGID, 0, [&] {
+      launch_batch_solver(BK_AGG, j, 0, D, off(BK_AGG), ns, g.total[BK_AGG], b->st);
     });
     static const int cgs_cls[3] = {FSD_TIMER_CGS_DOT, FSD_TIMER_CGS_UPDATE, FSD_TIMER_CGS_NORM};
     for (int mode = 0; mode < 3; ++mode)
-      batch_launch(b, cgs_cls[mode], j + 1, [&] {
-        launch_batch_solver(BK_CGS, j, mode, b->d_desc, off(BK_CGS), ns, b->total[BK_CGS], b->st);
+      batch_launch(b, g, cgs_cls[mode], j + 1, [&] {
+        launch_batch_solver(BK_CGS, j, mode, D, off(BK_CGS), ns, g.total[BK_CGS], b->st);
       });
-    if (j == j0 + cnt - 1) launch_batch_solver(BK_ARNOLDI, j, 0, b->d_desc, nullptr, ns, ns, b->st);
+    if (j == j0 + cnt - 1) launch_batch_solver(BK_ARNOLDI, j, 0, D, nullptr, ns, ns, b->st);
   }
 }
 
-// One lock-step segment.  Without timing it replays a captured graph of the segment's
+// One lock-step segment of a group.  Without timing it replays a captured graph of the segment's
 // launches, captured on first use for the current tables: the first cycle of every time
 // step runs the same systems with the same tables, so its segments are captured once.
-void batch_segment(fsd_batch* b, int j0, int cnt) {
+void batch_segment(fsd_batch* b, int group, int j0, int cnt) {
+  const fsd_batch::Group& g = b->groups[group];
   if (!b->use_graphs || b->timing) {
-    batch_segment_body(b, j0, cnt);
+    batch_segment_body(b, g, j0, cnt);
     HIPCHK(hipGetLastError());
     return;
   }
@@ -2921,13 +2959,13 @@ void batch_segment(fsd_batch* b, int j0, int cnt) {
     b->graphs_version = b->table_version;
   }
   hipGraphExec_t exec = nullptr;
-  for (auto& g : b->seg_graphs)
-    if (g.j0 == j0 && g.cnt == cnt) exec = g.exec;
+  for (auto& e : b->seg_graphs)
+    if (e.group == group && e.j0 == j0 && e.cnt == cnt) exec = e.exec;
   if (!exec) {
     hipGraph_t graph = nullptr;
     HIPCHK(hipStreamBeginCapture(b->st, hipStreamCaptureModeThreadLocal));
     try {
-      batch_segment_body(b, j0, cnt);
+      batch_segment_body(b, g, j0, cnt);
     } catch (...) {
       (void)hipStreamEndCapture(b->st, &graph);
       if (graph) (void)hipGraphDestroy(graph);
@@ -2937,7 +2975,7 @@ void batch_segment(fsd_batch* b, int j0, int cnt) {
     const hipError_t ie = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
     (void)hipGraphDestroy(graph);
     if (ie != hipSuccess) throw HipError(std::string("hipGraphInstantiate: ") + hipGetErrorString(ie));
-    b->seg_graphs.push_back({j0, cnt, exec});
+    b->seg_graphs.push_back({group, j0, cnt, exec});
   }
   HIPCHK(hipGraphLaunch(exec, b->st));
 }
@@ -3064,7 +3102,11 @@ fsd_status batch_run_fused(fsd_batch* b, const std::vector<fsd_system*>& act, do
       set_tables(b, cyc, prec);
       for (int j0 = 0;; j0 += S) {
         const int cnt = std::min(S, cyc[0]->m - j0);
-        batch_segment(b, j0, cnt);
+        for (int g = 0; g < int(b->groups.size()); ++g) {
+          const auto first = b->active.begin() + b->groups[g].first;
+          if (std::find(first, first + b->groups[g].ns, char(1)) != first + b->groups[g].ns)
+            batch_segment(b, g, j0, cnt);  // a group whose systems have all stopped is skipped
+        }
         const int ns = int(cyc.size());
         if (ns > b->stop_cap) {
           if (b->d_stop) HIPCHK(hipFree(b->d_stop));
@@ -3296,15 +3338,15 @@ fsd_status fsd_batch_time_kernel(fsd_batch* b, int timer, int reps, double* avg_
     set_tables(b, act, prec);
     // every system iterating: the kernels return early for a raised stop flag
     for (auto* s : act) HIPCHK(hipMemsetAsync(&s->d_ctl->stop, 0, sizeof(int), b->st));
-    const int ns = b->nsys;
-    auto off = [&](int kind) { return b->d_off + size_t(kind) * (ns + 1); };
-    auto one = [&]() {
+    auto one = [&](const fsd_batch::Group& g) {
+      const BatchDesc* D = b->desc_of(g);
+      auto off = [&](int kind) { return b->off_of(g, kind); };
       switch (timer) {
         case FSD_TIMER_PRECOND:
-          launch_batch_solver(BK_PRECOND, 0, 0, b->d_desc, off(BK_PRECOND), ns, b->total[BK_PRECOND], b->st);
+          launch_batch_solver(BK_PRECOND, 0, 0, D, off(BK_PRECOND), g.ns, g.total[BK_PRECOND], b->st);
           break;
         case FSD_TIMER_RIGID:
-          launch_batch_solver(BK_AGG, 0, 0, b->d_desc, off(BK_AGG), ns, b->total[BK_AGG], b->st);
+          launch_batch_solver(BK_AGG, 0, 0, D, off(BK_AGG), g.ns, g.total[BK_AGG], b->st);
           break;
         default: {
           int kind = BK_REAL, stage = 0;
@@ -3314,7 +3356,7 @@ fsd_status fsd_batch_time_kernel(fsd_batch* b, int timer, int reps, double* avg_
           if (timer == FSD_TIMER_FFT_Y) kind = BK_FFT_MID, stage = 1;
           if (timer == FSD_TIMER_GREEN) kind = BK_FFT_GREEN, stage = 2;
           if (timer == FSD_TIMER_INTERP) kind = BK_INTERP;
-          launch_batch_mobility(kind, prec, stage, b->d_desc, off(kind), ns, b->total[kind], b->shm[kind], b->st);
+          launch_batch_mobility(kind, prec, stage, D, off(kind), g.ns, g.total[kind], g.shm[kind], b->st);
         }
       }
     };
@@ -3323,10 +3365,11 @@ fsd_status fsd_batch_time_kernel(fsd_batch* b, int timer, int reps, double* avg_
     HIPCHK(hipEventCreate(&ev[1]));
     float ms = 0;
     try {
-      one();  // warm
+      for (const auto& g : b->groups) one(g);  // warm
       launch_timing_mark(b->st);
       HIPCHK(hipEventRecord(ev[0], b->st));
-      for (int r = 0; r < reps; ++r) one();
+      for (const auto& g : b->groups)
+        for (int r = 0; r < reps; ++r) one(g);
       HIPCHK(hipEventRecord(ev[1], b->st));
       launch_timing_mark(b->st);
       HIPCHK(hipStreamSynchronize(b->st));
