@@ -83,7 +83,8 @@ struct WaveParams {
   // the same multipliers rounded to FP32, 8 per entry: sinc, jv, the solve's and the
   // Brownian root's factors, 1/|k|, then 3 unused (16-byte aligned rows), or nullptr
   const float* gtab32;
-  // transform tiles (0: the default rules fft_lines_b / fft_green_rows): lines per workgroup
+  // transform tiles (0: the two-step passes where the side has them, else the default rules
+  // fft_lines_b / fft_green_rows): lines per workgroup
   // of the z and y passes, row pairs per workgroup of the x+Green pass
   int tile_b, tile_g;
 };
@@ -385,8 +386,8 @@ struct BatchDesc {
   const double* tw64;
   const float* tw32;
   void* grid;
-  int bl;  // lines per workgroup of the z and y passes
-  int bg;  // row slots per workgroup of the x+Green pass
+  int bl;  // lines per workgroup of the z and y passes (0: the two-step passes)
+  int bg;  // row slots per workgroup of the x+Green pass (0: the two-step pass)
   // gather spreading (8^3 blocks): per-block candidate lists
   const int* blk_start;
   const int* blk_end;
@@ -436,15 +437,23 @@ int lines_b_of(const WaveParams& wp, int rbytes);
 int green_g_of(const WaveParams& wp);
 bool tile_b_fits(int N, int B, int rbytes);
 bool tile_g_fits(int N, int G, int rbytes);
+// whether the system's line passes and its x+Green pass are the two-step ones (a side that has
+// them and no tile of its own)
+bool two_step_lines_of(const WaveParams& wp);
+bool two_step_green_of(const WaveParams& wp);
 // fill the spreading fields of d from a gather plan (d.wp must be set first)
 void spread_plan_desc(const SpreadPlan* sp, BatchDesc& d);
 // per-system block counts of each kind and the dynamic LDS the kinds need (prec: 0 FP64, 1 FP32)
-int batch_blocks(const BatchDesc& d, int kind);
+int batch_blocks(const BatchDesc& d, int kind, int prec);
+int batch_fft_blocks(const BatchDesc& d, int kind, int prec);
+size_t batch_fft_shm(const BatchDesc& d, int kind, int prec);
 size_t batch_shm(const BatchDesc& d, int kind, int prec);
 // one multi-system launch; stage: FFT stage 0..4 for the FFT kinds, j: Arnoldi step for
 // the preconditioner and CGS kinds (mode 0..2 in cgs_mode)
 void launch_batch_mobility(int kind, int prec, int stage, const BatchDesc* D, const int* off, int nsys, int total,
                            size_t shm, hipStream_t st);
+void launch_batch_fft(int prec, int stage, const BatchDesc* D, const int* off, int nsys, int total, size_t shm,
+                      hipStream_t st);
 void launch_batch_gather_stop(const BatchDesc* D, int nsys, int* out, hipStream_t st);
 void launch_batch_solver(int kind, int j, int cgs_mode, const BatchDesc* D, const int* off, int nsys, int total,
                          hipStream_t st);

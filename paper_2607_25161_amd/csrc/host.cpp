@@ -2257,8 +2257,9 @@ fsd_status fsd_autotune_tiles(fsd_system* s, int reps, int* lines_b, int* green_
       return ms;
     };
     // the y pass stands for both line passes (same body, strides differ)
+    s->wp.tile_b = s->wp.tile_g = 0;
     int best_b = 0;
-    double best = 1e300;
+    double best = two_step_lines_of(s->wp) ? timed(FSD_TIMER_FFT_Y) : 1e300;
     for (int B : {1, 2, 4, 8, 16, 32, 64}) {
       if (!tile_b_fits(N, B, rb)) continue;
       s->wp.tile_b = B;
@@ -2266,7 +2267,7 @@ fsd_status fsd_autotune_tiles(fsd_system* s, int reps, int* lines_b, int* green_
       if (ms < best) best = ms, best_b = B;
     }
     int best_g = 0;
-    best = 1e300;
+    best = two_step_green_of(s->wp) ? timed(FSD_TIMER_GREEN) : 1e300;
     for (int G : {1, 2, 3, 4, 6, 8}) {
       if (!tile_g_fits(N, G, rb)) continue;
       s->wp.tile_g = G;
@@ -2276,8 +2277,8 @@ fsd_status fsd_autotune_tiles(fsd_system* s, int reps, int* lines_b, int* green_
     s->wp.tile_b = best_b;
     s->wp.tile_g = best_g;
     s->drop_graphs();  // captured launches carry the old shapes
-    if (lines_b) *lines_b = best_b;
-    if (green_g) *green_g = best_g;
+    if (lines_b) *lines_b = lines_b_of(s->wp, rb);
+    if (green_g) *green_g = green_g_of(s->wp);
     return FSD_OK;
   });
 }
@@ -2720,8 +2721,8 @@ BatchDesc make_desc(fsd_system* s, int prec) {
   d.tw64 = s->d_tw64;
   d.tw32 = s->d_tw32;
   d.grid = s->d_grid;
-  d.bl = lines_b_of(s->wp, prec ? 4 : 8);
-  d.bg = green_g_of(s->wp);
+  d.bl = two_step_lines_of(s->wp) ? 0 : lines_b_of(s->wp, prec ? 4 : 8);
+  d.bg = two_step_green_of(s->wp) ? 0 : green_g_of(s->wp);
   spread_plan_desc(s->spread, d);
   d.lrow = lub ? s->d_lrow : nullptr;
   d.lcol = s->d_lcol;
@@ -2780,7 +2781,11 @@ void set_tables(fsd_batch* b, const std::vector<fsd_system*>& cyc, int prec) {
   for (int k = 0; k < ns; ++k) {
     BatchDesc& d = desc[k];
     d = make_desc(cyc[k], prec);
-    // narrower tiles (fewer lines, fewer row pairs) within the batch's LDS caps
+    // narrower tiles (fewer lines, fewer row pairs) within the batch's LDS caps; the two-step
+    // passes have one size and give way to run-time tiles where it is above the cap
+    if (b->lds_cap[0] && d.bl == 0 && batch_shm(d, BK_FFT_OUTER, prec) > b->lds_cap[0])
+      d.bl = fft_lines_b(d.wp.n, prec ? 4 : 8);
+    if (b->lds_cap[1] && d.bg == 0 && batch_shm(d, BK_FFT_GREEN, prec) > b->lds_cap[1]) d.bg = fft_green_rows(d.wp.n);
     if (b->lds_cap[0])
       while (d.bl > 1 && batch_shm(d, BK_FFT_OUTER, prec) > b->lds_cap[0]) d.bl /= 2;
     if (b->lds_cap[1])
@@ -2803,7 +2808,7 @@ void set_tables(fsd_batch* b, const std::vector<fsd_system*>& cyc, int prec) {
       int acc = 0;
       for (int k = g.first; k < first; ++k) {
         off.push_back(acc);
-        acc += batch_blocks(desc[k], kind);
+        acc += batch_blocks(desc[k], kind, prec);
         g.shm[kind] = std::max(g.shm[kind], batch_shm(desc[k], kind, prec));
       }
       off.push_back(acc);

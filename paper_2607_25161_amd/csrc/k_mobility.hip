@@ -13,9 +13,7 @@
 #include <algorithm>
 #include <type_traits>
 
-#include <mutex>
-
-#include "fsd_impl.hpp"
+#include "k_common.hpp"
 #include "k_rigid.hpp"
 
 namespace fsd {
@@ -24,17 +22,6 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kMaxP = 21;  // 3 * P weights computed by one 64-lane wavefront
 inline int nblocks(long long n, int t = kThreads) { return int((n + t - 1) / t); }
-
-template <typename R>
-struct C2;
-template <>
-struct C2<double> {
-  using T = double2;
-};
-template <>
-struct C2<float> {
-  using T = float2;
-};
 
 // Workgroups are dealt to the 8 XCDs round robin; map workgroup b of nblk so that each
 // XCD gets one contiguous range of logical blocks (neighbouring beads or grid blocks
@@ -475,46 +462,6 @@ void launch_interp_sheared(int nb, const double* pos4, const R* grid, const Wave
   const size_t cs = 2 * size_t(wp.n) * wp.n * wp.n;
   launch_k(k_interp_sheared<R>, nblocks(nb, 4), kThreads, 0, st, nb, (const double4*)pos4, grid, cs, wp, out, skip,
            body, (const double4*)r4, V);
-}
-
-// Global-memory accesses through a 32-bit element index i from a base the workgroup shares
-// (the caller keeps i sizeof(R) below 2^32), so a load or store takes a 32-bit offset
-// instead of a 64-bit address.  stg2 stores the pair p[i], p[i + 1] (i even); ldg4 loads
-// p[i .. i + 3] (i a multiple of 4, aligned); ldg2 loads the pair p[i], p[i + 1].
-template <typename R>
-__device__ __forceinline__ void stg2(R* p, unsigned i, R a, R b) {
-  typedef R V2 __attribute__((ext_vector_type(2)));
-  const unsigned bytes = i * unsigned(sizeof(R));
-  V2 v;
-  v.x = a;
-  v.y = b;
-  *(__attribute__((address_space(1))) V2*)((__attribute__((address_space(1))) char*)p + bytes) = v;
-}
-
-template <typename R>
-__device__ __forceinline__ R ldg1(const R* p, unsigned i) {
-  const unsigned bytes = i * unsigned(sizeof(R));
-  return *(__attribute__((address_space(1))) const R*)((__attribute__((address_space(1))) const char*)p + bytes);
-}
-
-template <typename R>
-__device__ __forceinline__ void ldg4(const R* p, unsigned i, R& a, R& b, R& c, R& d) {
-  typedef R V4 __attribute__((ext_vector_type(4)));
-  const unsigned bytes = i * unsigned(sizeof(R));
-  const V4 v = *(__attribute__((address_space(1))) const V4*)((__attribute__((address_space(1))) const char*)p + bytes);
-  a = v.x;
-  b = v.y;
-  c = v.z;
-  d = v.w;
-}
-
-template <typename R>
-__device__ __forceinline__ void ldg2(const R* p, unsigned i, R& a, R& b) {
-  typedef R V2 __attribute__((ext_vector_type(2)));
-  const unsigned bytes = i * unsigned(sizeof(R));
-  const V2 v = *(__attribute__((address_space(1))) const V2*)((__attribute__((address_space(1))) const char*)p + bytes);
-  a = v.x;
-  b = v.y;
 }
 
 template <typename R>
@@ -1374,812 +1321,11 @@ void launch_spread_fused(const SpreadPlan* sp, const double* lam, const WavePara
 }
 
 // ------------------------------------------------------------------------------------------
-// 3D FFT: three passes of batched 1D transforms, each line staged in LDS and
-// transformed by mixed-radix (4, 2, 3, 5) Stockham stages.
-// ------------------------------------------------------------------------------------------
-
-namespace {
-template <typename T>
-__device__ inline T cmul(T a, T b) {
-  T r;
-  r.x = a.x * b.x - a.y * b.y;
-  r.y = a.x * b.y + a.y * b.x;
-  return r;
-}
-template <typename T>
-__device__ inline T cadd(T a, T b) {
-  T r;
-  r.x = a.x + b.x;
-  r.y = a.y + b.y;
-  return r;
-}
-template <typename T>
-__device__ inline T csub(T a, T b) {
-  T r;
-  r.x = a.x - b.x;
-  r.y = a.y - b.y;
-  return r;
-}
-// Quotient and remainder by a divisor known only at run time, for dividends below 2^21:
-// the product with the FP32 reciprocal (v_rcp_f32, within 1 ulp) is within 1/4 of the true
-// quotient, so truncating it and one correction step give the exact result (a hardware
-// integer division sequence costs about 25 instructions per use in these index loops).
-struct FastDiv {
-  int d;
-  float inv;
-  __device__ explicit FastDiv(int d_) : d(d_), inv(__frcp_rn(float(d_))) {}
-  __device__ __forceinline__ int div(int a) const {
-    int q = int(float(a) * inv);
-    const int r = a - q * d;
-    q += (r >= d) - (r < 0);
-    return q;
-  }
-  __device__ __forceinline__ void divmod(int a, int& q, int& r) const {
-    q = div(a);
-    r = a - q * d;
-  }
-};
-
-// multiply by -i*sign... rot(v, s) = s * i * v
-template <typename T>
-__device__ inline T rot(T v, int s) {
-  T r;
-  r.x = -s * v.y;
-  r.y = s * v.x;
-  return r;
-}
-}  // namespace
-
-namespace {
-// One radix-Rd butterfly of a Stockham stage: reads Rd inputs nbf apart, twiddles them by
-// w^(r k tstride) (w = exp(s 2 pi i / N), the table tw), transforms and writes them Ns apart.
-template <typename T, typename R, int Rd>
-__device__ __forceinline__ void butterfly(const T* li, T* lo, const T* tw, int b, int nbf, int k, int Ns, int tstride,
-                                          int od, int s) {
-  T v[Rd];
-#pragma unroll
-  for (int r = 0; r < Rd; ++r) v[r] = li[b + r * nbf];
-  if (Ns > 1) {
-#pragma unroll
-    for (int r = 1; r < Rd; ++r) v[r] = cmul(v[r], tw[r * k * tstride]);
-  }
-  if (Rd == 8) {
-    // even and odd halves by 4-point transforms, joined by w^k = exp(s 2 pi i k / 8)
-    const T es02 = cadd(v[0], v[4]), ed02 = csub(v[0], v[4]), es13 = cadd(v[2], v[6]),
-            ed13 = rot(csub(v[2], v[6]), s);
-    const T os02 = cadd(v[1], v[5]), od02 = csub(v[1], v[5]), os13 = cadd(v[3], v[7]),
-            od13 = rot(csub(v[3], v[7]), s);
-    const T e0 = cadd(es02, es13), e1 = cadd(ed02, ed13), e2 = csub(es02, es13), e3 = csub(ed02, ed13);
-    const T o0 = cadd(os02, os13), o1 = cadd(od02, od13), o2 = csub(os02, os13), o3 = csub(od02, od13);
-    const R h8 = R(0.70710678118654752440), sr = R(s);
-    T t1, t3;
-    t1.x = h8 * (o1.x - sr * o1.y);  // w o1, w = (1 + s i) / sqrt 2
-    t1.y = h8 * (o1.y + sr * o1.x);
-    t3.x = -h8 * (o3.x + sr * o3.y);  // w^3 o3, w^3 = (-1 + s i) / sqrt 2
-    t3.y = h8 * (sr * o3.x - o3.y);
-    const T t2 = rot(o2, s);
-    lo[od] = cadd(e0, o0);
-    lo[od + 4 * Ns] = csub(e0, o0);
-    lo[od + Ns] = cadd(e1, t1);
-    lo[od + 5 * Ns] = csub(e1, t1);
-    lo[od + 2 * Ns] = cadd(e2, t2);
-    lo[od + 6 * Ns] = csub(e2, t2);
-    lo[od + 3 * Ns] = cadd(e3, t3);
-    lo[od + 7 * Ns] = csub(e3, t3);
-  } else if (Rd == 4) {
-    const T s02 = cadd(v[0], v[2]), d02 = csub(v[0], v[2]), s13 = cadd(v[1], v[3]), d13 = rot(csub(v[1], v[3]), s);
-    lo[od] = cadd(s02, s13);
-    lo[od + Ns] = cadd(d02, d13);
-    lo[od + 2 * Ns] = csub(s02, s13);
-    lo[od + 3 * Ns] = csub(d02, d13);
-  } else if (Rd == 2) {
-    lo[od] = cadd(v[0], v[1]);
-    lo[od + Ns] = csub(v[0], v[1]);
-  } else if (Rd == 3) {
-    const R c3 = R(-0.5), s3 = R(0.86602540378443864676);
-    const T sm = cadd(v[1], v[2]), jd = rot(csub(v[1], v[2]), s);  // s i (v1 - v2)
-    T m1, y1, y2;
-    m1.x = v[0].x + c3 * sm.x;
-    m1.y = v[0].y + c3 * sm.y;
-    y1.x = m1.x + s3 * jd.x;
-    y1.y = m1.y + s3 * jd.y;
-    y2.x = m1.x - s3 * jd.x;
-    y2.y = m1.y - s3 * jd.y;
-    lo[od] = cadd(v[0], sm);
-    lo[od + Ns] = y1;
-    lo[od + 2 * Ns] = y2;
-  } else {  // radix 5: cos and sin of 2 pi / 5 and 4 pi / 5
-    const R c1 = R(0.30901699437494742410), c2 = R(-0.80901699437494742410);
-    const R s1 = R(0.95105651629515357212), s2 = R(0.58778525229247312917);
-    const T t1 = cadd(v[1], v[4]), t2 = cadd(v[2], v[3]);
-    const T t3 = rot(csub(v[1], v[4]), s), t4 = rot(csub(v[2], v[3]), s);  // s i (v1 - v4), s i (v2 - v3)
-    T m1, m2, p1, p2;
-    m1.x = v[0].x + c1 * t1.x + c2 * t2.x;
-    m1.y = v[0].y + c1 * t1.y + c2 * t2.y;
-    m2.x = v[0].x + c2 * t1.x + c1 * t2.x;
-    m2.y = v[0].y + c2 * t1.y + c1 * t2.y;
-    p1.x = s1 * t3.x + s2 * t4.x;
-    p1.y = s1 * t3.y + s2 * t4.y;
-    p2.x = s2 * t3.x - s1 * t4.x;
-    p2.y = s2 * t3.y - s1 * t4.y;
-    lo[od] = cadd(v[0], cadd(t1, t2));
-    lo[od + Ns] = cadd(m1, p1);
-    lo[od + 2 * Ns] = cadd(m2, p2);
-    lo[od + 3 * Ns] = csub(m2, p2);
-    lo[od + 4 * Ns] = csub(m1, p1);
-  }
-}
-
-// Stockham stages (radices 8, 4, 2, 3, 5) on `nl` lines of length N held in LDS `ls`
-// elements apart (`in`, scratch `out`); returns the buffer holding the result.  The
-// radices come from the plan's packed code (4 bits per stage), so the stage loop indexes
-// no array.
-template <typename T, typename R>
-__device__ __forceinline__ T* stockham(T* in, T* out, const T* tw, int N, int ls, int nl, const FftPlan& plan,
-                                       int s) {
-  int Ns = 1;
-  const unsigned long long code = plan.rcode;
-  for (int stg = 0; stg < plan.nstage; ++stg) {
-    const int Rd = int((code >> (4 * stg)) & 15ull);
-    const int nbf = N / Rd;
-    const int tstride = N / (Ns * Rd);
-    const FastDiv dbf(nbf), dns(Ns);
-    for (int t = threadIdx.x; t < nl * nbf; t += blockDim.x) {
-      int l, b, j, k;
-      dbf.divmod(t, l, b);
-      dns.divmod(b, j, k);
-      const T* li = in + l * ls;
-      T* lo = out + l * ls;
-      const int od = j * Ns * Rd + k;
-      if (Rd == 8)
-        butterfly<T, R, 8>(li, lo, tw, b, nbf, k, Ns, tstride, od, s);
-      else if (Rd == 4)
-        butterfly<T, R, 4>(li, lo, tw, b, nbf, k, Ns, tstride, od, s);
-      else if (Rd == 2)
-        butterfly<T, R, 2>(li, lo, tw, b, nbf, k, Ns, tstride, od, s);
-      else if (Rd == 3)
-        butterfly<T, R, 3>(li, lo, tw, b, nbf, k, Ns, tstride, od, s);
-      else
-        butterfly<T, R, 5>(li, lo, tw, b, nbf, k, Ns, tstride, od, s);
-    }
-    __syncthreads();
-    T* tmp = in;
-    in = out;
-    out = tmp;
-    Ns *= Rd;
-  }
-  return in;
-}
-
-// Stockham stages on B lines (B a power of two, 2^lb) held S elements apart, with the
-// line as the fastest thread index: t -> (line t & (B - 1), butterfly t >> lb).  Lanes
-// that differ in the line meet distinct banks (the stride of fft_line_stride), and the
-// mapping needs one division per butterfly (by the stage's Ns) instead of two.
-// As stockham_lines for any number of lines nl (held S apart, S odd so that consecutive
-// lines start on distinct banks): t -> (line t mod nl, butterfly t / nl).
-template <typename T, typename R>
-__device__ __forceinline__ T* stockham_lm(T* in, T* out, const T* tw, int N, int S, int nl, const FftPlan& plan,
-                                          int s) {
-  int Ns = 1;
-  const unsigned long long code = plan.rcode;
-  const FastDiv dnl(nl);
-  for (int stg = 0; stg < plan.nstage; ++stg) {
-    const int Rd = int((code >> (4 * stg)) & 15ull);
-    const int nbf = N / Rd;
-    const int tstride = N / (Ns * Rd);
-    const FastDiv dns(Ns);
-    for (int t = threadIdx.x; t < nl * nbf; t += blockDim.x) {
-      int b, l, j, k;
-      dnl.divmod(t, b, l);
-      dns.divmod(b, j, k);
-      const T* li = in + l * S;
-      T* lo = out + l * S;
-      const int od = j * Ns * Rd + k;
-      if (Rd == 8)
-        butterfly<T, R, 8>(li, lo, tw, b, nbf, k, Ns, tstride, od, s);
-      else if (Rd == 4)
-        butterfly<T, R, 4>(li, lo, tw, b, nbf, k, Ns, tstride, od, s);
-      else if (Rd == 2)
-        butterfly<T, R, 2>(li, lo, tw, b, nbf, k, Ns, tstride, od, s);
-      else if (Rd == 3)
-        butterfly<T, R, 3>(li, lo, tw, b, nbf, k, Ns, tstride, od, s);
-      else
-        butterfly<T, R, 5>(li, lo, tw, b, nbf, k, Ns, tstride, od, s);
-    }
-    __syncthreads();
-    T* tmp = in;
-    in = out;
-    out = tmp;
-    Ns *= Rd;
-  }
-  return in;
-}
-
-template <typename T, typename R>
-__device__ __forceinline__ T* stockham_lines(T* in, T* out, const T* tw, int N, int S, int B, int lb,
-                                             const FftPlan& plan, int s) {
-  int Ns = 1;
-  const unsigned long long code = plan.rcode;
-  for (int stg = 0; stg < plan.nstage; ++stg) {
-    const int Rd = int((code >> (4 * stg)) & 15ull);
-    const int nbf = N / Rd;
-    const int tstride = N / (Ns * Rd);
-    const FastDiv dns(Ns);
-    for (int t = threadIdx.x; t < (nbf << lb); t += blockDim.x) {
-      const int l = t & (B - 1), b = t >> lb;
-      int j, k;
-      dns.divmod(b, j, k);
-      const T* li = in + l * S;
-      T* lo = out + l * S;
-      const int od = j * Ns * Rd + k;
-      if (Rd == 8)
-        butterfly<T, R, 8>(li, lo, tw, b, nbf, k, Ns, tstride, od, s);
-      else if (Rd == 4)
-        butterfly<T, R, 4>(li, lo, tw, b, nbf, k, Ns, tstride, od, s);
-      else if (Rd == 2)
-        butterfly<T, R, 2>(li, lo, tw, b, nbf, k, Ns, tstride, od, s);
-      else if (Rd == 3)
-        butterfly<T, R, 3>(li, lo, tw, b, nbf, k, Ns, tstride, od, s);
-      else
-        butterfly<T, R, 5>(li, lo, tw, b, nbf, k, Ns, tstride, od, s);
-    }
-    __syncthreads();
-    T* tmp = in;
-    in = out;
-    out = tmp;
-    Ns *= Rd;
-  }
-  return in;
-}
-
-// stockham_lines for a grid side N known at compile time: the radices (8s, then 4, 2, 3s,
-// 5s), the butterfly counts, the divisions by Ns and the LDS offsets of every stage fold
-// into constants.  Used for the common grid sides; others take stockham_lines.
-template <int Rem>
-constexpr int pick_radix() {
-  return Rem % 8 == 0 ? 8 : Rem % 4 == 0 ? 4 : Rem % 2 == 0 ? 2 : Rem % 3 == 0 ? 3 : 5;
-}
-
-template <typename T, typename R, int N, int Ns, int Rem>
-__device__ __forceinline__ T* stockham_n(T* in, T* out, const T* tw, int S, int B, int lb, int s) {
-  if constexpr (Rem == 1) {
-    return in;
-  } else {
-    constexpr int Rd = pick_radix<Rem>(), nbf = N / Rd, tstride = N / (Ns * Rd);
-    for (int t = threadIdx.x; t < (nbf << lb); t += blockDim.x) {
-      const int l = t & (B - 1), b = t >> lb;
-      const int j = b / Ns, k = b - j * Ns;
-      butterfly<T, R, Rd>(in + l * S, out + l * S, tw, b, nbf, k, Ns, tstride, j * Ns * Rd + k, s);
-    }
-    __syncthreads();
-    return stockham_n<T, R, N, Ns * Rd, Rem / Rd>(out, in, tw, S, B, lb, s);
-  }
-}
-
-// stockham_lm for a compile-time grid side (nl lines, dnl its divider)
-template <typename T, typename R, int N, int Ns, int Rem>
-__device__ __forceinline__ T* stockham_lm_n(T* in, T* out, const T* tw, int S, int nl, const FastDiv& dnl, int s) {
-  if constexpr (Rem == 1) {
-    return in;
-  } else {
-    constexpr int Rd = pick_radix<Rem>(), nbf = N / Rd, tstride = N / (Ns * Rd);
-    for (int t = threadIdx.x; t < nl * nbf; t += blockDim.x) {
-      int b, l;
-      dnl.divmod(t, b, l);
-      const int j = b / Ns, k = b - j * Ns;
-      butterfly<T, R, Rd>(in + l * S, out + l * S, tw, b, nbf, k, Ns, tstride, j * Ns * Rd + k, s);
-    }
-    __syncthreads();
-    return stockham_lm_n<T, R, N, Ns * Rd, Rem / Rd>(out, in, tw, S, nl, dnl, s);
-  }
-}
-
-template <typename T, typename R>
-__device__ __forceinline__ T* stockham_lm_any(T* in, T* out, const T* tw, int N, int S, int nl, const FftPlan& plan,
-                                              int s) {
-  const FastDiv dnl(nl);
-  switch (N) {
-    case 32: return stockham_lm_n<T, R, 32, 1, 32>(in, out, tw, S, nl, dnl, s);
-    case 40: return stockham_lm_n<T, R, 40, 1, 40>(in, out, tw, S, nl, dnl, s);
-    case 48: return stockham_lm_n<T, R, 48, 1, 48>(in, out, tw, S, nl, dnl, s);
-    case 64: return stockham_lm_n<T, R, 64, 1, 64>(in, out, tw, S, nl, dnl, s);
-    case 72: return stockham_lm_n<T, R, 72, 1, 72>(in, out, tw, S, nl, dnl, s);
-    case 80: return stockham_lm_n<T, R, 80, 1, 80>(in, out, tw, S, nl, dnl, s);
-    case 96: return stockham_lm_n<T, R, 96, 1, 96>(in, out, tw, S, nl, dnl, s);
-    case 120: return stockham_lm_n<T, R, 120, 1, 120>(in, out, tw, S, nl, dnl, s);
-    case 128: return stockham_lm_n<T, R, 128, 1, 128>(in, out, tw, S, nl, dnl, s);
-    default: return stockham_lm<T, R>(in, out, tw, N, S, nl, plan, s);
-  }
-}
-
-// stockham_lines with the grid side dispatched to a compile-time instance where there is one
-template <typename T, typename R>
-__device__ __forceinline__ T* stockham_lines_any(T* in, T* out, const T* tw, int N, int S, int B, int lb,
-                                                 const FftPlan& plan, int s) {
-  switch (N) {
-    case 32: return stockham_n<T, R, 32, 1, 32>(in, out, tw, S, B, lb, s);
-    case 40: return stockham_n<T, R, 40, 1, 40>(in, out, tw, S, B, lb, s);
-    case 48: return stockham_n<T, R, 48, 1, 48>(in, out, tw, S, B, lb, s);
-    case 64: return stockham_n<T, R, 64, 1, 64>(in, out, tw, S, B, lb, s);
-    case 72: return stockham_n<T, R, 72, 1, 72>(in, out, tw, S, B, lb, s);
-    case 80: return stockham_n<T, R, 80, 1, 80>(in, out, tw, S, B, lb, s);
-    case 96: return stockham_n<T, R, 96, 1, 96>(in, out, tw, S, B, lb, s);
-    case 120: return stockham_n<T, R, 120, 1, 120>(in, out, tw, S, B, lb, s);
-    case 128: return stockham_n<T, R, 128, 1, 128>(in, out, tw, S, B, lb, s);
-    default: return stockham_lines<T, R>(in, out, tw, N, S, B, lb, plan, s);
-  }
-}
-
-}  // namespace
-
-template <typename R, int DIR>
-__global__ __launch_bounds__(256) void k_fft_pass(R* __restrict__ data, size_t cs, FftPlan plan,
-                                                  const R* __restrict__ twiddle, int sign, int B, const int* __restrict__ skip) {
-  if (skip && *skip) return;
-  using T = typename C2<R>::T;
-  extern __shared__ unsigned char smem_raw[];
-  const int N = plan.n;
-  const int S = fft_line_stride(N, B, int(sizeof(T)));
-  T* buf0 = reinterpret_cast<T*>(smem_raw);
-  T* buf1 = buf0 + B * S;
-  T* tw = buf1 + B * S;
-  T* base = reinterpret_cast<T*>(data + blockIdx.y * cs);
-  const int line0 = blockIdx.x * B;
-  const T* twg = reinterpret_cast<const T*>(twiddle);
-  for (int t = threadIdx.x; t < N; t += blockDim.x) {
-    T w = twg[t];
-    if (sign > 0) w.y = -w.y;
-    tw[t] = w;
-  }
-  for (int t = threadIdx.x; t < B * N; t += blockDim.x) {
-    int l, e;
-    if (DIR == 0) {
-      l = t / N;
-      e = t % N;
-    } else {
-      l = t % B;
-      e = t / B;
-    }
-    const size_t gl = size_t(line0 + l);
-    size_t off;
-    if (DIR == 0)
-      off = gl * N + e;
-    else if (DIR == 1)
-      off = ((gl / N) * N + e) * N + (gl % N);
-    else
-      off = (size_t(e) * N + (gl / N)) * N + (gl % N);
-    buf0[l * S + e] = base[off];
-  }
-  __syncthreads();
-  const T* in = stockham<T, R>(buf0, buf1, tw, N, S, B, plan, sign > 0 ? 1 : -1);
-  for (int t = threadIdx.x; t < B * N; t += blockDim.x) {
-    int l, e;
-    if (DIR == 0) {
-      l = t / N;
-      e = t % N;
-    } else {
-      l = t % B;
-      e = t / B;
-    }
-    const size_t gl = size_t(line0 + l);
-    size_t off;
-    if (DIR == 0)
-      off = gl * N + e;
-    else if (DIR == 1)
-      off = ((gl / N) * N + e) * N + (gl % N);
-    else
-      off = (size_t(e) * N + (gl / N)) * N + (gl % N);
-    base[off] = in[l * S + e];
-  }
-}
-
-namespace {
-int lines_per_block(int N) {
-  int B = 1;
-  while (B * 2 * N <= 1024 && (N % (B * 2)) == 0) B *= 2;
-  return B;
-}
-}  // namespace
-
-template <typename R>
-void launch_fft3d(R* grid, int ncomp, size_t comp_stride, const FftPlan& plan, const R* twiddle, int sign,
-                  hipStream_t st, int pass, const int* skip) {
-  using T = typename C2<R>::T;
-  const int N = plan.n;
-  const int B = lines_per_block(N);
-  const size_t shm = sizeof(T) * (2 * size_t(B) * fft_line_stride(N, B, int(sizeof(T))) + N);
-  dim3 g(N * N / B, ncomp);
-  if (pass < 0 || pass == 0) k_fft_pass<R, 0><<<g, kThreads, shm, st>>>(grid, comp_stride, plan, twiddle, sign, B, skip);
-  if (pass < 0 || pass == 1) k_fft_pass<R, 1><<<g, kThreads, shm, st>>>(grid, comp_stride, plan, twiddle, sign, B, skip);
-  if (pass < 0 || pass == 2) k_fft_pass<R, 2><<<g, kThreads, shm, st>>>(grid, comp_stride, plan, twiddle, sign, B, skip);
-}
-
-namespace {
-// Block-wide copy of `count` elements, t -> store(t, load(t)), with U loads in flight per
-// thread: each thread issues its next U loads before it writes any of them, so one wait
-// covers U memory latencies (a plain strided loop waits once per element).
-template <int U, typename T, typename Load, typename Store>
-__device__ __forceinline__ void staged_copy(int count, Load&& load, Store&& store) {
-  for (int t0 = threadIdx.x; t0 < count; t0 += U * int(blockDim.x)) {
-    T v[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int t = t0 + u * int(blockDim.x);
-      if (t < count) v[u] = load(t);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int t = t0 + u * int(blockDim.x);
-      if (t < count) store(t, v[u]);
-    }
-  }
-}
-
-template <typename T>
-__device__ inline void load_twiddles(T* tw, const T* twg, int N, int sign) {
-  for (int t = threadIdx.x; t < N; t += blockDim.x) {
-    T w = twg[t];
-    if (sign > 0) w.y = -w.y;
-    tw[t] = w;
-  }
-}
-}  // namespace
-
-namespace {
-__device__ inline void sinc_jv_d(double x, double& s, double& j) {
-  if (x < 0.5) {
-    const double x2 = x * x;
-    s = 1.0 - x2 / 6.0 * (1.0 - x2 / 20.0 * (1.0 - x2 / 42.0 * (1.0 - x2 / 72.0 * (1.0 - x2 / 110.0))));
-    j = 1.0 - x2 / 10.0 * (1.0 - x2 / 28.0 * (1.0 - x2 / 54.0 * (1.0 - x2 / 88.0 * (1.0 - x2 / 130.0))));
-  } else {
-    double sn, cn;
-    sincos(x, &sn, &cn);
-    s = sn / x;
-    j = 3.0 * (sn - x * cn) / (x * x * x);
-  }
-}
-}  // namespace
-
-// ------------------------------------------------------------------------------------------
-// Coalesced wave-space pipeline for N <= 256 (5 passes, in place on the three packed
-// complex grids Z_c = F_c + i T_c):
-//   z, y  : transforms along z, then y; a workgroup takes B consecutive x of B lines,
-//           so every load and store is a run of B contiguous complex values
-//   x+G   : one workgroup per pair of rows (ky, kz) and (-ky, -kz) of all three grids:
-//           forward x transform, split of the packed spectra by Hermitian symmetry
-//           (F^(k) = (Z(k) + conj Z(-k)) / 2, T^(k) = (Z(k) - conj Z(-k)) / 2i, the -k
-//           partner lies in the paired row), Green's-function scaling, repacking as
-//           Y^ = U^ + i W^, inverse x transform
-//   y, z  : inverse transforms
-// The product is the same linear operator as the half-spectrum pipeline.
-// ------------------------------------------------------------------------------------------
-
-template <typename R, int DIR>
-__device__ __forceinline__ void fft_lines_body(R* __restrict__ grid, size_t cs, FftPlan plan,
-                                               const R* __restrict__ twiddle, int sign, int B,
-                                               const int* __restrict__ skip, int bx_, int by_, int gx_) {
-  if (skip && *skip) return;
-  using T = typename C2<R>::T;
-  extern __shared__ unsigned char smem_raw[];
-  const int N = plan.n;
-  const int S = fft_line_stride(N, B, int(sizeof(T)));
-  T* buf0 = reinterpret_cast<T*>(smem_raw);
-  T* buf1 = buf0 + B * S;
-  T* tw = buf1 + B * S;
-  T* base = reinterpret_cast<T*>(grid + by_ * cs);
-  const int line0 = bx_ * B;  // line gl = o N + x: B consecutive x of one o (B divides N)
-  const int o = line0 / N, x0 = line0 - o * N;
-  const int lb = __ffs(B) - 1;  // B is a power of two
-  // element e of line l sits at g[e * es + l]: a workgroup-uniform base and a 32-bit
-  // offset (its byte offset stays below 2 N^3 sizeof(R) <= 2^28 for N <= 256)
-  R* g = reinterpret_cast<R*>(base + (DIR == 1 ? size_t(o) * N * N : size_t(o) * N) + x0);
-  const unsigned es = DIR == 1 ? N : N * N;
-  load_twiddles(tw, reinterpret_cast<const T*>(twiddle), N, sign);
-  staged_copy<8, T>(
-      B * N,
-      [&](int t) {
-        T v;
-        ldg2(g, 2 * (unsigned(t >> lb) * es + unsigned(t & (B - 1))), v.x, v.y);
-        return v;
-      },
-      [&](int t, const T& v) { buf0[(t & (B - 1)) * S + (t >> lb)] = v; });
-  __syncthreads();
-  const T* Y = stockham_lines_any<T, R>(buf0, buf1, tw, N, S, B, lb, plan, sign);
-  for (int t = threadIdx.x; t < B * N; t += blockDim.x) {
-    const int l = t & (B - 1), e = t >> lb;
-    const T y = Y[l * S + e];
-    stg2(g, 2 * (unsigned(e) * es + unsigned(l)), y.x, y.y);
-  }
-}
-
-template <typename R, int DIR>
-__global__ __launch_bounds__(256) void k_fft_lines(R* __restrict__ grid, size_t cs, FftPlan plan,
-                                                   const R* __restrict__ twiddle, int sign, int B,
-                                                   const int* __restrict__ skip) {
-  fft_lines_body<R, DIR>(grid, cs, plan, twiddle, sign, B, skip, blockIdx.x, blockIdx.y, gridDim.x);
-}
-
-// TABLE: the cube, multipliers read from the table by |m|^2; otherwise (the sheared lattice)
-// computed per mode.  Two instantiations keep the per-mode FP64 arithmetic out of the
-// cube's register budget.
-// LDS of the x+Green pass with G row slots and complex values of tb bytes: two buffers of
-// 6 G lines (stride N | 1) and the twiddles, then (16-byte aligned) the 2 G row descriptors
-__host__ __device__ inline size_t xgreen_rows_offset(int N, int G, int tb) {
-  return (size_t(tb) * (12 * size_t(G) * (N | 1) + N) + 15) & ~size_t(15);
-}
-__host__ __device__ inline size_t xgreen_shm(int N, int G, int tb) {
-  return xgreen_rows_offset(N, G, tb) + 2 * size_t(G) * sizeof(int4);
-}
-
-template <typename R, bool TABLE>
-__device__ __forceinline__ void fft_xgreen_body(R* __restrict__ grid, size_t cs, FftPlan plan,
-                                                const R* __restrict__ twiddle, WaveParams wp, int G,
-                                                const int* __restrict__ skip, int bx_, int by_, int gx_) {
-  if (skip && *skip) return;
-  using T = typename C2<R>::T;
-  extern __shared__ unsigned char smem_raw[];
-  const int N = plan.n, NN = N * N;
-  // G row slots per workgroup; slot g takes the pair number p = bx G + g of the
-  // N^2/2 + 2 pairs {r, rp} (r = kz N + ky, rp = its (-kz, -ky) partner, r <= rp; the
-  // four self-paired rows have rp == r).  Line (g, c, q) = component c of row q (0: r,
-  // 1: rp) sits at (6 g + 2 c + q) N; lines of idle slots are zero.
-  const int NL = 6 * G, S = N | 1;  // lines S apart: an odd stride spreads them over the banks
-  T* buf0 = reinterpret_cast<T*>(smem_raw);
-  T* buf1 = buf0 + NL * S;
-  T* tw = buf1 + NL * S;
-  int4* rows = reinterpret_cast<int4*>(smem_raw + xgreen_rows_offset(N, G, int(sizeof(T))));
-  const int H = N / 2, npair = NN / 2 + 2;
-  const FastDiv dn(N);
-  auto row_of = [N, H](int p) {  // pair number -> its first row r
-    if (p <= H) return p;                        // kz = 0, ky = 0 .. N/2
-    p -= H + 1;
-    if (p < (H - 1) * N) return N + p;           // kz = 1 .. N/2 - 1, all ky
-    return H * N + (p - (H - 1) * N);            // kz = N/2, ky = 0 .. N/2
-  };
-  // one descriptor per (slot g, row q), index 2 g + q: x = the row's (kz, ky) packed with
-  // bit 31 set (0: no row), y, z = LDS offsets of its line and of its partner's line
-  // (component 0), w = the row's index in the grid (-1: none)
-  for (int i = threadIdx.x; i < 2 * G; i += blockDim.x) {
-    const int g = i >> 1, q = i & 1, pn = bx_ * G + g;
-    int4 v = make_int4(0, 0, 0, -1);
-    if (pn < npair) {
-      const int r = row_of(pn);
-      int kz, ky;
-      dn.divmod(r, kz, ky);
-      const int rp = (kz ? N - kz : 0) * N + (ky ? N - ky : 0);  // the row of (-kz, -ky)
-      if (q == 0 || rp != r) {
-        if (q) dn.divmod(rp, kz, ky);
-        const int qm = rp == r ? 0 : 1 - q;
-        v.x = int(0x80000000u | (unsigned(kz) << 15) | unsigned(ky));
-        v.y = (6 * g + q) * S;
-        v.z = (6 * g + qm) * S;
-        v.w = q ? rp : r;
-      }
-    }
-    rows[i] = v;
-  }
-  load_twiddles(tw, reinterpret_cast<const T*>(twiddle), N, -1);
-  __syncthreads();
-  staged_copy<8, T>(
-      NL * N,
-      [&](int t) {
-        int line, x;
-        dn.divmod(t, line, x);
-        const int g = line / 6, c = (line % 6) >> 1, q = line & 1;
-        const int row = rows[2 * g + q].w;
-        T v;
-        v.x = 0;
-        v.y = 0;
-        if (row >= 0) ldg2(grid, unsigned(c * cs) + 2 * unsigned(row * N + x), v.x, v.y);
-        return v;
-      },
-      [&](int t, const T& v) {
-        int line, x;
-        dn.divmod(t, line, x);
-        buf0[line * S + x] = v;
-      });
-  __syncthreads();
-  T* X = stockham_lm_any<T, R>(buf0, buf1, tw, N, S, NL, plan, -1);
-  T* O = (X == buf0) ? buf1 : buf0;
-  const double tp = 2.0 * M_PI / wp.L, gam = (!TABLE && wp.gam) ? *wp.gam : 0.0;
-  // items (row 2 g + q, x mode kx), kx fastest; each thread steps blockDim.x items at a time
-  int gq, kx;
-  dn.divmod(int(threadIdx.x), gq, kx);
-  const int dq = int(blockDim.x) / N, dr = int(blockDim.x) - dq * N;
-  for (; gq < 2 * G; gq += dq, kx += dr) {
-    if (kx >= N) {
-      kx -= N;
-      if (++gq >= 2 * G) break;
-    }
-    const int4 ri = rows[gq];
-    if (ri.x >= 0) continue;  // no row
-    const int kz = (ri.x >> 15) & 0x7fff, ky = ri.x & 0x7fff;
-    const int kxm = kx ? N - kx : 0;
-    const int o = ri.y + kx, om = ri.z + kxm;  // this mode and its (-k) partner, component 0
-    const bool nyq = (N % 2 == 0) && (kx == N / 2 || ky == N / 2 || kz == N / 2);
-    if (nyq || (kx == 0 && ky == 0 && kz == 0)) {
-      for (int c = 0; c < 3; ++c) {
-        O[o + 2 * c * S].x = 0;
-        O[o + 2 * c * S].y = 0;
-      }
-      continue;
-    }
-    // the per-mode arithmetic runs in the grid's precision R (the multipliers are tabulated
-    // in FP64 and rounded once).  F, T below are twice the split spectra
-    // F^ = (Z(k) + conj Z(-k)) / 2, T^ = (Z(k) - conj Z(-k)) / 2i; the halving moves into the
-    // scalar factor Bk (exact: the products scale by powers of two)
-    R Fr[3], Fi[3], Tr[3], Ti[3];
-    for (int c = 0; c < 3; ++c) {
-      const T z = X[o + 2 * c * S], zm = X[om + 2 * c * S];
-      Fr[c] = z.x + zm.x;
-      Fi[c] = z.y - zm.y;
-      Tr[c] = z.y + zm.y;
-      Ti[c] = zm.x - z.x;
-    }
-    // Cartesian wave vector of grid mode m: (2 pi / L)(m_x, m_y - gam m_x, m_z) (the
-    // reciprocal lattice of the sheared lattice; gam = 0 for the cube)
-    // signed mode numbers in [-N/2, N/2] (an even N's N/2 modes were zeroed above; an odd N
-    // keeps the symmetric range), so |m|^2 <= 3 (N/2)^2 indexes the multiplier table
-    const int mx = kx <= N / 2 ? kx : kx - N, my = ky <= N / 2 ? ky : ky - N, mz = kz <= N / 2 ? kz : kz - N;
-    const R k[3] = {R(tp * mx), R(tp * (my - gam * mx)), R(tp * mz)};
-    R sk, jk, Bk, ikn;
-    if (TABLE) {  // the multipliers depend on the integer |m|^2 alone
-      const int m2 = mx * mx + my * my + mz * mz;
-      if constexpr (sizeof(R) == 4) {  // the FP32 copy of the table (the same roundings)
-        const float4 g4 = *reinterpret_cast<const float4*>(wp.gtab32 + 8 * m2);
-        sk = g4.x;
-        jk = g4.y;
-        Bk = wp.brownian ? g4.w : g4.z;
-        ikn = wp.gtab32[8 * m2 + 4];
-      } else {
-        const double* gt = wp.gtab + 5 * m2;
-        sk = R(gt[0]);
-        jk = R(gt[1]);
-        Bk = R(wp.brownian ? gt[3] : gt[2]);
-        ikn = R(gt[4]);
-      }
-    } else {
-      const double kd[3] = {tp * mx, tp * (my - gam * mx), tp * mz};
-      const double k2 = kd[0] * kd[0] + kd[1] * kd[1] + kd[2] * kd[2];
-      const double kn = sqrt(k2);
-      double skd, jkd;
-      sinc_jv_d(kn * wp.a, skd, jkd);
-      const double qq = k2 / (4.0 * wp.xi * wp.xi);
-      const double damp = (1.0 + qq) * exp(-(1.0 - wp.eta_t) * qq) / wp.eta;
-      sk = R(skd);
-      jk = R(jkd);
-      ikn = R(1.0 / kn);
-      Bk = R(wp.brownian ? sqrt(wp.scale / (double(N) * N * N) * damp) / kn : wp.scale * damp / k2);
-    }
-    Bk *= R(0.5);
-    const R hjk = R(0.5) * jk;
-    const R kh[3] = {k[0] * ikn, k[1] * ikn, k[2] * ikn};
-    R gr[3], gi[3];
-    if (wp.brownian) {
-      for (int a = 0; a < 3; ++a) {
-        gr[a] = Fr[a];
-        gi[a] = Fi[a];
-      }
-    } else {
-      const R cxr[3] = {k[1] * Tr[2] - k[2] * Tr[1], k[2] * Tr[0] - k[0] * Tr[2], k[0] * Tr[1] - k[1] * Tr[0]};
-      const R cxi[3] = {k[1] * Ti[2] - k[2] * Ti[1], k[2] * Ti[0] - k[0] * Ti[2], k[0] * Ti[1] - k[1] * Ti[0]};
-      for (int a = 0; a < 3; ++a) {
-        gr[a] = sk * Fr[a] - hjk * cxi[a];
-        gi[a] = sk * Fi[a] + hjk * cxr[a];
-      }
-    }
-    const R pr = kh[0] * gr[0] + kh[1] * gr[1] + kh[2] * gr[2];
-    const R pim = kh[0] * gi[0] + kh[1] * gi[1] + kh[2] * gi[2];
-    R ur[3], ui[3];
-    for (int a = 0; a < 3; ++a) {
-      ur[a] = Bk * (gr[a] - pr * kh[a]);
-      ui[a] = Bk * (gi[a] - pim * kh[a]);
-    }
-    // U^ = sinc u^, W^ = (i/2) jv (k x u^); Y^ = U^ + i W^
-    const R kur[3] = {k[1] * ur[2] - k[2] * ur[1], k[2] * ur[0] - k[0] * ur[2], k[0] * ur[1] - k[1] * ur[0]};
-    const R kui[3] = {k[1] * ui[2] - k[2] * ui[1], k[2] * ui[0] - k[0] * ui[2], k[0] * ui[1] - k[1] * ui[0]};
-    for (int c = 0; c < 3; ++c) {
-      const R Ur = sk * ur[c], Ui = sk * ui[c];
-      const R Wr = -hjk * kui[c], Wi = hjk * kur[c];
-      T y;
-      y.x = Ur - Wi;
-      y.y = Ui + Wr;
-      O[o + 2 * c * S] = y;
-    }
-  }
-  __syncthreads();
-  for (int t = threadIdx.x; t < N; t += blockDim.x) tw[t].y = -tw[t].y;
-  __syncthreads();
-  const T* Y = stockham_lm_any<T, R>(O, X, tw, N, S, NL, plan, +1);
-  for (int t = threadIdx.x; t < NL * N; t += blockDim.x) {
-    int line, x;
-    dn.divmod(t, line, x);
-    const int g = line / 6, c = (line % 6) >> 1, q = line & 1;
-    const int row = rows[2 * g + q].w;
-    if (row < 0) continue;
-    const T y = Y[line * S + x];
-    stg2(grid, unsigned(c * cs) + 2 * unsigned(row * N + x), y.x, y.y);
-  }
-}
-
-template <typename R, bool TABLE>
-__global__ __launch_bounds__(256) void k_fft_xgreen(R* __restrict__ grid, size_t cs, FftPlan plan,
-                                                    const R* __restrict__ twiddle, WaveParams wp, int G,
-                                                    const int* __restrict__ skip) {
-  fft_xgreen_body<R, TABLE>(grid, cs, plan, twiddle, wp, G, skip, blockIdx.x, blockIdx.y, gridDim.x);
-}
-
-// row slots per workgroup of the x+Green pass (measured: 2 is fastest at 64^3 and 128^3)
-int fft_green_rows(int N) { return N >= 256 ? 1 : N >= 64 ? 2 : 256 / N; }
-
-bool tile_b_fits(int N, int B, int rbytes) {
-  return B >= 1 && (B & (B - 1)) == 0 && N % B == 0 &&
-         size_t(2 * rbytes) * (2 * size_t(B) * fft_line_stride(N, B, 2 * rbytes) + N) <= (size_t(64) << 10);
-}
-
-bool tile_g_fits(int N, int G, int rbytes) {
-  return G >= 1 && G <= 16 && xgreen_shm(N, G, 2 * rbytes) <= (size_t(64) << 10);
-}
-
-// lines per workgroup of the coalesced y/z passes: largest B in {16, 8, 4, 2, 1} dividing N
-// whose two LDS buffers and twiddles fit in 64 KB
-int fft_lines_b(int N, int rbytes) {
-  for (int B = 16; B > 1; B /= 2)
-    if (tile_b_fits(N, B, rbytes)) return B;
-  return 1;
-}
-
-int lines_b_of(const WaveParams& wp, int rbytes) {
-  return wp.tile_b > 0 && tile_b_fits(wp.n, wp.tile_b, rbytes) ? wp.tile_b : fft_lines_b(wp.n, rbytes);
-}
-
-int green_g_of(const WaveParams& wp) {
-  return wp.tile_g > 0 && tile_g_fits(wp.n, wp.tile_g, 8) ? wp.tile_g : fft_green_rows(wp.n);
-}
-
-template <typename R>
-void launch_wave_fft(R* grid, const FftPlan& plan, const R* twiddle, const WaveParams& wp, int stage,
-                     hipStream_t st, const int* skip) {
-  using T = typename C2<R>::T;
-  const int N = plan.n;
-  const size_t cs = 2 * size_t(N) * N * N;
-  if (stage == 2) {
-    const int G = green_g_of(wp);
-    const size_t shm = xgreen_shm(N, G, int(sizeof(T)));
-    const int nblk = (N * N / 2 + 2 + G - 1) / G;
-    if (wp.gtab && !wp.gam)  // the cube: tabulated multipliers
-      launch_k(k_fft_xgreen<R, true>, nblk, kThreads, shm, st, grid, cs, plan, twiddle, wp, G, skip);
-    else
-      launch_k(k_fft_xgreen<R, false>, nblk, kThreads, shm, st, grid, cs, plan, twiddle, wp, G, skip);
-  } else {
-    const int B = lines_b_of(wp, sizeof(R));
-    const size_t shm = sizeof(T) * (2 * size_t(B) * fft_line_stride(N, B, int(sizeof(T))) + N);
-    dim3 g(N * N / B, 3);
-    const int sign = stage < 2 ? -1 : +1;
-    if (stage == 0 || stage == 4)
-      launch_k(k_fft_lines<R, 2>, g, kThreads, shm, st, grid, cs, plan, twiddle, sign, B, skip);
-    else
-      launch_k(k_fft_lines<R, 1>, g, kThreads, shm, st, grid, cs, plan, twiddle, sign, B, skip);
-  }
-}
-
-// ------------------------------------------------------------------------------------------
 // multi-system launches: block -> (system, local block) by the prefix table, then the
 // single-system body with that system's pointers (the Arnoldi step maps z -> w)
 // ------------------------------------------------------------------------------------------
 
 namespace {
-
-template <typename R>
-__device__ inline const R* pick(const double* a, const float* b);
-template <>
-__device__ inline const double* pick<double>(const double* a, const float*) {
-  return a;
-}
-template <>
-__device__ inline const float* pick<float>(const double*, const float* b) {
-  return b;
-}
 
 constexpr int kBatchLpr = 16;  // lanes per bead row of the batched real-space sum
 constexpr int kBatchRealPasses = 4;  // row passes per workgroup there: the other systems fill the chip
@@ -2207,28 +1353,6 @@ __global__ __launch_bounds__(256, 4) void kb_spread(const BatchDesc* __restrict_
                              blockIdx.x - off[s]);
 }
 
-template <typename R, int STAGE>
-__global__ __launch_bounds__(256) void kb_fft(const BatchDesc* __restrict__ D, const int* __restrict__ off,
-                                             int nsys) {
-  const int s = batch_system(off, nsys, blockIdx.x);
-  const BatchDesc& d = D[s];
-  const int lb = blockIdx.x - off[s];
-  const int N = d.plan.n;
-  const size_t cs = 2 * size_t(N) * N * N;
-  R* grid = static_cast<R*>(d.grid);
-  const R* tw = pick<R>(d.tw64, d.tw32);
-  const int* stop = &d.ctl->stop;
-  if (STAGE == 2) {  // multi-system launches hold cubic systems only (fusable)
-    fft_xgreen_body<R, true>(grid, cs, d.plan, tw, d.wp, d.bg, stop, lb, 0, 0);
-  } else {
-    const int gx = N * N / d.bl;
-    if (STAGE == 0 || STAGE == 4)
-      fft_lines_body<R, 2>(grid, cs, d.plan, tw, STAGE == 0 ? -1 : +1, d.bl, stop, lb % gx, lb / gx, gx);
-    else
-      fft_lines_body<R, 1>(grid, cs, d.plan, tw, STAGE == 1 ? -1 : +1, d.bl, stop, lb % gx, lb / gx, gx);
-  }
-}
-
 template <typename R>
 __global__ __launch_bounds__(256) void kb_interp(const BatchDesc* __restrict__ D, const int* __restrict__ off,
                                                 int nsys) {
@@ -2253,8 +1377,7 @@ void spread_plan_desc(const SpreadPlan* sp, BatchDesc& d) {
   d.nbin = ok ? sp->nbin : 0;
 }
 
-int batch_blocks(const BatchDesc& d, int kind) {
-  const int N = d.plan.n;
+int batch_blocks(const BatchDesc& d, int kind, int prec) {
   switch (kind) {
     case BK_PRECOND:
     case BK_AGG:
@@ -2265,9 +1388,8 @@ int batch_blocks(const BatchDesc& d, int kind) {
       return d.nbin * d.nbin * d.nbin;
     case BK_FFT_OUTER:
     case BK_FFT_MID:
-      return N * N / d.bl * 3;
     case BK_FFT_GREEN:
-      return (N * N / 2 + 2 + d.bg - 1) / d.bg;
+      return batch_fft_blocks(d, kind, prec);
     case BK_INTERP:
       return (d.nb + 3) / 4;
     case BK_CGS:
@@ -2278,8 +1400,6 @@ int batch_blocks(const BatchDesc& d, int kind) {
 }
 
 size_t batch_shm(const BatchDesc& d, int kind, int prec) {
-  const size_t rb = prec ? sizeof(float) : sizeof(double), tb = 2 * rb;
-  const size_t N = d.plan.n;
   switch (kind) {
     case BK_REAL:
       return prec ? RealPoly<float>::kBytes : RealPoly<double>::kBytes;
@@ -2287,9 +1407,8 @@ size_t batch_shm(const BatchDesc& d, int kind, int prec) {
       return prec ? SpreadTile<float, false>::kBytes : SpreadTile<double, false>::kBytes;
     case BK_FFT_OUTER:
     case BK_FFT_MID:
-      return tb * (2 * size_t(d.bl) * fft_line_stride(int(N), d.bl, int(tb)) + N);
     case BK_FFT_GREEN:
-      return xgreen_shm(int(N), d.bg, int(tb));
+      return batch_fft_shm(d, kind, prec);
     default:
       return 0;
   }
@@ -2297,7 +1416,7 @@ size_t batch_shm(const BatchDesc& d, int kind, int prec) {
 
 namespace {
 template <typename R>
-void batch_mobility(int kind, int stage, const BatchDesc* D, const int* off, int nsys, int total, size_t shm,
+void batch_mobility(int kind, const BatchDesc* D, const int* off, int nsys, int total, size_t shm,
                     hipStream_t st) {
   switch (kind) {
     case BK_REAL:
@@ -2305,21 +1424,6 @@ void batch_mobility(int kind, int stage, const BatchDesc* D, const int* off, int
       break;
     case BK_SPREAD:
       kb_spread<R><<<total, 256, shm, st>>>(D, off, nsys);
-      break;
-    case BK_FFT_OUTER:
-      if (stage == 0)
-        kb_fft<R, 0><<<total, kThreads, shm, st>>>(D, off, nsys);
-      else
-        kb_fft<R, 4><<<total, kThreads, shm, st>>>(D, off, nsys);
-      break;
-    case BK_FFT_MID:
-      if (stage == 1)
-        kb_fft<R, 1><<<total, kThreads, shm, st>>>(D, off, nsys);
-      else
-        kb_fft<R, 3><<<total, kThreads, shm, st>>>(D, off, nsys);
-      break;
-    case BK_FFT_GREEN:
-      kb_fft<R, 2><<<total, kThreads, shm, st>>>(D, off, nsys);
       break;
     case BK_INTERP:
       kb_interp<R><<<total, kThreads, 0, st>>>(D, off, nsys);
@@ -2333,16 +1437,14 @@ void batch_mobility(int kind, int stage, const BatchDesc* D, const int* off, int
 void launch_batch_mobility(int kind, int prec, int stage, const BatchDesc* D, const int* off, int nsys, int total,
                            size_t shm, hipStream_t st) {
   if (total <= 0) return;
-  if (prec)
-    batch_mobility<float>(kind, stage, D, off, nsys, total, shm, st);
+  if (kind == BK_FFT_OUTER || kind == BK_FFT_MID || kind == BK_FFT_GREEN)
+    launch_batch_fft(prec, stage, D, off, nsys, total, shm, st);
+  else if (prec)
+    batch_mobility<float>(kind, D, off, nsys, total, shm, st);
   else
-    batch_mobility<double>(kind, stage, D, off, nsys, total, shm, st);
+    batch_mobility<double>(kind, D, off, nsys, total, shm, st);
 }
 
-template void launch_wave_fft<double>(double*, const FftPlan&, const double*, const WaveParams&, int, hipStream_t,
-                                      const int*);
-template void launch_wave_fft<float>(float*, const FftPlan&, const float*, const WaveParams&, int, hipStream_t,
-                                     const int*);
 template void launch_spread_gather<double>(const SpreadPlan*, const double*, const WaveParams&, double*, hipStream_t, const int*);
 template void launch_spread_gather<float>(const SpreadPlan*, const double*, const WaveParams&, float*, hipStream_t, const int*);
 template void launch_spread_fused<double>(const SpreadPlan*, const double*, const WaveParams&, double*, const double*,
@@ -2367,55 +1469,4 @@ template void launch_interp_sheared<double>(int, const double*, const double*, c
                                             const int*, const int*, const double*, const double*);
 template void launch_interp_sheared<float>(int, const double*, const float*, const WaveParams&, double*, hipStream_t,
                                            const int*, const int*, const double*, const double*);
-// ------------------------------------------------------------------------------------------
-// the allocation-free transform (fsd_fft3d_noalloc): its twiddle table lives in file-scope
-// device memory, one copy per GPU held until the process ends, sized for the largest n
-// ------------------------------------------------------------------------------------------
-
-static __device__ __align__(256) double scratch[2 * kNoAllocFftMax];
-
-// exp(-2 pi i t / n) for t < n, interleaved (re, im)
-__global__ void k_twiddles(int n, double* __restrict__ tw) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n) return;
-  double sv, cv;
-  sincospi(2.0 * double(t) / double(n), &sv, &cv);
-  tw[2 * t] = cv;
-  tw[2 * t + 1] = -sv;
-}
-
-namespace {
-std::mutex g_scratch_mu;
-double* g_scratch_ptr[kMaxDevices] = {nullptr};
-}  // namespace
-
-// the device address of this GPU's copy of `scratch`, looked up once per device
-hipError_t noalloc_scratch(double** out) {
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-  std::lock_guard<std::mutex> lock(g_scratch_mu);
-  if (!g_scratch_ptr[dev]) {
-    void* p = nullptr;
-    e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-    if (e != hipSuccess) return e;
-    g_scratch_ptr[dev] = static_cast<double*>(p);
-  }
-  *out = g_scratch_ptr[dev];
-  return hipSuccess;
-}
-
-hipError_t launch_fft3d_noalloc(int n, int sign, double* data, const FftPlan& plan, hipStream_t st) {
-  double* tw = nullptr;
-  hipError_t e = noalloc_scratch(&tw);
-  if (e != hipSuccess) return e;
-  k_twiddles<<<(n + 255) / 256, 256, 0, st>>>(n, tw);
-  launch_fft3d<double>(data, 1, 2 * size_t(n) * n * n, plan, tw, sign, st);
-  return hipGetLastError();
-}
-
-template void launch_fft3d<double>(double*, int, size_t, const FftPlan&, const double*, int, hipStream_t, int, const int*);
-template void launch_fft3d<float>(float*, int, size_t, const FftPlan&, const float*, int, hipStream_t, int, const int*);
-
 }  // namespace fsd
