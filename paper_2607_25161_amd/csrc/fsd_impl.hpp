@@ -166,7 +166,7 @@ void launch_real_sum(int nb, const double* pos4, const double* lam, const int* r
 template <typename R>
 void launch_spread(int nb, const double* pos4, const double* lam, const WaveParams& wp, R* grid,
                    hipStream_t st, const int* skip = nullptr);
-// Spreading (grids without 8^3 blocks) and interpolation on a sheared lattice (wp.gam): grid point
+// Spreading and interpolation on a sheared lattice (wp.gam) without a plan (no 8^3 blocks): grid point
 // (i, j, k) sits at sheared coordinates (i, j, k) h, and each grid row j takes the P x-points
 // around its own centre p_x - gam (j h - p_y).  Spreading scatters with atomic adds into a
 // zeroed grid; interpolation adds into out as launch_interp does (with V: + Sigma^T V).

@@ -842,7 +842,7 @@ void mob_fft(fsd_system* s, int stage, const int* skip) {
 
 template <typename R>
 void mob_interp(fsd_system* s, double* out, const int* skip, const double* Vr) {
-  if (s->le) {
+  if (s->le && !s->spread) {
     launch_interp_sheared<R>(s->nb, s->d_pos4, static_cast<const R*>(s->d_grid), s->wp, out, s->st, skip, s->d_body,
                              s->d_r4, Vr);
     return;

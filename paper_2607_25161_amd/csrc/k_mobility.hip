@@ -464,39 +464,20 @@ void launch_interp_sheared(int nb, const double* pos4, const R* grid, const Wave
            body, (const double4*)r4, V);
 }
 
+// Interpolation on grids without a plan: one wavefront per bead, weights computed here.
 template <typename R>
-__device__ __forceinline__ void interp_body(int nb, const double4* __restrict__ pos,
+__global__ __launch_bounds__(256) void k_interp(int nb, const double4* __restrict__ pos,
                                                 const R* __restrict__ grid, size_t cs, WaveParams wp,
                                                 double* __restrict__ out, const int* __restrict__ skip,
                                                 const int* __restrict__ body, const double4* __restrict__ r4,
-                                                const double* __restrict__ V, const int* __restrict__ order,
-                                                const int4* __restrict__ ostart, const R* __restrict__ ow,
-                                                int bx_, int by_, int gx_) {
+                                                const double* __restrict__ V) {
   if (skip && *skip) return;
-  // one wavefront per bead.  With order (the spreading plan's sorted beads, their
-  // support starts and weights), beads are visited in spatial order, each XCD taking one
-  // contiguous range, and the weights come from the plan instead of being recomputed.
   __shared__ R wts[4][3 * kMaxP];
   __shared__ int sta[4][3];
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int nblk = gx_ > 0 ? gx_ : (nb + 3) / 4;
-  const int k = (order ? xcd_remap(bx_, nblk) : bx_) * 4 + wv;
-  const bool live = k < nb;
-  const int i = live ? (order ? order[k] : k) : 0;
-  if (live) {
-    if (order) {
-      const int P = wp.support;
-      if (lane < 3 * P) wts[wv][(lane / P) * kMaxP + lane % P] = ow[size_t(k) * 3 * P + lane];
-      if (lane == 0) {
-        const int4 s4 = ostart[k];
-        sta[wv][0] = s4.x;
-        sta[wv][1] = s4.y;
-        sta[wv][2] = s4.z;
-      }
-    } else {
-      axis_weights<R>(pos[i], wp, lane, wts[wv], sta[wv]);
-    }
-  }
+  const int i = blockIdx.x * 4 + wv;
+  const bool live = i < nb;
+  if (live) axis_weights<R>(pos[i], wp, lane, wts[wv], sta[wv]);
   __syncthreads();
   if (!live) return;
   const int P = wp.support, N = wp.n;
@@ -595,33 +576,6 @@ __device__ __forceinline__ void interp_body(int nb, const double4* __restrict__ 
     }
     for (int k = 0; k < 6; ++k) o[k] += add[k];
   }
-}
-
-template <typename R>
-__global__ __launch_bounds__(256) void k_interp(int nb, const double4* __restrict__ pos,
-                                                const R* __restrict__ grid, size_t cs, WaveParams wp,
-                                                double* __restrict__ out, const int* __restrict__ skip,
-                                                const int* __restrict__ body, const double4* __restrict__ r4,
-                                                const double* __restrict__ V,
-                                                const int* __restrict__ order, const int4* __restrict__ ostart,
-                                                const R* __restrict__ ow) {
-  interp_body<R>(nb, pos, grid, cs, wp, out, skip, body, r4, V, order, ostart, ow, blockIdx.x, blockIdx.y, gridDim.x);
-}
-
-template <typename R>
-void launch_interp(int nb, const double* pos4, const R* grid, const WaveParams& wp, double* out, hipStream_t st,
-                   const int* skip, const int* body, const double* r4, const double* V, const SpreadPlan* sp) {
-  const size_t cs = 2 * size_t(wp.n) * wp.n * wp.n;
-  const R* ow = nullptr;
-  if (sp) {
-    if (std::is_same<R, double>::value)
-      ow = reinterpret_cast<const R*>(sp->weights);
-    else
-      ow = reinterpret_cast<const R*>(sp->weights32);
-  }
-  launch_k(k_interp<R>, nblocks(nb, 4), kThreads, 0, st, nb, (const double4*)pos4, grid, cs, wp, out, skip, body,
-                                                   (const double4*)r4, V, sp ? sp->perm : nullptr,
-                                                   sp ? sp->starts : nullptr, ow);
 }
 
 const int* spread_plan_order(const SpreadPlan* sp) { return sp ? sp->perm : nullptr; }
@@ -1056,6 +1010,9 @@ __device__ __forceinline__ Acc64 mma4(double a, double b, Acc64 c) {
 __device__ __forceinline__ Acc32 mma4(float a, float b, Acc32 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
+// Up to here four wavefronts share a bead in interpolation: 32 beads at P = 14 take 5.3 us instead of
+// 11.8, 2,048 at P = 11 11.4 instead of 9.7 (FP64)
+constexpr int kShareBeads = 512;
 template <typename R>
 struct AccOf {
   using T = Acc64;
@@ -1321,6 +1278,214 @@ void launch_spread_fused(const SpreadPlan* sp, const double* lam, const WavePara
 }
 
 // ------------------------------------------------------------------------------------------
+// Interpolation with a plan: beads in the plan's spatial order, its weights and starts
+// ------------------------------------------------------------------------------------------
+
+// What interpolation reads of a plan.
+template <typename R>
+struct BeadArgs {
+  const int* perm;
+  const int4* starts;
+  const short* rows;
+  const R* weights;
+};
+
+// a wavefront-uniform load, through the scalar cache
+template <typename T>
+__device__ __forceinline__ T uload(const T* p, size_t i) {
+  return ((__attribute__((address_space(4))) const T*)p)[i];
+}
+
+// a += b with the halves of the wavefront (the 16-lane rows of each half) merged: afterwards the
+// lower half (the even rows) holds the sums of a, the upper half (the odd rows) those of b
+__device__ __forceinline__ float merge32(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float merge16(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ double merge32(double a, double b) {
+  const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+}
+__device__ __forceinline__ double merge16(double a, double b) {
+  const auto l = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+}
+template <int CTRL>
+__device__ __forceinline__ float row_move(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double row_move(double v) {
+  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true),
+                          __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true));
+}
+template <typename R>
+__device__ __forceinline__ R row_sum(R v) {  // over the 16 lanes of a row, in every lane
+  v += row_move<0x128>(v);
+  v += row_move<0x124>(v);
+  v += row_move<0x122>(v);
+  v += row_move<0x121>(v);
+  return v;
+}
+
+// out_i += the grid's velocities at bead i (+ Sigma^T V): sum over the P^3 support points of
+// w_x w_y w_z times six components.  Lanes take (x, y) columns of the support and walk z: in FP32
+// pairs of x points (one aligned 16-byte load, points outside the support weighted 0), in FP64
+// single columns (with pairs the wider support and the registers cost more than the loads save).
+// What bounds it is the 48 P^3 (24 in FP32) bytes a bead that pass through the CU's first-level
+// cache, so the rest is kept out of the way: the bead's order, start and w_z come through the
+// scalar cache, its other weights by one load per lane, nothing goes through LDS, and the six sums are merged by lane swaps (6 -> 3 -> 2 values) before they are reduced.
+// WPB wavefronts share a bead when there are too few beads to fill the chip: two halves of the
+// columns times two halves of z, joined through LDS.
+// Measured: 32 beads FP64 11.8 -> 5.3 us, 2,048 on 64^3 11.0 -> 9.7; on the sheared lattice, where weights
+// and row starts were recomputed for every apply, 2,048 FP64 21 -> 12 us, 6,011 FP32 36 -> 16.
+template <typename R, bool SHEAR, int WPB>
+__device__ __forceinline__ void interp_plan_body(int nb, const BeadArgs<R>& ba, const R* __restrict__ grid,
+                                                 size_t cs, const WaveParams& wp, double* __restrict__ out,
+                                                 const int* __restrict__ skip, const int* __restrict__ body,
+                                                 const double4* __restrict__ r4, const double* __restrict__ V, int bx,
+                                                 int nblk) {
+  if (skip && *skip) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int k = xcd_remap(bx, nblk) * (4 / WPB) + (WPB == 1 ? wave : 0);
+  if (k >= nb) return;  // whole wavefronts (WPB 1), whole workgroups (WPB 4)
+  const int P = wp.support, N = wp.n, wlen = SHEAR ? P * P + P : 3 * P;
+  const int i = uload(ba.perm, k);
+  const int sx = uload(&ba.starts[k].x, 0), sy = uload(&ba.starts[k].y, 0), sz = uload(&ba.starts[k].z, 0);
+  const R* w = ba.weights + size_t(k) * wlen;
+  const unsigned plane = 2u * N * N;
+  const int n1 = min(P, N - sz);  // planes before the columns wrap to z = 0
+  const int zh = WPB == 1 ? 0 : (P + 1) / 2, z0 = WPB > 1 && wave >= 2 ? zh : 0, z1 = WPB > 1 && wave < 2 ? zh : P;
+  const R *g0 = grid, *g1 = grid + cs, *g2 = grid + 2 * cs;
+  R a[6] = {0, 0, 0, 0, 0, 0};
+  constexpr bool kPaired = sizeof(R) == 4;
+  const int ncol = kPaired ? P / 2 + 1 : P;  // columns, or pairs that can touch the support, per row
+  for (int q = lane + (WPB == 1 ? 0 : 64 * (wave & 1)); q < ncol * P; q += WPB == 1 ? 64 : 128) {
+    const int ky = q / ncol, cx = q - ky * ncol;
+    int y = sy + ky;
+    y -= y >= N ? N : 0;
+    const int s = SHEAR ? int(ba.rows[size_t(k) * P + ky]) : sx;
+    const R wy = SHEAR ? R(1) : w[P + ky];
+    const R* wrow = SHEAR ? w + ky * P : w;
+    R wa, wb = 0;
+    int x;
+    if (kPaired) {
+      const int k0 = 2 * cx - (s & 1);  // support offset of the pair's first point, from -1
+      x = (s & ~1) + 2 * cx;
+      wa = k0 >= 0 && k0 < P ? wrow[k0] * wy : R(0);
+      wb = k0 + 1 < P ? wrow[k0 + 1] * wy : R(0);
+    } else {
+      x = s + cx;
+      wa = wrow[cx] * wy;
+    }
+    x -= x >= N ? N : 0;
+    const unsigned col = 2u * (y * N + x);
+    unsigned off = col + unsigned(z0 < n1 ? sz + z0 : z0 - n1) * plane;
+#pragma unroll 4
+    for (int kz = z0; kz < z1; ++kz) {
+      if (kz == n1) off = col;
+      const R wz = uload(w, wlen - P + kz);
+      if (kPaired) {
+        const R u0 = wa * wz, u1 = wb * wz;
+        R b0, b1, b2, b3;
+        ldg4(g0, off, b0, b1, b2, b3);
+        a[0] += u0 * b0 + u1 * b2;
+        a[3] += u0 * b1 + u1 * b3;
+        ldg4(g1, off, b0, b1, b2, b3);
+        a[1] += u0 * b0 + u1 * b2;
+        a[4] += u0 * b1 + u1 * b3;
+        ldg4(g2, off, b0, b1, b2, b3);
+        a[2] += u0 * b0 + u1 * b2;
+        a[5] += u0 * b1 + u1 * b3;
+      } else {
+        const R u = wa * wz;
+        R f, t;
+        ldg2(g0, off, f, t);
+        a[0] += u * f;
+        a[3] += u * t;
+        ldg2(g1, off, f, t);
+        a[1] += u * f;
+        a[4] += u * t;
+        ldg2(g2, off, f, t);
+        a[2] += u * f;
+        a[5] += u * t;
+      }
+      off += plane;
+    }
+  }
+  // velocities to the lower half of the wavefront, angular velocities to the upper; then components
+  // 0 and 1 to the even and odd rows, component 2 to both
+  R s0 = merge32(a[0], a[3]), s1 = merge32(a[1], a[4]), s2 = merge32(a[2], a[5]);
+  s0 = row_sum(merge16(s0, s1));
+  s2 = row_sum(merge16(s2, s2));
+  if (WPB > 1) {
+    __shared__ R part[WPB][6];
+    if ((lane & 15) == 0) {
+      const int h = 3 * (lane >> 5), c = (lane >> 4) & 1;
+      part[wave][h + c] = s0;
+      if (c == 0) part[wave][h + 2] = s2;
+    }
+    __syncthreads();
+    if (wave) return;
+    const int h = 3 * (lane >> 5), c = (lane >> 4) & 1;
+    s0 = part[0][h + c] + part[1][h + c] + (part[2][h + c] + part[3][h + c]);
+    s2 = part[0][h + 2] + part[1][h + 2] + (part[2][h + 2] + part[3][h + 2]);
+  }
+  if (lane & 15) return;
+  const int c = (lane >> 4) & 1;  // this lane's components: c, and 2 in an even row
+  double add0 = double(s0), add2 = double(s2);
+  if (V) {  // Sigma^T V: (U + W x r, W) of the bead's body
+    const double* v = V + 6 * size_t(body[i]);
+    const double4 r = r4[i];
+    if (lane < 32) {
+      add0 += c ? v[1] + (v[5] * r.x - v[3] * r.z) : v[0] + (v[4] * r.z - v[5] * r.y);
+      add2 += v[2] + (v[3] * r.y - v[4] * r.x);
+    } else {
+      add0 += v[3 + c];
+      add2 += v[5];
+    }
+  }
+  double* o = out + 6 * size_t(i) + 3 * (lane >> 5);
+  o[c] += add0;
+  if (c == 0) o[2] += add2;
+}
+
+template <typename R, bool SHEAR, int WPB>
+__global__ __launch_bounds__(256) void k_interp_plan(int nb, BeadArgs<R> ba, const R* __restrict__ grid, size_t cs,
+                                                     WaveParams wp, double* __restrict__ out,
+                                                     const int* __restrict__ skip, const int* __restrict__ body,
+                                                     const double4* __restrict__ r4, const double* __restrict__ V) {
+  interp_plan_body<R, SHEAR, WPB>(nb, ba, grid, cs, wp, out, skip, body, r4, V, blockIdx.x, gridDim.x);
+}
+
+template <typename R>
+void launch_interp(int nb, const double* pos4, const R* grid, const WaveParams& wp, double* out, hipStream_t st,
+                   const int* skip, const int* body, const double* r4, const double* V, const SpreadPlan* sp) {
+  const size_t cs = 2 * size_t(wp.n) * wp.n * wp.n;
+  const double4* r = (const double4*)r4;
+  if (!sp) {
+    launch_k(k_interp<R>, nblocks(nb, 4), kThreads, 0, st, nb, (const double4*)pos4, grid, cs, wp, out, skip, body, r, V);
+    return;
+  }
+  const BeadArgs<R> ba{sp->perm, sp->starts, sp->rows, plan_weights<R>(sp)};
+  const bool share = nb <= kShareBeads;
+#define FSD_INTERP(S_, W_) \
+  launch_k(k_interp_plan<R, S_, W_>, nblocks(nb, 4 / W_), kThreads, 0, st, nb, ba, grid, cs, wp, out, skip, body, r, V)
+  if (sp->sheared) {
+    if (share) FSD_INTERP(true, 4); else FSD_INTERP(true, 1);
+  } else {
+    if (share) FSD_INTERP(false, 4); else FSD_INTERP(false, 1);
+  }
+#undef FSD_INTERP
+}
+
+// ------------------------------------------------------------------------------------------
 // multi-system launches: block -> (system, local block) by the prefix table, then the
 // single-system body with that system's pointers (the Arnoldi step maps z -> w)
 // ------------------------------------------------------------------------------------------
@@ -1359,9 +1524,9 @@ __global__ __launch_bounds__(256) void kb_interp(const BatchDesc* __restrict__ D
   const int s = batch_system(off, nsys, blockIdx.x);
   const BatchDesc& d = D[s];
   const size_t cs = 2 * size_t(d.wp.n) * d.wp.n * d.wp.n;
-  interp_body<R>(d.nb, (const double4*)d.pos4, static_cast<const R*>(d.grid), cs, d.wp, d.w, &d.ctl->stop, d.body,
-                 (const double4*)d.r4, d.z + 6 * size_t(d.nb), d.perm, d.starts, pick<R>(d.w64, d.w32),
-                 blockIdx.x - off[s], 0, 0);
+  interp_plan_body<R, false, 1>(d.nb, {d.perm, d.starts, nullptr, pick<R>(d.w64, d.w32)},
+                                static_cast<const R*>(d.grid), cs, d.wp, d.w, &d.ctl->stop, d.body,
+                                (const double4*)d.r4, d.z + 6 * size_t(d.nb), blockIdx.x - off[s], off[s + 1] - off[s]);
 }
 
 // spreading fields of a batch descriptor (blk_start == nullptr: no plan of 8^3 blocks)
