@@ -254,7 +254,8 @@ void launch_pair_forces(int nb, const double* pos4, const int* body, const int* 
 // *flag |= 1 when beads of different bodies in the real-space list are closer than 1.5 a
 void launch_overlap_check(int nb, const double* pos4, const int* body, const int* rowptr, const uint32_t* col,
                           double L, double gam, double a, int* flag, hipStream_t st);
-void launch_lub_apply(int nb, const int* rowptr, const uint32_t* col, const double* coef,
+// f = sgn R_nf wt (translational rows)
+void launch_lub_apply(int nb, double sgn, const int* rowptr, const uint32_t* col, const double* coef,
                       const double* wt, double* f, hipStream_t st, const int* skip = nullptr);
 // fused: y2 = Sigma (lambda - R_nf Sigma^T V) with lubrication evaluated on the fly
 // (lrow == nullptr: no lubrication)
@@ -337,10 +338,14 @@ void launch_bead_rigid_vel(int nb, const int* body, const double* r4, const doub
 // S_j = sum_i sym(r_i (F_i + f_i)) per aggregate (9 each); f may be null
 void launch_stresslets(int na, const int* offsets, const double* r4, const double* F, const double* f, double* S,
                        hipStream_t st);
-// Lanczos step k: alpha[k] = h1[k] + h2[k], beta[k] = sqrt(nrm2[0]), scal[0] = 1 / beta[k]
-void launch_lanczos_coef(int k, const double* h1, const double* h2, const double* nrm2, double* alpha, double* beta,
-                         double* scal, hipStream_t st);
-void launch_scale_dev(size_t n, const double* a, const double* x, double* y, hipStream_t st);  // y = a[0] x
+// Passes of a Lanczos step over nq basis vectors of length n (k_lanczos_pass): mode 0, 1, 2 as the
+// CGS chain, on lanczos_blocks(n) workgroups (nq partials each), 3 the norm of w.  coef collects
+// this step's projection on its own vector.  launch_lanczos_next turns the norm's partials into
+// beta and the next vector.
+int lanczos_blocks(size_t n);
+void launch_lanczos_pass(int mode, size_t n, int nq, const double* V, const double* pin, double* w, double* pout,
+                         double* coef, hipStream_t st);
+void launch_lanczos_next(size_t n, const double* pin, const double* w, double* v, double* beta, hipStream_t st);
 
 // ---- Brownian terms (k_brownian.hip) ------------------------------------------------------
 // Noise stream: Philox4x64-10 under key (k0, k1); normal e of the stream comes from the

@@ -327,7 +327,7 @@ struct fsd_system {
   bool psi_w_set = false, psi_r_set = false, psi_nf_set = false;
   double *d_psi_w = nullptr, *d_psi_r = nullptr, *d_psi_nf = nullptr;
   double *d_ub = nullptr, *d_fb = nullptr, *d_lan = nullptr, *d_lc = nullptr, *d_u6 = nullptr;
-  double *d_lh = nullptr, *d_lpart = nullptr;  // Lanczos reorthogonalisation coefficients and partials
+  double *d_lh = nullptr, *d_lpart = nullptr;  // Lanczos coefficients and partial sums
   SpreadPlan* spread = nullptr;  // gather spreading (nullptr: atomic scatter)
   std::vector<double> h_tab, h_tab32;  // the smooth part's coefficients (RealPoly), before rounding to R
 
@@ -993,15 +993,8 @@ void ensure_brownian(fsd_system* s) {
   s->d_psi_nf = dalloc<double>(o, 3 * nb);
   s->d_lan = dalloc<double>(o, size_t(s->lan_max + 1) * 6 * nb);
   s->d_lc = dalloc<double>(o, s->lan_max + 1);
-  s->d_lh = dalloc<double>(o, 5 * size_t(s->lan_max + 2));  // h1, h2, ||w||^2, alpha, beta (and 1/beta)
-  s->d_lpart = dalloc<double>(o, size_t(s->lan_max + 2) * 1024);  // launch_dots partials: <= 1024 blocks
-}
-
-double dev_dot(fsd_system* s, size_t n, const double* x, const double* y) {
-  launch_dots(n, 1, x, n, y, s->d_part, s->d_h, s->d_counters, s->st);
-  HIPCHK(hipMemcpyAsync(s->h_small, s->d_h, sizeof(double), hipMemcpyDeviceToHost, s->st));
-  HIPCHK(hipStreamSynchronize(s->st));
-  return s->h_small[0];
+  s->d_lh = dalloc<double>(o, 2 * size_t(s->lan_max + 2));  // alpha and |z|, beta
+  s->d_lpart = dalloc<double>(o, 2 * size_t(lanczos_blocks(6 * nb)) * (s->lan_max + 1));
 }
 
 // out = A^{1/2} z for a symmetric positive semi-definite operator by the Lanczos
@@ -1011,58 +1004,86 @@ double dev_dot(fsd_system* s, size_t n, const double* x, const double* y) {
 // keeps alpha_k, beta_k and the next vector on the device; the host reads the coefficients
 // every kCheck steps and stops once T^{1/2} e1 changes by less than tol (relative) between
 // two reads, or at a breakdown.  Returns the number of Lanczos steps.
+// A check runs while the GPU works on the next kCheck steps, which are dropped when it stops; the
+// root is the one of the checked steps.  T^{1/2} e1 costs O(k^3) on the host (1 ms at k = 100), so
+// a check first bounds the change from below by the last kCheck entries, O(k^2).
 template <typename Apply>
 int lanczos_sqrt(fsd_system* s, size_t n, Apply&& apply, const double* z, double* out, double tol) {
   constexpr int kCheck = 4;
-  const double b0 = std::sqrt(std::max(dev_dot(s, n, z, z), 0.0));
-  if (b0 == 0.0) {
-    launch_zero(out, sizeof(double) * n, s->st);
-    return 0;
-  }
   const int L = s->lan_max + 2;
-  double *h1 = s->d_lh, *h2 = s->d_lh + L, *nrm2 = s->d_lh + 2 * L, *alpha = s->d_lh + 3 * L,
-         *beta = s->d_lh + 4 * L;
-  double* scal = nrm2 + 1;
+  double *alpha = s->d_lh, *beta = s->d_lh + L, *norm = alpha + L - 1;  // |z| after the alphas
   double* V = s->d_lan;
   double* w = s->d_t;
-  launch_scale(n, 1.0 / b0, z, V, s->st);
-  std::vector<double> al(s->lan_max), be(s->lan_max), prev;
+  double *P0 = s->d_lpart, *P1 = P0 + size_t(lanczos_blocks(n)) * (s->lan_max + 1);
+  hipEvent_t ev[2] = {s->ev_fork, s->ev_join};
+  launch_lanczos_pass(3, n, 1, V, nullptr, const_cast<double*>(z), P0, nullptr, s->st);
+  launch_lanczos_next(n, P0, z, V, norm, s->st);
+  std::vector<double> root;
   int k = 0;
-  for (int j = 0; j < s->lan_max; ++j) {
-    double* vj = V + size_t(j) * n;
-    apply(vj, w);
-    launch_dots(n, j + 1, V, n, w, s->d_lpart, h1, s->d_counters, s->st);
-    launch_axpy_dots(n, j + 1, V, n, h1, w, 0, s->d_lpart, h2, s->d_counters, s->st);
-    launch_axpy_dots(n, j + 1, V, n, h2, w, 1, s->d_lpart, nrm2, s->d_counters, s->st);
-    launch_lanczos_coef(j, h1, h2, nrm2, alpha, beta, scal, s->st);
-    if (j + 1 < s->lan_max) launch_scale_dev(n, scal, w, V + size_t(j + 1) * n, s->st);
-    if ((j + 1) % kCheck != 0 && j + 1 != s->lan_max) continue;
-    HIPCHK(hipMemcpyAsync(s->h_small, alpha, sizeof(double) * (j + 1), hipMemcpyDeviceToHost, s->st));
-    HIPCHK(hipMemcpyAsync(s->h_small + L, beta, sizeof(double) * (j + 1), hipMemcpyDeviceToHost, s->st));
-    HIPCHK(hipStreamSynchronize(s->st));
-    // the first breakdown ends the basis
-    k = j + 1;
-    for (int i = 0; i <= j; ++i)
-      if (s->h_small[L + i] <= 1e-14 * std::fabs(s->h_small[i])) {
+  // whether the root of the first len steps (read-back buffer slot) ends the iteration
+  auto done = [&](int len, int before, int slot) {
+    HIPCHK(hipEventSynchronize(ev[slot]));
+    const double* a = s->h_small + size_t(slot) * 2 * L;
+    const double* b = a + L;
+    if (a[L - 1] == 0.0) return true;  // z = 0
+    k = len;
+    for (int i = 0; i < len; ++i)
+      if (b[i] <= 1e-14 * std::fabs(a[i])) {  // the first breakdown ends the basis
         k = i + 1;
         break;
       }
-    std::vector<double> a(s->h_small, s->h_small + k), b(s->h_small + L, s->h_small + L + std::max(k - 1, 0));
-    std::vector<double> cur = tridiag_sqrt_e1(a, b);
-    double diff = 0, nrm = 0;
-    for (size_t i = 0; i < cur.size(); ++i) {
-      const double d = cur[i] - (i < prev.size() ? prev[i] : 0.0);
-      diff += d * d;
-      nrm += cur[i] * cur[i];
+    const bool last = k < len || len == s->lan_max;
+    const std::vector<double> al(a, a + k), be(b, b + std::max(k - 1, 0));
+    if (!last) {
+      if (before == 0) return false;
+      double tail2, nrm2;
+      tridiag_sqrt_tail(al, be, len - before, tail2, nrm2);
+      if (tail2 > 1.0001 * tol * tol * nrm2) return false;
     }
-    prev.swap(cur);
-    if (diff <= tol * tol * nrm || k <= j || j + 1 == s->lan_max) break;
+    root = tridiag_sqrt_e1(al, be);
+    if (!last) {
+      const std::vector<double> old = tridiag_sqrt_e1({a, a + before}, {b, b + before - 1});
+      double diff = 0, nrm = 0;
+      for (size_t i = 0; i < root.size(); ++i) {
+        const double d = root[i] - (i < old.size() ? old[i] : 0.0);
+        diff += d * d;
+        nrm += root[i] * root[i];
+      }
+      if (!(diff <= tol * tol * nrm)) return false;
+    }
+    for (double& x : root) x *= a[L - 1];
+    return true;
+  };
+  int len = 0, checked = 0, slot = 0;  // steps issued; steps of the last check made
+  bool stop = false;
+  while (!stop && len < s->lan_max) {
+    const int from = len;
+    len = std::min(len + kCheck, s->lan_max);
+    for (int j = from; j < len; ++j) {
+      apply(V + size_t(j) * n, w);
+      launch_lanczos_pass(0, n, j + 1, V, nullptr, w, P0, nullptr, s->st);
+      launch_lanczos_pass(1, n, j + 1, V, P0, w, P1, alpha + j, s->st);
+      launch_lanczos_pass(2, n, j + 1, V, P1, w, P0, alpha + j, s->st);
+      launch_lanczos_next(n, P0, w, j + 1 < s->lan_max ? V + size_t(j + 1) * n : nullptr, beta + j, s->st);
+    }
+    HIPCHK(hipMemcpyAsync(s->h_small + size_t(slot) * 2 * L, alpha, sizeof(double) * 2 * L, hipMemcpyDeviceToHost,
+                          s->st));
+    HIPCHK(hipEventRecord(ev[slot], s->st));
+    if (from > checked) {  // the steps before these
+      stop = done(from, checked, 1 - slot);
+      checked = from;
+    }
+    slot = 1 - slot;
   }
-  std::vector<double> c(prev.size());
-  for (size_t i = 0; i < c.size(); ++i) c[i] = b0 * prev[i];
-  HIPCHK(hipMemcpyAsync(s->d_lc, c.data(), sizeof(double) * c.size(), hipMemcpyHostToDevice, s->st));
-  launch_combine(n, int(c.size()), V, n, s->d_lc, out, s->st);
-  HIPCHK(hipStreamSynchronize(s->st));  // c lives on the host stack
+  if (!stop) done(len, checked, 1 - slot);
+  if (root.empty()) {
+    launch_zero(out, sizeof(double) * n, s->st);
+    return 0;
+  }
+  double* c = s->h_small + 4 * size_t(L);  // free again: its last copy precedes the events waited for above
+  std::copy(root.begin(), root.end(), c);
+  HIPCHK(hipMemcpyAsync(s->d_lc, c, sizeof(double) * root.size(), hipMemcpyHostToDevice, s->st));
+  launch_combine(n, int(root.size()), V, n, s->d_lc, out, s->st);
   return k;
 }
 
@@ -1089,15 +1110,14 @@ void brownian_terms(fsd_system* s) {
       s, 6 * nb, [&](const double* in, double* out) { apply_mobility<double>(s, in, out, 1); }, s->d_psi_r,
       s->d_u6, s->p.lanczos_tol);
   launch_axpby(6 * nb, amp, s->d_u6, amp, s->d_ub, s->st);
-  // near field: Lanczos on R_nf (the lubrication product returns -R_nf w)
+  // near field: Lanczos on R_nf
   const bool lub = s->p.r_lub > 0 && s->nlub > 0;
   if (lub) {
     if (!s->psi_nf_set) launch_normals(3 * nb, kn, s->d_psi_nf, s->st);
     s->lan_its[1] = lanczos_sqrt(
         s, 3 * nb,
         [&](const double* in, double* out) {
-          launch_lub_apply(s->nb, s->d_lrow, s->d_lcol, s->d_lcoef, in, out, s->st);
-          launch_scale(3 * nb, -1.0, out, out, s->st);
+          launch_lub_apply(s->nb, 1.0, s->d_lrow, s->d_lcol, s->d_lcoef, in, out, s->st);
         },
         s->d_psi_nf, s->d_fb, s->p.lanczos_tol);
     launch_scale(3 * nb, amp, s->d_fb, s->d_fb, s->st);
@@ -1685,9 +1705,9 @@ fsd_status fsd_init_aggregates(fsd_system* s, int32_t n_agg, const int32_t* off,
     s->d_h = dalloc<double>(o, 2 * size_t(s->m + 1) + 16);
     s->d_part = dalloc<double>(o, std::max(size_t(s->m + 2) * 1024, size_t(96) * cgs_blocks(n)));
     s->d_U = dalloc<double>(o, 6 * size_t(n_agg));
-    // small read-backs: GMRES columns, and the Lanczos alpha and beta (lan_max + 2 each)
-    HIPCHK(hipHostMalloc((void**)&s->h_small,
-                         sizeof(double) * std::max(2 * size_t(s->m + 1) + 8, 2 * size_t(s->lan_max + 2))));
+    // small read-backs: a norm, and two sets of the Lanczos alpha and beta and a root's coefficients
+    // (lan_max + 2 each)
+    HIPCHK(hipHostMalloc((void**)&s->h_small, sizeof(double) * 5 * size_t(s->lan_max + 2)));
     HIPCHK(hipHostMalloc((void**)&s->h_ctl, sizeof(GmresCtl)));
     s->d_ctl = reinterpret_cast<GmresCtl*>(dalloc<double>(o, (sizeof(GmresCtl) + 7) / 8));
     s->d_H = dalloc<double>(o, size_t(s->m + 1) * s->m);
@@ -1904,7 +1924,7 @@ fsd_status fsd_get_stresslets(fsd_system* s, double* S_agg, double* S_mean) {
     launch_zero(s->d_fst, sizeof(double) * 3 * nb, s->st);
     if (lub) {
       launch_bead_rigid_vel(nb, s->d_body, s->d_r4, s->d_x + nb6, s->d_wst, s->st);
-      launch_lub_apply(nb, s->d_lrow, s->d_lcol, s->d_lcoef, s->d_wst, s->d_fst, s->st);
+      launch_lub_apply(nb, -1.0, s->d_lrow, s->d_lcol, s->d_lcoef, s->d_wst, s->d_fst, s->st);
       launch_lub_strain(nb, s->d_pos4, s->d_r4, s->L, s->gam(), s->d_lrow, s->d_lcol, s->d_lcoef, s->d_E, s->d_wst,
                         s->st);
       launch_axpby(3 * size_t(nb), -1.0, s->d_wst, 1.0, s->d_fst, s->st);

@@ -1,5 +1,7 @@
 // Kernels of the saddle operator outside the mobility, the preconditioner and
 // the FP64 Krylov vector operations.
+#include <algorithm>
+
 #include "fsd_impl.hpp"
 #include "k_rigid.hpp"
 
@@ -95,8 +97,8 @@ void launch_pair_forces(int nb, const double* pos4, const int* body, const int* 
   k_pair_forces<<<nblocks(nb), kThreads, 0, st>>>(nb, (const double4*)pos4, body, rowptr, col, pf, fe, accumulate);
 }
 
-// f_i = -sum_k R_pair,ik (w_i - w_k), R_pair = X nn + Y (I - nn)
-__global__ void k_lub_apply(int nb, const int* __restrict__ rowptr, const uint32_t* __restrict__ col,
+// f_i = sgn sum_k R_pair,ik (w_i - w_k), R_pair = X nn + Y (I - nn)
+__global__ void k_lub_apply(int nb, double sgn, const int* __restrict__ rowptr, const uint32_t* __restrict__ col,
                             const double* __restrict__ coef, const double* __restrict__ wt, double* __restrict__ f, const int* __restrict__ skip) {
   if (skip && *skip) return;
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -113,14 +115,14 @@ __global__ void k_lub_apply(int nb, const int* __restrict__ rowptr, const uint32
     ay += c[1] * dy + g * c[3];
     az += c[1] * dz + g * c[4];
   }
-  f[3 * i] = -ax;
-  f[3 * i + 1] = -ay;
-  f[3 * i + 2] = -az;
+  f[3 * i] = sgn * ax;
+  f[3 * i + 1] = sgn * ay;
+  f[3 * i + 2] = sgn * az;
 }
 
-void launch_lub_apply(int nb, const int* rowptr, const uint32_t* col, const double* coef, const double* wt, double* f,
-                      hipStream_t st, const int* skip) {
-  k_lub_apply<<<nblocks(nb), kThreads, 0, st>>>(nb, rowptr, col, coef, wt, f, skip);
+void launch_lub_apply(int nb, double sgn, const int* rowptr, const uint32_t* col, const double* coef, const double* wt,
+                      double* f, hipStream_t st, const int* skip) {
+  k_lub_apply<<<nblocks(nb, 64), 64, 0, st>>>(nb, sgn, rowptr, col, coef, wt, f, skip);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -272,35 +274,6 @@ __global__ void k_set_value(double* p, double v) {
 }
 
 void launch_set_value(double* p, double v, hipStream_t st) { k_set_value<<<1, 64, 0, st>>>(p, v); }
-
-// Lanczos step k's coefficients on the device: alpha_k = the two Gram-Schmidt passes'
-// projections on v_k, beta_k = ||w||, scal = 1 / beta_k (0 at a breakdown)
-__global__ void k_lanczos_coef(int k, const double* __restrict__ h1, const double* __restrict__ h2,
-                               const double* __restrict__ nrm2, double* __restrict__ alpha, double* __restrict__ beta,
-                               double* __restrict__ scal) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  alpha[k] = h1[k] + h2[k];
-  const double b = sqrt(fmax(nrm2[0], 0.0));
-  beta[k] = b;
-  scal[0] = b > 0 ? 1.0 / b : 0.0;
-}
-
-void launch_lanczos_coef(int k, const double* h1, const double* h2, const double* nrm2, double* alpha, double* beta,
-                         double* scal, hipStream_t st) {
-  k_lanczos_coef<<<1, 64, 0, st>>>(k, h1, h2, nrm2, alpha, beta, scal);
-}
-
-// y = a[0] x, the factor read from device memory
-__global__ void k_scale_dev(size_t n, const double* __restrict__ a, const double* __restrict__ x,
-                            double* __restrict__ y) {
-  const size_t i = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  y[i] = a[0] * x[i];
-}
-
-void launch_scale_dev(size_t n, const double* a, const double* x, double* y, hipStream_t st) {
-  k_scale_dev<<<nblocks((long long)n), kThreads, 0, st>>>(n, a, x, y);
-}
 
 void launch_axpby(size_t n, double a, const double* x, double b, double* y, hipStream_t st) {
   k_axpby<<<nblocks((long long)n), kThreads, 0, st>>>(n, a, x, b, y);
@@ -877,6 +850,111 @@ __global__ __launch_bounds__(kCgsThreads) void k_cgs_chain(size_t n, int nq, con
                                                            const int* __restrict__ skip) {
   if (skip && *skip) return;
   cgs_chain_body<MODE>(n, nq, V, ldv, pin, w, pout, hout, blockIdx.x, gridDim.x);
+}
+
+// ------------------------------------------------------------------------------------------
+// Lanczos steps of the Brownian square roots: the passes of the chain above for any number of
+// basis vectors (the roots take up to lanczos_maxit).  Each workgroup owns a slice of the vectors
+// and walks the basis 32 vectors at a time; partial sums go to part[b nq + q] and every workgroup of
+// the next pass adds them in the same fixed order.  The earlier form (8 vectors at a time, the last
+// workgroup adding the partials after a fence and a ticket) took 141 us for the three passes of a
+// step at 50 of 100 vectors of 18,033 (6,011 beads), seven launches a step; these take 38, five launches.
+// MODE 0: partials of V^T w.  MODE 1: h = the summed partials, w -= V h, partials of V^T w; *coef =
+// the last of h.  MODE 2: the same update, partials of w.w; *coef += the last of h.  MODE 3: partials
+// of w.w alone.
+// ------------------------------------------------------------------------------------------
+namespace {
+constexpr int kLanBlocks = 256;  // partials a workgroup adds in one sweep of its threads
+}
+
+int lanczos_blocks(size_t n) { return int(std::min<size_t>((n + kCgsThreads - 1) / kCgsThreads, kLanBlocks)); }
+
+template <int MODE>
+__global__ __launch_bounds__(kCgsThreads) void k_lanczos_pass(size_t n, int nq, const double* __restrict__ V,
+                                                              const double* __restrict__ pin, double* __restrict__ w,
+                                                              double* __restrict__ pout, double* __restrict__ coef) {
+  extern __shared__ double h[];  // nq
+  __shared__ double sh[kCgsWaves][kCgsMax];
+  __shared__ double other[128];
+  const int t = threadIdx.x, G = gridDim.x;
+  const size_t i0 = size_t(blockIdx.x) * kCgsThreads + t, step = size_t(G) * kCgsThreads;
+  if (MODE == 1 || MODE == 2) {
+    const int c = t & 127, mid = (G + 1) / 2, b0 = t < 128 ? 0 : mid, b1 = t < 128 ? mid : G;
+    for (int q0 = 0; q0 < nq; q0 += 128) {
+      double v = 0.0;
+      if (q0 + c < nq) {
+#pragma unroll 8
+        for (int b = b0; b < b1; ++b) v += pin[size_t(b) * nq + q0 + c];
+      }
+      if (t >= 128) other[c] = v;
+      __syncthreads();
+      if (t < 128 && q0 + c < nq) h[q0 + c] = v + other[c];
+      __syncthreads();
+    }
+    if (blockIdx.x == 0 && t == 0) coef[0] = MODE == 1 ? h[nq - 1] : coef[0] + h[nq - 1];
+    for (size_t i = i0; i < n; i += step) {
+      double s = 0.0;
+#pragma unroll 16
+      for (int q = 0; q < nq; ++q) s += h[q] * V[size_t(q) * n + i];
+      w[i] -= s;
+    }
+  }
+  double acc[kCgsMax];
+  if (MODE <= 1) {
+    for (int q0 = 0; q0 < nq; q0 += kCgsMax) {
+      const int cnt = min(kCgsMax, nq - q0);
+#pragma unroll
+      for (int u = 0; u < kCgsMax; ++u) acc[u] = 0.0;
+      for (size_t i = i0; i < n; i += step) {
+        const double wi = w[i];
+#pragma unroll
+        for (int u = 0; u < kCgsMax; ++u)
+          if (u < cnt) acc[u] += V[size_t(q0 + u) * n + i] * wi;
+      }
+      block_sums(acc, cnt, sh);
+      if (t < cnt) pout[size_t(blockIdx.x) * nq + q0 + t] = sh[0][t];
+      __syncthreads();
+    }
+  } else {
+    acc[0] = 0.0;
+    for (size_t i = i0; i < n; i += step) acc[0] += w[i] * w[i];
+    block_sums(acc, 1, sh);
+    if (t == 0) pout[blockIdx.x] = sh[0][0];
+  }
+}
+
+// beta = ||w|| from the G <= 256 partials pin (stored to *beta), v = w / beta (0 at a breakdown);
+// v == nullptr: the norm alone
+__global__ __launch_bounds__(kCgsThreads) void k_lanczos_next(size_t n, int G, const double* __restrict__ pin,
+                                                              const double* __restrict__ w, double* __restrict__ v,
+                                                              double* __restrict__ beta) {
+  __shared__ double sh[kCgsWaves];
+  const double tot = wave_total(int(threadIdx.x) < G ? pin[threadIdx.x] : 0.0);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = tot;
+  __syncthreads();
+  const double b = sqrt(fmax(sh[0] + sh[1] + sh[2] + sh[3], 0.0)), sc = b > 0 ? 1.0 / b : 0.0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *beta = b;
+  const size_t i = size_t(blockIdx.x) * kCgsThreads + threadIdx.x;
+  if (v && i < n) v[i] = sc * w[i];
+}
+
+void launch_lanczos_pass(int mode, size_t n, int nq, const double* V, const double* pin, double* w, double* pout,
+                         double* coef, hipStream_t st) {
+  const int g = lanczos_blocks(n);
+  const uint32_t shm = uint32_t(sizeof(double)) * nq;
+  if (mode == 0)
+    launch_k(k_lanczos_pass<0>, g, kCgsThreads, shm, st, n, nq, V, pin, w, pout, coef);
+  else if (mode == 1)
+    launch_k(k_lanczos_pass<1>, g, kCgsThreads, shm, st, n, nq, V, pin, w, pout, coef);
+  else if (mode == 2)
+    launch_k(k_lanczos_pass<2>, g, kCgsThreads, shm, st, n, nq, V, pin, w, pout, coef);
+  else
+    launch_k(k_lanczos_pass<3>, g, kCgsThreads, shm, st, n, nq, V, pin, w, pout, coef);
+}
+
+void launch_lanczos_next(size_t n, const double* pin, const double* w, double* v, double* beta, hipStream_t st) {
+  const int g = v ? nblocks((long long)n, kCgsThreads) : 1;
+  launch_k(k_lanczos_next, g, kCgsThreads, 0, st, n, lanczos_blocks(n), pin, w, v, beta);
 }
 
 // w.w from the mode-2 partials, then the Arnoldi update (one workgroup)
