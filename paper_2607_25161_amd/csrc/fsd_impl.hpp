@@ -402,6 +402,10 @@ struct BatchDesc {
   const double* w64;
   const float* w32;
   int nbin;
+  // interpolation by blocks: its sums per list place, the places of a bead's slots
+  int by_blocks, slots;
+  const int* where;
+  void* places;
   // lubrication and preconditioner
   const int* lrow;
   const uint32_t* lcol;
@@ -424,6 +428,7 @@ enum BatchKind {
   BK_FFT_MID,    // y passes
   BK_FFT_GREEN,  // x transforms with the Green's-function scaling
   BK_INTERP,
+  BK_JOIN,  // adds the places of interpolation by blocks
   BK_AGG,
   BK_CGS,
   BK_COUNT,
@@ -450,6 +455,7 @@ bool two_step_green_of(const WaveParams& wp);
 void spread_plan_desc(const SpreadPlan* sp, BatchDesc& d);
 // per-system block counts of each kind and the dynamic LDS the kinds need (prec: 0 FP64, 1 FP32)
 int batch_blocks(const BatchDesc& d, int kind, int prec);
+bool interp_by_blocks(int nb, int prec);  // multi-system launches: nb of all systems
 int batch_fft_blocks(const BatchDesc& d, int kind, int prec);
 size_t batch_fft_shm(const BatchDesc& d, int kind, int prec);
 size_t batch_shm(const BatchDesc& d, int kind, int prec);

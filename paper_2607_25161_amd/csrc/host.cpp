@@ -2824,6 +2824,9 @@ void set_tables(fsd_batch* b, const std::vector<fsd_system*>& cyc, int prec) {
     while (first < ns && held + 0.5 * grid_bytes_of(desc[first], prec) <= per_group);
     g.ns = first - g.first;
     g.off = off.size();
+    int beads = 0;
+    for (int k = g.first; k < first; ++k) beads += desc[k].nb;
+    for (int k = g.first; k < first; ++k) desc[k].by_blocks = interp_by_blocks(beads, prec);
     for (int kind = 0; kind < BK_COUNT; ++kind) {
       int acc = 0;
       for (int k = g.first; k < first; ++k) {
@@ -2956,7 +2959,10 @@ void batch_segment_body(fsd_batch* b, const fsd_batch::Group& g, int j0, int cnt
       const int kind = (stage == 0 || stage == 4) ? BK_FFT_OUTER : (stage == 2 ? BK_FFT_GREEN : BK_FFT_MID);
       mob(cls_of[stage], kind, stage);
     }
-    mob(FSD_TIMER_INTERP, BK_INTERP, 0);
+    batch_launch(b, g, FSD_TIMER_INTERP, 0, [&] {
+      for (int kind : {BK_INTERP, BK_JOIN})
+        launch_batch_mobility(kind, prec, 0, D, off(kind), ns, g.total[kind], g.shm[kind], b->st);
+    });
     batch_launch(b, g, FSD_TIMER_RIGID, 0, [&] {
       launch_batch_solver(BK_AGG, j, 0, D, off(BK_AGG), ns, g.total[BK_AGG], b->st);
     });
@@ -3382,6 +3388,8 @@ fsd_status fsd_batch_time_kernel(fsd_batch* b, int timer, int reps, double* avg_
           if (timer == FSD_TIMER_GREEN) kind = BK_FFT_GREEN, stage = 2;
           if (timer == FSD_TIMER_INTERP) kind = BK_INTERP;
           launch_batch_mobility(kind, prec, stage, D, off(kind), g.ns, g.total[kind], g.shm[kind], b->st);
+          if (kind == BK_INTERP)
+            launch_batch_mobility(BK_JOIN, prec, 0, D, off(BK_JOIN), g.ns, g.total[BK_JOIN], 0, b->st);
         }
       }
     };

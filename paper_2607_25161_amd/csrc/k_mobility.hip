@@ -57,6 +57,10 @@ struct SpreadPlan {
   int *blk_start = nullptr, *blk_end = nullptr, *pk_in = nullptr, *pk_out = nullptr, *pv_in = nullptr,
       *pv_out = nullptr;
   int4* cand = nullptr;
+  int* where = nullptr;     // place in cand of every slot of sorted bead k (-1: unused), kcx kc^2 each
+  // one allocation: the sort's keys, values and temporary storage while the plan is built, later
+  // interpolation's six sums of every place in cand
+  void* scratch = nullptr;
   void* ptemp = nullptr;
   size_t ptemp_bytes = 0;
   int4* starts = nullptr;   // (sx, sy, sz, bin) per bead, sorted order
@@ -634,15 +638,20 @@ SpreadPlan* spread_plan_create(int nb, int N, int P, bool sheared) {
     const size_t slots = size_t(nb) * sp->kcx * sp->kc * sp->kc;
     ok = hipMalloc(&sp->blk_start, sizeof(int) * nbins) == hipSuccess &&
          hipMalloc(&sp->blk_end, sizeof(int) * nbins) == hipSuccess &&
-         hipMalloc(&sp->pk_in, sizeof(int) * slots) == hipSuccess &&
-         hipMalloc(&sp->pk_out, sizeof(int) * slots) == hipSuccess &&
-         hipMalloc(&sp->pv_in, sizeof(int) * slots) == hipSuccess &&
-         hipMalloc(&sp->pv_out, sizeof(int) * slots) == hipSuccess &&
-         hipMalloc(&sp->cand, sizeof(int4) * slots) == hipSuccess;
+         hipMalloc(&sp->cand, sizeof(int4) * slots) == hipSuccess &&
+         hipMalloc(&sp->where, sizeof(int) * slots) == hipSuccess;
     size_t pb = 0;
     hipcub::DeviceRadixSort::SortPairs(nullptr, pb, sp->pk_in, sp->pk_out, sp->pv_in, sp->pv_out, int(slots));
     sp->ptemp_bytes = pb;
-    ok = ok && hipMalloc(&sp->ptemp, pb) == hipSuccess;
+    const size_t four = (4 * sizeof(int) * slots + 255) / 256 * 256;
+    ok = ok && hipMalloc(&sp->scratch, std::max(four + pb, 6 * sizeof(double) * slots)) == hipSuccess;
+    if (ok) {
+      sp->pk_in = static_cast<int*>(sp->scratch);
+      sp->pk_out = sp->pk_in + slots;
+      sp->pv_in = sp->pk_out + slots;
+      sp->pv_out = sp->pv_in + slots;
+      sp->ptemp = static_cast<char*>(sp->scratch) + four;
+    }
   }
   if (!ok) {
     spread_plan_destroy(sp);
@@ -668,12 +677,9 @@ void spread_plan_destroy(SpreadPlan* sp) {
   (void)hipFree(sp->temp);
   (void)hipFree(sp->blk_start);
   (void)hipFree(sp->blk_end);
-  (void)hipFree(sp->pk_in);
-  (void)hipFree(sp->pk_out);
-  (void)hipFree(sp->pv_in);
-  (void)hipFree(sp->pv_out);
   (void)hipFree(sp->cand);
-  (void)hipFree(sp->ptemp);
+  (void)hipFree(sp->where);
+  (void)hipFree(sp->scratch);
   delete sp;
 }
 
@@ -750,13 +756,13 @@ __global__ void k_bin_bounds(int nb, const int* __restrict__ keys, int* start, i
   if (k == nb - 1 || keys[k + 1] != c) end[c] = k + 1;
 }
 
-// the slots of sorted bead k: the blocks its support reaches (their index as the key, k as the
-// value), the remaining slots a sentinel key past the last block.  SHEAR: along x, the blocks from
+// the slots of sorted bead k: the blocks its support reaches (their index as the key, the slot's
+// number as the value), the remaining slots a sentinel key past the last block.  SHEAR: along x, the blocks from
 // the first to the last point of the rows that lie in the block row
 template <bool SHEAR>
 __global__ void k_block_slots(int nb, const int4* __restrict__ starts, const double4* __restrict__ pos,
                               const int* __restrict__ perm, WaveParams wp, int nbin, int kc, int kcx,
-                              int* __restrict__ keys, int* __restrict__ vals) {
+                              int* __restrict__ keys, int* __restrict__ vals, int* __restrict__ where) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= nb) return;
   const int P = wp.support;
@@ -787,27 +793,30 @@ __global__ void k_block_slots(int nb, const int4* __restrict__ starts, const dou
       for (int jx = 0; jx < nx; ++jx) {
         const int bz = (b0[2] + jz) % nbin, bx = wrapi(x0 + jx, nbin);
         keys[size_t(k) * per + q] = (bz * nbin + by) * nbin + bx;
-        vals[size_t(k) * per + q] = k;
+        vals[size_t(k) * per + q] = k * per + q;
         ++q;
       }
   }
   for (; q < per; ++q) {
     keys[size_t(k) * per + q] = sentinel;
-    vals[size_t(k) * per + q] = k;
+    vals[size_t(k) * per + q] = k * per + q;
+    where[size_t(k) * per + q] = -1;
   }
 }
 
 // list bounds per block and the candidate records from the sorted slots (sentinels ignored)
-__global__ void k_block_lists(int n, int nbin, int N, const int* __restrict__ keys, const int* __restrict__ vals,
-                              const int4* __restrict__ starts, const int* __restrict__ perm, int* __restrict__ start,
-                              int* __restrict__ end, int4* __restrict__ cand) {
+__global__ void k_block_lists(int n, int nbin, int N, int per, const int* __restrict__ keys,
+                              const int* __restrict__ vals, const int4* __restrict__ starts,
+                              const int* __restrict__ perm, int* __restrict__ start, int* __restrict__ end,
+                              int4* __restrict__ cand, int* __restrict__ where) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= n) return;
   const int c = keys[p];
   if (c >= nbin * nbin * nbin) return;
   if (p == 0 || keys[p - 1] != c) start[c] = p;
   if (p == n - 1 || keys[p + 1] != c) end[c] = p + 1;
-  const int k = vals[p];
+  const int k = vals[p] / per;
+  where[vals[p]] = p;
   const int4 s = starts[k];
   const int ox = point_offset(8 * (c % nbin), s.x, N), oy = point_offset(8 * (c / nbin % nbin), s.y, N),
             oz = point_offset(8 * (c / (nbin * nbin)), s.z, N);
@@ -840,10 +849,10 @@ hipError_t spread_plan_update(SpreadPlan* sp, const double* pos4, const WavePara
     const int kc = sp->kc, kcx = sp->kcx, slots = nb * kcx * kc * kc;
     if (sp->sheared)
       k_block_slots<true><<<nblocks(nb), kThreads, 0, st>>>(nb, sp->starts, pos, sp->perm, wp, sp->nbin, kc, kcx,
-                                                            sp->pk_in, sp->pv_in);
+                                                            sp->pk_in, sp->pv_in, sp->where);
     else
       k_block_slots<false><<<nblocks(nb), kThreads, 0, st>>>(nb, sp->starts, pos, sp->perm, wp, sp->nbin, kc, kcx,
-                                                             sp->pk_in, sp->pv_in);
+                                                             sp->pk_in, sp->pv_in, sp->where);
     int pbits = 1;
     while ((1 << pbits) <= nbins) ++pbits;  // the sentinel nbins included
     size_t pb = sp->ptemp_bytes;
@@ -852,8 +861,9 @@ hipError_t spread_plan_update(SpreadPlan* sp, const double* pos4, const WavePara
       return e;
     if ((e = hipMemsetAsync(sp->blk_start, 0, sizeof(int) * nbins, st)) != hipSuccess) return e;
     if ((e = hipMemsetAsync(sp->blk_end, 0, sizeof(int) * nbins, st)) != hipSuccess) return e;
-    k_block_lists<<<nblocks(slots), kThreads, 0, st>>>(slots, sp->nbin, wp.n, sp->pk_out, sp->pv_out, sp->starts,
-                                                       sp->perm, sp->blk_start, sp->blk_end, sp->cand);
+    k_block_lists<<<nblocks(slots), kThreads, 0, st>>>(slots, sp->nbin, wp.n, kcx * kc * kc, sp->pk_out, sp->pv_out,
+                                                       sp->starts, sp->perm, sp->blk_start, sp->blk_end, sp->cand,
+                                                       sp->where);
   }
   return hipGetLastError();
 }
@@ -988,7 +998,7 @@ __global__ __launch_bounds__(BS* BS* BS) void k_spread_gather(const int* __restr
 // sum is in list order.  The products of 81,920 beads take 45 us in FP64 and 22 in FP32 at the
 // matrix rate; what is left is the latency from the candidate's record to its weights and the
 // store of the grid, which other blocks' wavefronts cover.  Measured in the first pass of the
-// saddle operator (128^3, beside 140 and 115 us of pair sum): 246 us in FP64 and 173 in FP32; with
+// saddle operator (128^3, beside 140 and 115 us of pair sum): 234 us in FP64 and 163 in FP32; with
 // one lane per (x, y) column on the vector units it took 415 and 278.  The scatter with atomics of
 // the sheared lattice took 250 (FP64, 2,048 beads) to 410 us (FP32, 6,011), now 17 and 22.
 template <typename R, bool SHEAR>
@@ -1013,6 +1023,18 @@ __device__ __forceinline__ Acc32 mma4(float a, float b, Acc32 c) {
 // Up to here four wavefronts share a bead in interpolation: 32 beads at P = 14 take 5.3 us instead of
 // 11.8, 2,048 at P = 11 11.4 instead of 9.7 (FP64)
 constexpr int kShareBeads = 512;
+// Interpolation by blocks (k_interp_tile) or by beads (k_interp_plan), in us, random beads, P = 14:
+//   beads / grid       3000 / 64   4096 / 64   4096 / 128   8192 / 64   16384 / 64   16384 / 96
+//   FP64, cube        22.8, 29.2  27.4, 36.7   36.2, 81.5  42.0, 63.3   71.4, 119    64.9, 125
+//   FP32, cube        18.5, 17.5  21.4, 22.2   27.5, 37.1  30.7, 39.5   50.3, 73.4   41.8, 78.8
+//   FP64, sheared     32.3, 29.2  39.1, 37.9   42.2, 84.2  60.6, 63.9    103, 120    93.0, 125
+//   FP32, sheared     26.2, 17.2  31.2, 21.7   32.8, 37.4  49.5, 38.6   82.7, 74.9   60.5, 78.2
+// A sheared block stages the 64 weights of a plane per candidate, which in FP32 pays only where a
+// block has few of them.  A batch counts the beads of a launch.
+bool interp_by_blocks(int nb, int N, bool sheared, int bytes) {
+  if (!sheared) return nb >= 4096;
+  return nb >= 8192 && (bytes == 8 || double(N) * N * N >= 50.0 * nb);
+}
 template <typename R>
 struct AccOf {
   using T = Acc64;
@@ -1032,6 +1054,76 @@ struct BlockArgs {
   int nbin;
 };
 
+// The weight windows of n staged candidates (records rec, on a sheared lattice the rows' offsets
+// row_x) into win: the plane of A (or w_x and w_y), then w_z.  Eight lanes serve a candidate, so the
+// addresses are shifts and a wrap (dividing a running index by the window's length took more
+// instructions than the products).
+template <typename R, bool SHEAR, int S>
+__device__ __forceinline__ void stage_windows(R* win, const int4* rec, const int* row_x, const R* __restrict__ weights,
+                                              int n, int P, int N, int wlen) {
+  constexpr int A = SHEAR ? 9 : 3, C = SpreadTile<R, SHEAR>::kCand;
+  const int i = threadIdx.x & 7;
+#pragma unroll
+  for (int c0 = 0; c0 < C; c0 += 32) {
+    const int c = c0 + int(threadIdx.x >> 3);
+    if (c >= n) break;
+    const int4 rc = rec[c];
+    R wv[A];
+#pragma unroll
+    for (int a = 0; a < A; ++a) {
+      int o, at;
+      if (a == A - 1) {
+        o = ((rc.z >> 16) & 255) + i;
+        at = wlen - P;
+      } else if (SHEAR) {
+        int oy = ((rc.z >> 8) & 255) + a;
+        oy -= oy >= N ? N : 0;
+        o = row_x[8 * c + a];
+        o = o < N ? o + i : P;
+        at = oy * P;
+      } else {
+        o = ((rc.z >> (8 * a)) & 255) + i;
+        at = a * P;
+      }
+      o -= o >= N ? N : 0;
+      wv[a] = 0;
+      if (o < P) wv[a] = SHEAR ? weights[size_t(rc.x) * wlen + at + o] : ldg1(weights, rc.x * wlen + at + o);
+    }
+#pragma unroll
+    for (int a = 0; a < A; ++a) win[c * S + 8 * a + i] = wv[a];
+  }
+}
+
+// whether staged candidate c reaches rows y0 + qy and the next of the block (which it reaches):
+// the offset of the first row below P, or of the second one after the wrap
+template <bool SHEAR>
+__device__ __forceinline__ bool reaches_rows(const int4* rec, const int* row_x, int c, int qy, int P, int N) {
+  if (SHEAR) {
+    bool hit = false;
+#pragma unroll
+    for (int y = 0; y < 2; ++y) {
+      const int ox = row_x[8 * c + qy + y];
+      hit = hit || ox < P || (ox > N - 8 && ox < N);
+    }
+    return hit;
+  }
+  int oy = ((rec[c].z >> 8) & 255) + qy;
+  oy -= oy >= N ? N : 0;
+  return oy < P || oy == N - 1;
+}
+
+// offset of x0 from the start of each candidate's rows y0 .. y0 + 7, or N: outside the support
+template <typename R>
+__device__ __forceinline__ void stage_rows(int* row_x, const int4* rec, const short* __restrict__ rows, int n, int x0,
+                                           int P, int N) {
+  for (int q = threadIdx.x; q < 8 * n; q += 256) {
+    const int4 rc = rec[q >> 3];
+    int oy = ((rc.z >> 8) & 255) + (q & 7);
+    oy -= oy >= N ? N : 0;
+    row_x[q] = oy < P ? point_offset(x0, rows[size_t(rc.x) * P + oy], N) : N;
+  }
+}
+
 // the value of the lane 8 further in the row of 16
 __device__ __forceinline__ float ror8(float v) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x128, 0xf, 0xf, true));
@@ -1048,7 +1140,7 @@ __device__ __forceinline__ void spread_tile_body(const BlockArgs<R>& ba, const d
   if (skip && *skip) return;
   using Tile = SpreadTile<R, SHEAR>;
   using Acc = typename AccOf<R>::T;
-  constexpr int C = Tile::kCand, S = Tile::kStride, NT = 256;
+  constexpr int C = Tile::kCand, S = Tile::kStride;
   const int P = wp.support, N = wp.n, nbin = ba.nbin;
   const int wlen = SHEAR ? P * P + P : 3 * P;
   R* win = reinterpret_cast<R*>(smem);
@@ -1071,82 +1163,30 @@ __device__ __forceinline__ void spread_tile_body(const BlockArgs<R>& ba, const d
   Acc acc[3] = {};
   if (t < S) win[C * S + t] = 0;  // the candidate of zero weights
   constexpr int NW = Tile::kPlane + 8;               // window points of a candidate
-  constexpr int UL = (C * 6 + NT - 1) / NT;          // moments per thread
+  constexpr int UL = C / 32;                         // candidates per eight lanes
   for (int c0 = 0; c0 < total; c0 += C) {
     const int n = min(C, total - c0);
     if (c0 > 0) __syncthreads();
     if (t < n) rec[t] = ba.cand[cb + c0 + t];
     __syncthreads();
-    if (SHEAR) {  // offset of x0 from the start of the candidate's row y0 + y, or N: outside the support
-      for (int q = t; q < 8 * n; q += NT) {
-        const int4 rc = rec[q >> 3];
-        int oy = ((rc.z >> 8) & 255) + (q & 7);
-        oy -= oy >= N ? N : 0;
-        row_x[q] = oy < P ? point_offset(x0, ba.rows[size_t(rc.x) * P + oy], N) : N;
-      }
+    if (SHEAR) {
+      stage_rows<R>(row_x, rec, ba.rows, n, x0, P, N);
       __syncthreads();
     }
-    // the moments' loads are issued before the first of the weights' is waited for; three of those
-    // are in flight at a time (more take registers, and a wavefront a SIMD with them)
+    // the moments' loads are issued before the first of the weights' is waited for
     double lv[UL];
 #pragma unroll
     for (int u = 0; u < UL; ++u) {
-      const unsigned q = t + u * NT, c = q / 6;
-      if (c < unsigned(n)) lv[u] = lam[6 * size_t(rec[c].y) + (q - 6 * c)];
+      const int c = (t >> 3) + 32 * u;
+      if (c < n && (t & 7) < 6) lv[u] = lam[6 * size_t(rec[c].y) + (t & 7)];
     }
-    for (unsigned q0 = t; q0 < unsigned(n * NW); q0 += 3 * NT) {
-      R wv[3];
-#pragma unroll
-      for (int u = 0; u < 3; ++u) {
-        const unsigned q = q0 + u * NT, c = q / NW, i = q - c * NW;
-        wv[u] = 0;
-        if (c >= unsigned(n)) continue;
-        const int4 rc = rec[c];
-        int o, at;
-        if (i >= Tile::kPlane) {
-          o = ((rc.z >> 16) & 255) + i - Tile::kPlane;
-          at = wlen - P;
-        } else if (SHEAR) {
-          int oy = ((rc.z >> 8) & 255) + (i >> 3);
-          oy -= oy >= N ? N : 0;
-          o = row_x[8 * c + (i >> 3)];
-          o = o < N ? o + (i & 7) : P;
-          at = oy * P;
-        } else {
-          o = ((rc.z >> (i & 8)) & 255) + (i & 7);
-          at = i < 8 ? 0 : P;
-        }
-        o -= o >= N ? N : 0;
-        if (o < P) wv[u] = SHEAR ? ba.weights[size_t(rc.x) * wlen + at + o] : ldg1(ba.weights, rc.x * wlen + at + o);
-      }
-#pragma unroll
-      for (int u = 0; u < 3; ++u) {
-        const unsigned q = q0 + u * NT, c = q / NW, i = q - c * NW;
-        if (c < unsigned(n)) win[c * S + i] = wv[u];
-      }
-    }
+    stage_windows<R, SHEAR, S>(win, rec, row_x, ba.weights, n, P, N, wlen);
 #pragma unroll
     for (int u = 0; u < UL; ++u) {
-      const unsigned q = t + u * NT, c = q / 6;
-      if (c < unsigned(n)) win[c * S + NW + q - 6 * c] = R(lv[u]);
+      const int c = (t >> 3) + 32 * u;
+      if (c < n && (t & 7) < 6) win[c * S + NW + (t & 7)] = R(lv[u]);
     }
-    // the candidates that reach the wavefront's rows (the block they all reach): the offset of the
-    // first row below P, or of the second one after the wrap
-    bool hit = false;
-    if (lane < n) {
-      if (SHEAR) {
-#pragma unroll
-        for (int y = 0; y < 2; ++y) {
-          const int ox = row_x[8 * lane + qy + y];
-          hit = hit || ox < P || (ox > N - 8 && ox < N);
-        }
-      } else {
-        const int z = rec[lane].z;
-        int oy = ((z >> 8) & 255) + qy;
-        oy -= oy >= N ? N : 0;
-        hit = oy < P || oy == N - 1;
-      }
-    }
+    const bool hit = lane < n && reaches_rows<SHEAR>(rec, row_x, lane, qy, P, N);
     const unsigned long long hits = __ballot(hit);
     const int cnt = __popcll(hits);
     if (hit) list[__popcll(hits & ((1ull << lane) - 1ull))] = lane * S;
@@ -1464,6 +1504,178 @@ __global__ __launch_bounds__(256) void k_interp_plan(int nb, BeadArgs<R> ba, con
   interp_plan_body<R, SHEAR, WPB>(nb, ba, grid, cs, wp, out, skip, body, r4, V, blockIdx.x, gridDim.x);
 }
 
+// Interpolation of large systems, the spreading product turned round: a wavefront holds its two rows
+// of the block (16 points of a plane, 8 planes, 6 components) in registers as the A operand, each
+// grid value read once, and takes the candidates that reach them 16 at a time,
+//   T(z, c; b) = sum over (x, y) of G(z, c; x, y) A_b(x, y),
+// 12 matrix products, then weights the planes by w_z and adds them, two in a lane (FP32: four), the
+// others by swaps of lanes.  The four wavefronts' sums meet in LDS and go to the candidate's place in
+// part; k_interp_join adds a bead's places.  The gather (interp_plan_body) moves every bead's support
+// through the first-level cache, 84 KB of cache lines a bead in FP64 (57 in FP32): 229 and 149 us at
+// 81,920 beads on 128^3.  Here the two kernels take 131 and 77, of which the joining 16 and 15; the
+// products alone would take 60 and 30, the rest is staging (latency and address arithmetic) and
+// groups of sixteen that are not full.  Candidates as rows and planes as columns, whose sums cross
+// eight lanes each, took 178 and 109; windows 40 values apart (four candidates' groups of points on
+// the same banks) 15 us more in FP64.
+template <typename R, bool SHEAR>
+struct InterpTile {
+  using S = SpreadTile<R, SHEAR>;
+  static constexpr int kStride = SHEAR ? 76 : 28;  // sixteen candidates' groups of four points on all banks
+  static constexpr size_t kBytes = sizeof(R) * (S::kCand + 1) * kStride + sizeof(int4) * S::kCand +
+                                   sizeof(int) * 4 * (S::kCand + 16) + (SHEAR ? sizeof(int) * 8 * S::kCand : 0) +
+                                   sizeof(R) * 4 * 6 * (S::kCand + 1) + 4 * sizeof(unsigned long long);
+};
+
+template <typename R, bool SHEAR>
+__device__ __forceinline__ void interp_tile_body(const BlockArgs<R>& ba, const WaveParams& wp,
+                                                 const R* __restrict__ grid, size_t cs, R* __restrict__ part,
+                                                 const int* __restrict__ skip, unsigned char* smem, int bx_) {
+  if (skip && *skip) return;
+  using Tile = SpreadTile<R, SHEAR>;
+  using Acc = typename AccOf<R>::T;
+  constexpr int C = Tile::kCand, S = InterpTile<R, SHEAR>::kStride, WZ = Tile::kPlane;
+  const int P = wp.support, N = wp.n, nbin = ba.nbin, wlen = SHEAR ? P * P + P : 3 * P;
+  R* win = reinterpret_cast<R*>(smem);
+  int4* rec = reinterpret_cast<int4*>(win + (C + 1) * S);
+  unsigned long long* masks = reinterpret_cast<unsigned long long*>(rec + C);
+  R* sums = reinterpret_cast<R*>(masks + 4);  // [wavefront][candidate][6]
+  int* lists = reinterpret_cast<int*>(sums + 4 * 6 * (C + 1));
+  int* row_x = lists + 4 * (C + 16);
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  int* list = lists + wave * (C + 16);
+  R* mine = sums + wave * 6 * (C + 1);
+  const int bl = xcd_remap(bx_, nbin * nbin * nbin);
+  const int cb = ba.blk_start[bl], total = ba.blk_end[bl] - cb;
+  if (total <= 0) return;
+  const int x0 = (bl % nbin) * 8, y0 = (bl / nbin % nbin) * 8, z0 = bl / (nbin * nbin) * 8, qy = 2 * wave;
+  // A operand, step s: point (x = kq + 4 (s % 2), y = s / 2), row (half, plane); lanes of force and
+  // torque trade what they load as in spreading
+  const int m = lane & 15, kq = lane >> 4, plane = m & 7, half = m >> 3;
+  R g[3][4];
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+#pragma unroll
+    for (int y = 0; y < 2; ++y) {
+      const unsigned p = (unsigned(z0 + plane) * N + y0 + qy + y) * N + x0 + kq + 4 * half;
+      R f, q;
+      ldg2(grid + c * cs, 2 * p, f, q);
+      const R got = ror8(half ? f : q);
+      g[c][2 * y] = half ? got : f;
+      g[c][2 * y + 1] = half ? q : got;
+    }
+  if (t < S) win[C * S + t] = 0;  // the candidate of zero weights
+  int4 next;
+  if (t < min(C, total)) next = ba.cand[cb + t];
+  for (int c0 = 0; c0 < total; c0 += C) {
+    const int n = min(C, total - c0);
+    if (t < n) rec[t] = next;
+    if (t < min(C, total - c0 - C)) next = ba.cand[cb + c0 + C + t];
+    __syncthreads();
+    if (SHEAR) {
+      stage_rows<R>(row_x, rec, ba.rows, n, x0, P, N);
+      __syncthreads();
+    }
+    stage_windows<R, SHEAR, S>(win, rec, row_x, ba.weights, n, P, N, wlen);
+    const bool hit = lane < n && reaches_rows<SHEAR>(rec, row_x, lane, qy, P, N);
+    const unsigned long long hits = __ballot(hit);
+    const int cnt = __popcll(hits);
+    if (hit) list[__popcll(hits & ((1ull << lane) - 1ull))] = lane;
+    if (lane < 16) list[cnt + lane] = C;
+    if (lane == 0) masks[wave] = hits;
+    __syncthreads();
+    for (int e = 0; e < cnt; e += 16) {
+      const int ci = list[e + m];
+      const R* w = win + ci * S;
+      Acc acc[3] = {};
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int x = kq + 4 * (s & 1), y = qy + (s >> 1);
+        const R a = SHEAR ? w[8 * y + x] : w[x] * w[8 + y];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) acc[c] = mma4(g[c][s], a, acc[c]);
+      }
+      // rows of the products: FP64 has row 4 r + kq in register r, FP32 row 4 kq + r
+      R u[3];
+      if (sizeof(R) == 8) {
+        const R za = w[WZ + kq], zb = w[WZ + 4 + kq];
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+          u[c] = merge32(acc[c][0] * za + acc[c][1] * zb, acc[c][2] * za + acc[c][3] * zb);
+      } else {
+        const R* z = w + WZ + 4 * (kq & 1);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) u[c] = acc[c][0] * z[0] + acc[c][1] * z[1] + acc[c][2] * z[2] + acc[c][3] * z[3];
+      }
+      R* out = mine + 6 * ci + 3 * (kq >> 1);
+      out[kq & 1] = merge16(u[0], u[1]);
+      const R last = merge16(u[2], u[2]);
+      if (!(kq & 1)) out[2] = last;
+    }
+    __syncthreads();
+    for (int q = t; q < 6 * n; q += 256) {
+      const int c = q / 6;
+      R u = 0;
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (masks[v] >> c & 1) u += sums[v * 6 * (C + 1) + q];
+      part[size_t(6) * (cb + c0) + q] = u;
+    }
+  }
+}
+
+template <typename R, bool SHEAR>
+__global__ __launch_bounds__(256, 4) void k_interp_tile(BlockArgs<R> ba, WaveParams wp, const R* __restrict__ grid,
+                                                        size_t cs, R* __restrict__ part,
+                                                        const int* __restrict__ skip) {
+  extern __shared__ unsigned char smem_raw[];
+  interp_tile_body<R, SHEAR>(ba, wp, grid, cs, part, skip, smem_raw, blockIdx.x);
+}
+
+// out_i += the sums of bead i's places (+ Sigma^T V), one thread per bead and component
+template <typename R>
+__device__ __forceinline__ void interp_join_body(int nb, int per, const int* __restrict__ perm,
+                                                 const int* __restrict__ where, const R* __restrict__ part,
+                                                 double* __restrict__ out, const int* __restrict__ skip,
+                                                 const int* __restrict__ body, const double4* __restrict__ r4,
+                                                 const double* __restrict__ V, int t) {
+  if (skip && *skip) return;
+  const int k = t / 6, c = t - 6 * k;
+  if (k >= nb) return;
+  const int* w = where + size_t(k) * per;
+  R u = 0;
+  for (int q0 = 0; q0 < per; q0 += 4) {
+    int p[4];
+    R v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) p[j] = q0 + j < per ? w[q0 + j] : -1;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = p[j] >= 0 ? part[size_t(6) * p[j] + c] : R(0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) u += v[j];
+    if (p[3] < 0) break;  // the used slots come first
+  }
+  const int i = perm[k];
+  double add = double(u);
+  if (V) {
+    const double* v = V + 6 * size_t(body[i]);
+    const double4 r = r4[i];
+    add += v[c];
+    if (c == 0) add += v[4] * r.z - v[5] * r.y;
+    if (c == 1) add += v[5] * r.x - v[3] * r.z;
+    if (c == 2) add += v[3] * r.y - v[4] * r.x;
+  }
+  out[6 * size_t(i) + c] += add;
+}
+
+template <typename R>
+__global__ __launch_bounds__(256) void k_interp_join(int nb, int per, const int* __restrict__ perm,
+                                                     const int* __restrict__ where, const R* __restrict__ part,
+                                                     double* __restrict__ out, const int* __restrict__ skip,
+                                                     const int* __restrict__ body, const double4* __restrict__ r4,
+                                                     const double* __restrict__ V) {
+  interp_join_body<R>(nb, per, perm, where, part, out, skip, body, r4, V, blockIdx.x * 256 + threadIdx.x);
+}
+
 template <typename R>
 void launch_interp(int nb, const double* pos4, const R* grid, const WaveParams& wp, double* out, hipStream_t st,
                    const int* skip, const int* body, const double* r4, const double* V, const SpreadPlan* sp) {
@@ -1471,6 +1683,19 @@ void launch_interp(int nb, const double* pos4, const R* grid, const WaveParams& 
   const double4* r = (const double4*)r4;
   if (!sp) {
     launch_k(k_interp<R>, nblocks(nb, 4), kThreads, 0, st, nb, (const double4*)pos4, grid, cs, wp, out, skip, body, r, V);
+    return;
+  }
+  if (sp->BS == 8 && interp_by_blocks(nb, wp.n, sp->sheared, sizeof(R))) {
+    const int nblk = sp->nbin * sp->nbin * sp->nbin;
+    R* part = static_cast<R*>(sp->scratch);
+    if (sp->sheared)
+      launch_k(k_interp_tile<R, true>, nblk, 256, InterpTile<R, true>::kBytes, st, block_args<R>(sp), wp, grid, cs, part,
+               skip);
+    else
+      launch_k(k_interp_tile<R, false>, nblk, 256, InterpTile<R, false>::kBytes, st, block_args<R>(sp), wp, grid, cs,
+               part, skip);
+    launch_k(k_interp_join<R>, nblocks(6LL * nb), 256, 0, st, nb, sp->kcx * sp->kc * sp->kc, sp->perm, sp->where, part,
+             out, skip, body, r, V);
     return;
   }
   const BeadArgs<R> ba{sp->perm, sp->starts, sp->rows, plan_weights<R>(sp)};
@@ -1529,6 +1754,27 @@ __global__ __launch_bounds__(256) void kb_interp(const BatchDesc* __restrict__ D
                                 (const double4*)d.r4, d.z + 6 * size_t(d.nb), blockIdx.x - off[s], off[s + 1] - off[s]);
 }
 
+template <typename R>
+__global__ __launch_bounds__(256, 4) void kb_interp_tile(const BatchDesc* __restrict__ D, const int* __restrict__ off,
+                                                         int nsys) {
+  const int s = batch_system(off, nsys, blockIdx.x);
+  const BatchDesc& d = D[s];
+  const size_t cs = 2 * size_t(d.wp.n) * d.wp.n * d.wp.n;
+  extern __shared__ unsigned char smem_raw[];
+  const BlockArgs<R> ba{d.blk_start, d.blk_end, d.cand, nullptr, pick<R>(d.w64, d.w32), d.nbin};
+  interp_tile_body<R, false>(ba, d.wp, static_cast<const R*>(d.grid), cs, static_cast<R*>(d.places), &d.ctl->stop,
+                             smem_raw, blockIdx.x - off[s]);
+}
+
+template <typename R>
+__global__ __launch_bounds__(256) void kb_interp_join(const BatchDesc* __restrict__ D, const int* __restrict__ off,
+                                                      int nsys) {
+  const int s = batch_system(off, nsys, blockIdx.x);
+  const BatchDesc& d = D[s];
+  interp_join_body<R>(d.nb, d.slots, d.perm, d.where, static_cast<const R*>(d.places), d.w, &d.ctl->stop, d.body,
+                      (const double4*)d.r4, d.z + 6 * size_t(d.nb), (blockIdx.x - off[s]) * 256 + threadIdx.x);
+}
+
 // spreading fields of a batch descriptor (blk_start == nullptr: no plan of 8^3 blocks)
 void spread_plan_desc(const SpreadPlan* sp, BatchDesc& d) {
   const bool ok = sp && sp->BS == 8;
@@ -1540,7 +1786,12 @@ void spread_plan_desc(const SpreadPlan* sp, BatchDesc& d) {
   d.w64 = ok ? sp->weights : nullptr;
   d.w32 = ok ? sp->weights32 : nullptr;
   d.nbin = ok ? sp->nbin : 0;
+  d.slots = ok ? sp->kcx * sp->kc * sp->kc : 0;
+  d.where = ok ? sp->where : nullptr;
+  d.places = ok ? sp->scratch : nullptr;
 }
+
+bool interp_by_blocks(int nb, int prec) { return interp_by_blocks(nb, 0, false, prec ? 4 : 8); }
 
 int batch_blocks(const BatchDesc& d, int kind, int prec) {
   switch (kind) {
@@ -1556,7 +1807,9 @@ int batch_blocks(const BatchDesc& d, int kind, int prec) {
     case BK_FFT_GREEN:
       return batch_fft_blocks(d, kind, prec);
     case BK_INTERP:
-      return (d.nb + 3) / 4;
+      return d.by_blocks ? d.nbin * d.nbin * d.nbin : (d.nb + 3) / 4;
+    case BK_JOIN:
+      return d.by_blocks ? (6 * d.nb + 255) / 256 : 0;
     case BK_CGS:
       return d.ncgs;
     default:
@@ -1570,6 +1823,8 @@ size_t batch_shm(const BatchDesc& d, int kind, int prec) {
       return prec ? RealPoly<float>::kBytes : RealPoly<double>::kBytes;
     case BK_SPREAD:
       return prec ? SpreadTile<float, false>::kBytes : SpreadTile<double, false>::kBytes;
+    case BK_INTERP:
+      return !d.by_blocks ? 0 : prec ? InterpTile<float, false>::kBytes : InterpTile<double, false>::kBytes;
     case BK_FFT_OUTER:
     case BK_FFT_MID:
     case BK_FFT_GREEN:
@@ -1591,7 +1846,13 @@ void batch_mobility(int kind, const BatchDesc* D, const int* off, int nsys, int 
       kb_spread<R><<<total, 256, shm, st>>>(D, off, nsys);
       break;
     case BK_INTERP:
-      kb_interp<R><<<total, kThreads, 0, st>>>(D, off, nsys);
+      if (shm)
+        kb_interp_tile<R><<<total, 256, shm, st>>>(D, off, nsys);
+      else
+        kb_interp<R><<<total, kThreads, 0, st>>>(D, off, nsys);
+      break;
+    case BK_JOIN:
+      kb_interp_join<R><<<total, 256, 0, st>>>(D, off, nsys);
       break;
     default:
       break;
