@@ -363,6 +363,7 @@ void launch_combine(size_t n, int k, const double* V, size_t ldv, const double* 
                     hipStream_t st);                                                       // out = V c
 void launch_take_trans(int nb, const double* v6, double* t3, hipStream_t st);
 void launch_sub(size_t n, const double* b, const double* ax, double* r, hipStream_t st);
+void launch_copy(size_t n, const double* from, double* to, hipStream_t st);
 void launch_zero(void* p, size_t bytes, hipStream_t st);  // bytes a multiple of 4
 void launch_timing_mark(hipStream_t st);  // empty kernel bracketing timed launches
 

@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <functional>
 #include <map>
+#include <mutex>
 #include <tuple>
 #include <cmath>
 #include <cstdio>
@@ -300,7 +301,9 @@ struct fsd_system {
   NeighborWork* nw = nullptr;   // real-space list workspace
   NeighborWork* nwl = nullptr;  // lubrication list workspace
   int* h_flags = nullptr;       // pinned: overlap, singular block (checked at the next sync)
-  double* h_scal = nullptr;     // pinned: small reductions read by the host (outer residual)
+  double* h_io = nullptr;       // pinned: vectors on their way to and from the caller (HostIo)
+  size_t io_cap = 0;            // its doubles
+  std::mutex io_lock;
 
   // resumable solve (state machine advanced after each stream synchronisation)
   struct SolveState {
@@ -405,8 +408,8 @@ struct fsd_system {
     nwl = nullptr;
     if (h_flags) (void)hipHostFree(h_flags);
     h_flags = nullptr;
-    if (h_scal) (void)hipHostFree(h_scal);
-    h_scal = nullptr;
+    if (h_io) (void)hipHostFree(h_io);
+    h_io = nullptr;
     if (spread) spread_plan_destroy(spread);
     spread = nullptr;
     for (void* q : owned) (void)hipFree(q);
@@ -444,6 +447,57 @@ fsd_status guarded(fsd_system* s, F&& f) {
     return fail(s, FSD_EDEVICE, e.what());
   }
 }
+
+// Vectors that an entry point exchanges with the caller.  They pass through pinned memory that the
+// copying kernel reads or writes itself: a copy from or to pageable memory takes a staging buffer of
+// the runtime and, beyond a few KB, a DMA engine, each with its own hand-over (an apply of 64 beads
+// 79 -> 72 us, of 2,048 101 -> 75, of 40,000 819 -> 783).  The lock is for read-outs from several
+// threads.  What does not fit (8 MB) goes the pageable way.
+constexpr size_t kIoDoubles = 1 << 20;
+
+struct HostIo {
+  explicit HostIo(fsd_system* sys) : s(sys), hold(sys->io_lock) {}
+  ~HostIo() {
+    if (busy) (void)hipStreamSynchronize(s->st);  // left by an exception: nothing may read h_io later
+  }
+  void in(double* dev, const double* host, size_t n) {
+    if (used + n > s->io_cap) {
+      HIPCHK(hipMemcpyAsync(dev, host, sizeof(double) * n, hipMemcpyHostToDevice, s->st));
+      return;
+    }
+    std::memcpy(s->h_io + used, host, sizeof(double) * n);
+    busy = true;
+    launch_copy(n, s->h_io + used, dev, s->st);
+    used += n;
+  }
+  void out(double* host, const double* dev, size_t n) {
+    if (used + n > s->io_cap) {
+      HIPCHK(hipMemcpyAsync(host, dev, sizeof(double) * n, hipMemcpyDeviceToHost, s->st));
+      return;
+    }
+    busy = true;
+    launch_copy(n, dev, s->h_io + used, s->st);
+    outs[n_out++] = {host, s->h_io + used, n};
+    used += n;
+  }
+  // waits for the stream; the caller's buffers are complete afterwards
+  void finish() {
+    HIPCHK(hipStreamSynchronize(s->st));
+    busy = false;
+    for (int k = 0; k < n_out; ++k) std::memcpy(outs[k].to, outs[k].from, sizeof(double) * outs[k].n);
+  }
+  struct Out {
+    double* to;
+    const double* from;
+    size_t n;
+  };
+  fsd_system* s;
+  std::lock_guard<std::mutex> hold;
+  size_t used = 0;
+  bool busy = false;
+  Out outs[4];
+  int n_out = 0;
+};
 
 // ---- event timing -------------------------------------------------------------------------
 void harvest_timers(fsd_system* s) {
@@ -861,13 +915,31 @@ double grid_bytes(const fsd_system* s) {
   return 3.0 * 2.0 * N * N * N * sizeof(R);
 }
 
+// the fused first pass (Sigma/lubrication reduction, real-space sum, spreading) of y = A x; without
+// `rigid`, of its first rows
+template <typename R>
+void mob_first(fsd_system* s, const double* x, double* y, const int* skip, bool rigid = true) {
+  const size_t nb6 = 6 * size_t(s->nb);
+  const bool lub = rigid && s->p.r_lub > 0 && s->nlub > 0;
+  const RealArgs ra{s->nb, reinterpret_cast<const double4*>(s->d_pos4), s->d_nrow, s->d_ncol, s->rp, y,
+                    spread_plan_order(s->spread)};
+  const RigidArgs ga{rigid ? s->na : 0, s->d_offsets, s->d_body, reinterpret_cast<const double4*>(s->d_r4), x + nb6,
+                     lub ? s->d_lrow : nullptr, s->d_lcol, s->d_lcoef, y + nb6};
+  launch_spread_fused<R>(s->spread, x, s->wp, static_cast<R*>(s->d_grid), table_of<R>(s), s->lpr, ra, ga, s->st, skip);
+}
+
 // `side`, when given, is further work independent of the wave-space chain: it follows the
 // real-space sum on the side stream (on the system stream when nothing is forked).
 template <typename R>
 void apply_mobility(fsd_system* s, const double* lam, double* out, int parts, const int* skip = nullptr,
                     const double* Vr = nullptr, const std::function<void(hipStream_t)>* side = nullptr) {
-  const bool fork = (parts & 1) && (parts & 2) && !s->timing;
-  if (parts & 1) {
+  // with a plan of 8^3 blocks the two parts share the first launch of the saddle operator (no
+  // aggregates in it) instead of an event, a second stream and a wait (64 beads: 81 -> 66 us)
+  const bool fused = parts == 3 && !side && !s->timing && spread_fuses(s->spread);
+  const bool fork = (parts & 1) && (parts & 2) && !s->timing && !fused;
+  if (fused) {
+    mob_first<R>(s, lam, out, skip, false);
+  } else if (parts & 1) {
     hipStream_t rs = s->st;
     if (fork) {
       HIPCHK(hipEventRecord(s->ev_fork, s->st));
@@ -885,7 +957,7 @@ void apply_mobility(fsd_system* s, const double* lam, double* out, int parts, co
   }
   if (parts & 2) {
     const double full = grid_bytes<R>(s), beads = 80.0 * s->nb;
-    {
+    if (!fused) {
       Timed t(s, FSD_TIMER_SPREAD, full + beads);
       mob_spread<R>(s, lam, skip);
     }
@@ -907,18 +979,6 @@ void apply_mobility(fsd_system* s, const double* lam, double* out, int parts, co
 double rigid_bytes(const fsd_system* s) {
   const bool lub = s->p.r_lub > 0 && s->nlub > 0;
   return 80.0 * s->nb + 96.0 * s->na + (lub ? 4.0 * (s->nb + 1) + 44.0 * s->nlub : 0.0);
-}
-
-// the fused first pass (Sigma/lubrication reduction, real-space sum, spreading) of y = A x
-template <typename R>
-void mob_first(fsd_system* s, const double* x, double* y, const int* skip) {
-  const size_t nb6 = 6 * size_t(s->nb);
-  const bool lub = s->p.r_lub > 0 && s->nlub > 0;
-  const RealArgs ra{s->nb, reinterpret_cast<const double4*>(s->d_pos4), s->d_nrow, s->d_ncol, s->rp, y,
-                    spread_plan_order(s->spread)};
-  const RigidArgs ga{s->na, s->d_offsets, s->d_body, reinterpret_cast<const double4*>(s->d_r4), x + nb6,
-                     lub ? s->d_lrow : nullptr, s->d_lcol, s->d_lcoef, y + nb6};
-  launch_spread_fused<R>(s->spread, x, s->wp, static_cast<R*>(s->d_grid), table_of<R>(s), s->lpr, ra, ga, s->st, skip);
 }
 
 // y1 = M lambda + Sigma^T V, y2 = Sigma (lambda - R_nf Sigma^T V).  With a spreading plan
@@ -1725,7 +1785,8 @@ fsd_status fsd_init_aggregates(fsd_system* s, int32_t n_agg, const int32_t* off,
     s->nwl = neighbor_work_create(nb);
     if (!s->nw || !s->nwl) throw ApiError(FSD_ENOMEM, "neighbour-list workspace allocation failed");
     HIPCHK(hipHostMalloc((void**)&s->h_flags, 2 * sizeof(int)));
-    HIPCHK(hipHostMalloc((void**)&s->h_scal, 4 * sizeof(double)));
+    s->io_cap = std::min(2 * s->n, kIoDoubles);
+    HIPCHK(hipHostMalloc((void**)&s->h_io, sizeof(double) * s->io_cap));
     s->h_flags[0] = s->h_flags[1] = 0;
     s->spread = spread_plan_create(nb, s->wp.n, s->wp.support, s->le);  // nullptr: scatter
     upload_tables(s);
@@ -1843,9 +1904,10 @@ fsd_status fsd_solve(fsd_system* s, double* U, double* lam, fsd_solve_info* info
   if (!U) return fail(s, FSD_EINVAL, "null output");
   return guarded(s, [&]() -> fsd_status {
     fsd_status r = solve_current(s, info);
-    HIPCHK(hipMemcpyAsync(U, s->d_U, sizeof(double) * 6 * s->na, hipMemcpyDeviceToHost, s->st));
-    if (lam) HIPCHK(hipMemcpyAsync(lam, s->d_x, sizeof(double) * 6 * s->nb, hipMemcpyDeviceToHost, s->st));
-    HIPCHK(hipStreamSynchronize(s->st));
+    HostIo io(s);
+    io.out(U, s->d_U, 6 * size_t(s->na));
+    if (lam) io.out(lam, s->d_x, 6 * size_t(s->nb));
+    io.finish();
     return r;
   });
 }
@@ -1873,8 +1935,9 @@ fsd_status fsd_get_state(const fsd_system* cs, double* com, double* quat, double
   fsd_status c = check_ready(s);
   if (c) return c;
   return guarded(s, [&]() -> fsd_status {
-    if (com) HIPCHK(hipMemcpyAsync(com, s->d_com, sizeof(double) * 3 * s->na, hipMemcpyDeviceToHost, s->st));
-    if (quat) HIPCHK(hipMemcpyAsync(quat, s->d_quat, sizeof(double) * 4 * s->na, hipMemcpyDeviceToHost, s->st));
+    HostIo io(s);
+    if (com) io.out(com, s->d_com, 3 * size_t(s->na));
+    if (quat) io.out(quat, s->d_quat, 4 * size_t(s->na));
     if (x_bead) {
       launch_bead_positions(s->nb, s->na, s->d_body, s->d_xbody, s->d_com, s->d_quat, s->L, s->gam(), s->d_r4,
                             s->d_pos4, s->st);
@@ -1886,7 +1949,7 @@ fsd_status fsd_get_state(const fsd_system* cs, double* com, double* quat, double
         for (int i = s->h_offsets[j]; i < s->h_offsets[j + 1]; ++i)
           for (int d = 0; d < 3; ++d) x_bead[3 * i + d] = X[3 * j + d] + r4[4 * size_t(i) + d];
     }
-    HIPCHK(hipStreamSynchronize(s->st));
+    io.finish();
     return FSD_OK;
   });
 }
@@ -1898,8 +1961,9 @@ fsd_status fsd_get_velocities(const fsd_system* cs, double* U) {
   if (c) return c;
   if (!s->solved) return fail(s, FSD_ESTATE, "no solve has completed");
   return guarded(s, [&]() -> fsd_status {
-    HIPCHK(hipMemcpyAsync(U, s->d_U, sizeof(double) * 6 * s->na, hipMemcpyDeviceToHost, s->st));
-    HIPCHK(hipStreamSynchronize(s->st));
+    HostIo io(s);
+    io.out(U, s->d_U, 6 * size_t(s->na));
+    io.finish();
     return FSD_OK;
   });
 }
@@ -2019,13 +2083,14 @@ fsd_status fsd_apply_mobility(fsd_system* s, const double* lam, double* u, int p
   return guarded(s, [&]() -> fsd_status {
     prepare(s);
     const size_t nb6 = 6 * size_t(s->nb);
-    HIPCHK(hipMemcpyAsync(s->d_z, lam, sizeof(double) * nb6, hipMemcpyHostToDevice, s->st));
+    HostIo io(s);
+    io.in(s->d_z, lam, nb6);
     if (precision == FSD_MIXED)
       apply_mobility<float>(s, s->d_z, s->d_w, parts);
     else
       apply_mobility<double>(s, s->d_z, s->d_w, parts);
-    HIPCHK(hipMemcpyAsync(u, s->d_w, sizeof(double) * nb6, hipMemcpyDeviceToHost, s->st));
-    HIPCHK(hipStreamSynchronize(s->st));
+    io.out(u, s->d_w, nb6);
+    io.finish();
     return FSD_OK;
   });
 }
@@ -2036,10 +2101,11 @@ fsd_status fsd_apply_saddle(fsd_system* s, const double* x, double* y, int preci
   if (!x || !y) return fail(s, FSD_EINVAL, "bad arguments");
   return guarded(s, [&]() -> fsd_status {
     prepare(s);
-    HIPCHK(hipMemcpyAsync(s->d_z, x, sizeof(double) * s->n, hipMemcpyHostToDevice, s->st));
+    HostIo io(s);
+    io.in(s->d_z, x, s->n);
     apply_saddle_p(s, s->d_z, s->d_w, precision == FSD_MIXED);
-    HIPCHK(hipMemcpyAsync(y, s->d_w, sizeof(double) * s->n, hipMemcpyDeviceToHost, s->st));
-    HIPCHK(hipStreamSynchronize(s->st));
+    io.out(y, s->d_w, s->n);
+    io.finish();
     return FSD_OK;
   });
 }
@@ -2050,10 +2116,11 @@ fsd_status fsd_apply_precond(fsd_system* s, const double* r, double* z) {
   if (!r || !z) return fail(s, FSD_EINVAL, "bad arguments");
   return guarded(s, [&]() -> fsd_status {
     prepare(s);
-    HIPCHK(hipMemcpyAsync(s->d_r, r, sizeof(double) * s->n, hipMemcpyHostToDevice, s->st));
+    HostIo io(s);
+    io.in(s->d_r, r, s->n);
     apply_precond(s, s->d_r, s->d_z);
-    HIPCHK(hipMemcpyAsync(z, s->d_z, sizeof(double) * s->n, hipMemcpyDeviceToHost, s->st));
-    HIPCHK(hipStreamSynchronize(s->st));
+    io.out(z, s->d_z, s->n);
+    io.finish();
     return FSD_OK;
   });
 }
@@ -2065,8 +2132,9 @@ fsd_status fsd_get_rhs(fsd_system* s, double* b) {
   return guarded(s, [&]() -> fsd_status {
     prepare(s);
     assemble_rhs(s);
-    HIPCHK(hipMemcpyAsync(b, s->d_b, sizeof(double) * s->n, hipMemcpyDeviceToHost, s->st));
-    HIPCHK(hipStreamSynchronize(s->st));
+    HostIo io(s);
+    io.out(b, s->d_b, s->n);
+    io.finish();
     return FSD_OK;
   });
 }

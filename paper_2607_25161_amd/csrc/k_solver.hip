@@ -290,6 +290,16 @@ void launch_zero(void* p, size_t bytes, hipStream_t st) {
   k_zero_words<<<nblocks((long long)n), kThreads, 0, st>>>(n, static_cast<uint32_t*>(p));
 }
 
+__global__ void k_copy(size_t n, const double* __restrict__ from, double* __restrict__ to) {
+  const size_t i = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i < n) to[i] = from[i];
+}
+
+// either side may be pinned host memory
+void launch_copy(size_t n, const double* from, double* to, hipStream_t st) {
+  if (n) k_copy<<<nblocks((long long)n), kThreads, 0, st>>>(n, from, to);
+}
+
 // An empty kernel launched when per-kernel timing is switched on and again when it is
 // switched off: in a profiler trace the launches between the two are the timed ones.
 __global__ void k_timing_mark() {}
