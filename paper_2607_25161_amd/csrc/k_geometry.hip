@@ -144,7 +144,8 @@ struct NeighborWork {
   int *cell_start = nullptr, *cell_end = nullptr, *counts = nullptr;
   void* temp = nullptr;
   size_t temp_bytes = 0;
-  int* total = nullptr;  // pinned host, row count of the last build
+  double4* pos = nullptr;  // the beads in sorted order, index and body in the fourth word
+  int* total = nullptr;    // pinned host, row count of the last build
 };
 
 NeighborWork* neighbor_work_create(int nb) {
@@ -155,6 +156,7 @@ NeighborWork* neighbor_work_create(int nb) {
             hipMalloc(&w->vals_in, sizeof(int) * nb) == hipSuccess &&
             hipMalloc(&w->vals_out, sizeof(int) * nb) == hipSuccess &&
             hipMalloc(&w->counts, sizeof(int) * (nb + 1)) == hipSuccess &&
+            hipMalloc(&w->pos, sizeof(double4) * nb) == hipSuccess &&
             hipHostMalloc(&w->total, sizeof(int)) == hipSuccess;
   size_t b1 = 0, b2 = 0;
   hipcub::DeviceRadixSort::SortPairs(nullptr, b1, w->keys_in, w->keys_out, w->vals_in, w->vals_out, nb);
@@ -175,6 +177,7 @@ void neighbor_work_destroy(NeighborWork* w) {
   (void)hipFree(w->vals_in);
   (void)hipFree(w->vals_out);
   (void)hipFree(w->counts);
+  (void)hipFree(w->pos);
   (void)hipFree(w->cell_start);
   (void)hipFree(w->cell_end);
   (void)hipFree(w->temp);
@@ -192,9 +195,18 @@ __global__ void k_cell_keys(int nb, const double4* __restrict__ pos, double cs, 
 }
 
 // [start, end) of every cell c in the sorted keys, by binary search (empty cells get
-// start == end), so no clearing of the two arrays is needed
-__global__ void k_cell_bounds(int nb, int ncell, const int* __restrict__ keys, int* start, int* end) {
+// start == end), so no clearing of the two arrays is needed; and the beads in sorted order, with
+// their index and body in the fourth word, so that the search reads its candidates in a row
+__global__ void k_cell_bounds(int nb, int ncell, const int* __restrict__ keys, const int* __restrict__ sorted,
+                              const double4* __restrict__ pos, const int* __restrict__ body, int* start, int* end,
+                              double4* __restrict__ spos) {
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
+  if (c < nb) {
+    const int j = sorted[c];
+    double4 p = pos[j];
+    p.w = __hiloint2double(body[j], j);
+    spos[c] = p;
+  }
   if (c >= ncell) return;
   int lo = 0, hi = nb;  // first key >= c
   while (lo < hi) {
@@ -210,59 +222,87 @@ __global__ void k_cell_bounds(int nb, int ncell, const int* __restrict__ keys, i
   end[c] = e;
 }
 
-// One wavefront per bead scans the 27 surrounding cells (nc >= 3, so each cell is visited
-// once and the minimum image is unique), its lanes testing 64 candidates of a cell at a
-// time; a ballot gives each hit its place, so a row lists its pairs cell by cell in sorted
-// order whatever the wavefront width.  Cells live in sheared coordinates; their side covers
-// the cutoff sphere's sheared extent r_c sqrt(1 + gam^2), and distances are Cartesian.
+// One wavefront per bead searches the 27 surrounding cells (nc >= 3, so each cell is visited
+// once and the minimum image is unique).  The three cells of a row lie together in sorted order,
+// or in two pieces around the box's edge: lane 2 r + h holds piece h of row r.  Their candidates
+// are tested 64 at a time across the pieces, four such rounds loaded together; a ballot gives each
+// hit its place, so a row lists its pairs cell by cell in sorted order whatever the wavefront
+// width.  Cells live in sheared coordinates; their side covers the cutoff sphere's sheared extent
+// r_c sqrt(1 + gam^2), and distances are Cartesian.
+// What bounds it: the latency of its loads.  Cell after cell, each with a chain of bounds, index and
+// position, the two searches of 81,920 beads (189 neighbours each, and the lubrication pairs) took
+// 640 us to count and 690 to fill, now 282 and 314 (with the image found by a division 409 and 474;
+// two or eight rounds at a time 302 and 308 to count); of 1,500 beads 40 and 41 us, now 13 each.
 template <bool FILL>
 __global__ __launch_bounds__(256) void k_cell_pairs(int nb, const double4* __restrict__ pos,
                                                     const int* __restrict__ body, double L, double gam, double cs,
                                                     int nc, double rc2, int exclude_same_body,
                                                     const int* __restrict__ start, const int* __restrict__ end,
-                                                    const int* __restrict__ sorted, int* counts,
+                                                    const double4* __restrict__ spos, int* counts,
                                                     const int* __restrict__ rowptr, uint32_t* __restrict__ col) {
+  constexpr int U = 4;
   const int lane = threadIdx.x & 63;
   const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (i >= nb) return;  // whole wavefronts leave together
   if (!FILL && i == 0 && lane == 0) counts[nb] = 0;  // the scan's last input: rowptr[nb] = total
   const double4 p = pos[i];
   const int bi = body[i];
+  const int base = FILL ? rowptr[i] : 0;
   const int cx = min(nc - 1, int(p.x / cs)), cy = min(nc - 1, int(p.y / cs)), cz = min(nc - 1, int(p.z / cs));
+  const bool edge = cx == 0 || cx == nc - 1;
+  int first = 0, n = 0;
+  if (lane < 18) {
+    const int r = lane >> 1;
+    const int z = (cz + r / 3 - 1 + nc) % nc, y = (cy + r % 3 - 1 + nc) % nc, c = (z * nc + y) * nc;
+    int xa = cx - 1, xb = cx + 1;  // cells xa .. xb
+    if (cx == 0) xa = lane & 1 ? 0 : nc - 1, xb = lane & 1 ? 1 : nc - 1;
+    if (cx == nc - 1) xa = lane & 1 ? 0 : nc - 2, xb = lane & 1 ? 0 : nc - 1;
+    if (edge || !(lane & 1)) {
+      first = start[c + xa];
+      n = end[c + xb] - first;
+    }
+  }
+  int upto = n;  // candidates up to and with this piece
+#pragma unroll
+  for (int o = 1; o < 32; o <<= 1) {
+    const int v = __shfl_up(upto, o);
+    if (lane >= o) upto += v;
+  }
+  const int before = upto - n, shift = first - before, total = __builtin_amdgcn_readlane(upto, 17);
+  const int step = __builtin_amdgcn_readfirstlane(edge ? 1 : 2);  // inner beads have no second pieces
+  const double iL = 1.0 / L;  // a pair within the cutoff is at most L / 3 apart, far from the ties of rint
   const unsigned long long below = (1ull << lane) - 1ull;
   int cnt = 0;
-  const int base = FILL ? rowptr[i] : 0;
-  for (int dz = -1; dz <= 1; ++dz) {
-    const int z = (cz + dz + nc) % nc;
-    for (int dy = -1; dy <= 1; ++dy) {
-      const int y = (cy + dy + nc) % nc;
-      for (int dx = -1; dx <= 1; ++dx) {
-        const int x = (cx + dx + nc) % nc;
-        const int c = (z * nc + y) * nc + x;
-        const int k1 = end[c];
-        for (int k0 = start[c]; k0 < k1; k0 += 64) {
-          const int k = k0 + lane;
-          bool hit = false;
-          uint32_t entry = 0;
-          if (k < k1) {
-            const int j = sorted[k];
-            if (j != i && !(exclude_same_body && body[j] == bi)) {
-              const double4 q = pos[j];
-              double ddx = p.x - q.x, ddy = p.y - q.y, ddz = p.z - q.z;
-              const double sx = -rint(ddx / L), sy = -rint(ddy / L), sz = -rint(ddz / L);
-              ddx += sx * L;
-              ddy += sy * L;
-              ddz += sz * L;
-              ddx += gam * ddy;
-              hit = ddx * ddx + ddy * ddy + ddz * ddz < rc2;
-              if (FILL && hit) entry = pack_entry(j, int(sx), int(sy), int(sz));
-            }
-          }
-          const unsigned long long m = __ballot(hit);
-          if (FILL && hit) col[base + cnt + __popcll(m & below)] = entry;
-          cnt += __popcll(m);
-        }
-      }
+  for (int g0 = 0; g0 < total; g0 += 64 * U) {
+    int k[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) k[u] = __builtin_amdgcn_readlane(shift, 0);
+    for (int r = step; r < 18; r += step) {
+      const int from = __builtin_amdgcn_readlane(before, r), by = __builtin_amdgcn_readlane(shift, r);
+#pragma unroll
+      for (int u = 0; u < U; ++u) k[u] = g0 + 64 * u + lane >= from ? by : k[u];
+    }
+    double4 q[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int g = g0 + 64 * u + lane;
+      q[u] = spos[g < total ? k[u] + g : 0];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = __double2loint(q[u].w);
+      double ddx = p.x - q[u].x, ddy = p.y - q[u].y, ddz = p.z - q[u].z;
+      const double sx = -rint(ddx * iL), sy = -rint(ddy * iL), sz = -rint(ddz * iL);
+      ddx += sx * L;
+      ddy += sy * L;
+      ddz += sz * L;
+      ddx += gam * ddy;
+      const bool hit = g0 + 64 * u + lane < total && j != i &&
+                       !(exclude_same_body && __double2hiint(q[u].w) == bi) &&
+                       ddx * ddx + ddy * ddy + ddz * ddz < rc2;
+      const unsigned long long m = __ballot(hit);
+      if (FILL && hit) col[base + cnt + __popcll(m & below)] = pack_entry(j, int(sx), int(sy), int(sz));
+      cnt += __popcll(m);
     }
   }
   if (!FILL && lane == 0) counts[i] = cnt;
@@ -329,9 +369,10 @@ hipError_t neighbors_count(NeighborWork* w, int nb, const double* pos4v, const i
     if ((e = hipcub::DeviceRadixSort::SortPairs(w->temp, tb, w->keys_in, w->keys_out, w->vals_in, w->vals_out, nb, 0,
                                                  bits, st)) != hipSuccess)
       return e;
-    k_cell_bounds<<<nblocks(ncell), kThreads, 0, st>>>(nb, ncell, w->keys_out, w->cell_start, w->cell_end);
+    k_cell_bounds<<<nblocks(std::max(nb, ncell)), kThreads, 0, st>>>(nb, ncell, w->keys_out, w->vals_out, pos, body,
+                                                                     w->cell_start, w->cell_end, w->pos);
     k_cell_pairs<false><<<nblocks(nb, 4), kThreads, 0, st>>>(nb, pos, body, L, gam, cs, nc, rc2, exclude_same_body,
-                                                           w->cell_start, w->cell_end, w->vals_out, w->counts,
+                                                           w->cell_start, w->cell_end, w->pos, w->counts,
                                                            nullptr, nullptr);
   } else {
     const int nmax = int(reach / L) + 1;
@@ -356,7 +397,7 @@ hipError_t neighbors_fill(NeighborWork* w, int nb, const double* pos4v, const in
   if (nc >= 3) {
     const double cs = L / nc;
     k_cell_pairs<true><<<nblocks(nb, 4), kThreads, 0, st>>>(nb, pos, body, L, gam, cs, nc, rc2, exclude_same_body,
-                                                          w->cell_start, w->cell_end, w->vals_out, nullptr, rowptr,
+                                                          w->cell_start, w->cell_end, w->pos, nullptr, rowptr,
                                                           col);
   } else {
     const int nmax = int(cutoff * sqrt(1.0 + gam * gam) / L) + 1;
