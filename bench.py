@@ -35,10 +35,11 @@ METRIC = "bead-solves/s at 1e-5 saddle residual vs plain FP64; p50/p99 solve lat
 PEAK_HBM_GBS = 8000.0
 
 
-# kernel behind each timer class (rocprofv3 names), for matching the two measurements
-KERNEL_OF = {"real_sum": "k_real_sum", "spread": "k_spread_fused", "fft_first": "k_fft_lines<2>",
-             "fft_y": "k_fft_lines<1>", "fft_green": "k_fft_xgreen", "fft_last": "k_fft_lines<2>",
-             "interp": "k_interp", "rigid_lub": "k_agg_lub", "precond": "k_precond_fused",
+# kernel behind each timer class (rocprofv3 names), for matching the two measurements; from 4,096
+# beads on interpolation is k_interp_tile and k_interp_join, in batches kb_interp_tile and kb_interp_join
+KERNEL_OF = {"real_sum": "k_real_sum", "spread": "k_spread_fused", "fft_first": "k_wave_lines<2>",
+             "fft_y": "k_wave_lines<1>", "fft_green": "k_wave_green", "fft_last": "k_wave_lines<2>",
+             "interp": "k_interp_plan", "rigid_lub": "k_agg_lub", "precond": "k_precond_fused",
              "cgs_dot": "k_cgs_chain<0>", "cgs_update": "k_cgs_chain<1>", "cgs_norm_arnoldi": "k_cgs_chain<2>"}
 
 
@@ -47,7 +48,7 @@ def batch_kernel_names(prec):
     R = "float" if prec else "double"
     return {"real_sum": f"kb_real<{R}>", "spread": f"kb_spread<{R}>", "fft_first": f"kb_fft<{R}, 0>",
             "fft_y": f"kb_fft<{R}, 1>", "fft_green": f"kb_fft<{R}, 2>", "fft_last": f"kb_fft<{R}, 4>",
-            "interp": f"kb_interp<{R}>", "rigid_lub": "kb_agg", "precond": "kb_precond",
+            "interp": f"kb_interp_tile<{R}>", "rigid_lub": "kb_agg", "precond": "kb_precond",
             "cgs_dot": "kb_cgs<0>", "cgs_update": "kb_cgs<1>", "cgs_norm_arnoldi": "kb_cgs<2>"}
 
 
@@ -71,11 +72,11 @@ def kernel_table(timers, steps, names=None):
 
 
 # source file of each kernel, whose hash the counter summaries record
-SOURCE_OF = {"kb_fft<float, 2>": "k_mobility.hip", "kb_fft<float, 0>": "k_mobility.hip",
-             "kb_fft<float, 1>": "k_mobility.hip", "kb_fft<float, 4>": "k_mobility.hip",
-             "kb_spread<float>": "k_mobility.hip", "kb_interp<float>": "k_mobility.hip",
-             "k_real_sum": "k_mobility.hip", "k_spread_fused": "k_mobility.hip", "k_spread_split": "k_mobility.hip", "k_fft_lines<1>": "k_mobility.hip",
-             "k_fft_lines<2>": "k_mobility.hip", "k_fft_xgreen": "k_mobility.hip", "k_interp": "k_mobility.hip",
+SOURCE_OF = {"kb_fft<float, 2>": "fft_regs.hpp", "kb_fft<float, 0>": "fft_regs.hpp",
+             "kb_fft<float, 1>": "fft_regs.hpp", "kb_fft<float, 4>": "fft_regs.hpp",
+             "kb_spread<float>": "k_mobility.hip", "kb_interp_tile<float>": "k_mobility.hip",
+             "k_real_sum": "k_mobility.hip", "k_spread_fused": "k_mobility.hip", "k_wave_lines<1>": "fft_regs.hpp",
+             "k_wave_lines<2>": "fft_regs.hpp", "k_wave_green": "fft_regs.hpp", "k_interp_plan": "k_mobility.hip",
              "k_agg_lub": "k_solver.hip", "k_precond_fused": "k_solver.hip", "k_cgs_chain<0>": "k_solver.hip",
              "k_cgs_chain<1>": "k_solver.hip", "k_cgs_chain<2>": "k_solver.hip"}
 

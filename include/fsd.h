@@ -205,8 +205,9 @@ fsd_status fsd_autotune_xi(fsd_system* s, double xi_lo, double xi_hi, int reps, 
 
 /* Measured tile shapes of the transform passes: the lines per workgroup of the z and y
  * passes (B, a divisor of the grid side) and the row pairs per workgroup of the x+Green pass
- * (G) are timed over reps back-to-back launches each (fsd_time_kernel) in the system's
- * precision, and the fastest are kept for every later launch of s (captured graphs are
+ * (G), and the two-step passes of sides that have them (B or G reported as 0), are timed over
+ * reps back-to-back launches each (fsd_time_kernel) in the system's precision, and the fastest
+ * are kept for every later launch of s (captured graphs are
  * rebuilt).  Both stay within 64 KB of LDS per workgroup.  lines_b and green_g (may be
  * NULL) get the choice.  The grid is left undefined, as by fsd_time_kernel. */
 fsd_status fsd_autotune_tiles(fsd_system* s, int reps, int* lines_b, int* green_g);

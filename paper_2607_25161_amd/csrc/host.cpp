@@ -868,8 +868,9 @@ const float* twiddle_of<float>(fsd_system* s) {
 }
 
 // out = M lam (parts: 1 real space, 2 wave space); with Vr != nullptr the rigid
-// velocities Sigma^T Vr are added in the interpolation kernel.  Untimed, the
-// real-space sum runs on the side stream, overlapping spreading and the transforms.
+// velocities Sigma^T Vr are added in the interpolation kernel.  Untimed, on a grid
+// without a plan of 8^3 blocks, the real-space sum runs on the side stream, overlapping spreading
+// and the transforms.
 // One launch of each mobility kernel class (the wave-space ones work on the system grid).
 template <typename R>
 void mob_real(fsd_system* s, const double* lam, double* out, hipStream_t rs, const int* skip) {

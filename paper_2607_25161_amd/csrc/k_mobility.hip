@@ -6,8 +6,8 @@
 // and interpolated to the beads, where the grid holds u_c + i w_c.
 //
 // Real space: per neighbour pair within the cutoff, the free-space RPY block
-// minus the smooth inverse transform of the damped multiplier, read from a
-// table by cubic interpolation.
+// minus the smooth inverse transform of the damped multiplier, held as
+// piecewise polynomials of the distance.
 #include <hipcub/hipcub.hpp>
 
 #include <algorithm>
@@ -108,9 +108,10 @@ __device__ __forceinline__ void smooth_part(const R* T, R r, R inv_w, R (&f)[5])
 // 12 of the 17 loads of a pair: at 15.5 million pairs (81,920 beads) 367 us in FP64 and 230 in
 // FP32, the rate at which a CU looks up cache lines.  As 64 intervals of degree 6 (FP64) or 128
 // of degree 3 (FP32) it is 18 or 10 KB that every workgroup copies to LDS, and is closer to the
-// quadrature than the table was (4e-14 of the self mobility against 1e-13): 140 us in FP64 (with
-// four wavefronts a SIMD; 154 with the three that its registers would leave), 114 in FP32.  A workgroup takes a contiguous chunk of rows, in the plan's spatial order where there
-// is one, so that the copy is paid once per many rows.
+// quadrature than the table was (4e-14 of the self mobility against 1e-13): with 32 lanes a row 140 us in FP64
+// (with four wavefronts a SIMD; 154 with the three that its registers would leave) and 112 in FP32,
+// with 16 132 and 108.  A workgroup takes a contiguous chunk of rows, in the plan's spatial order
+// where there is one, so that the copy is paid once per many rows.
 template <typename R, int LPR>
 __device__ __forceinline__ void real_sum_body(int nb, const double4* __restrict__ pos,
                                               const double* __restrict__ lam, const int* __restrict__ rowptr,
@@ -998,7 +999,7 @@ __global__ __launch_bounds__(BS* BS* BS) void k_spread_gather(const int* __restr
 // sum is in list order.  The products of 81,920 beads take 45 us in FP64 and 22 in FP32 at the
 // matrix rate; what is left is the latency from the candidate's record to its weights and the
 // store of the grid, which other blocks' wavefronts cover.  Measured in the first pass of the
-// saddle operator (128^3, beside 140 and 115 us of pair sum): 234 us in FP64 and 163 in FP32; with
+// saddle operator (128^3, beside 132 and 108 us of pair sum): 224 us in FP64 and 159 in FP32; with
 // one lane per (x, y) column on the vector units it took 415 and 278.  The scatter with atomics of
 // the sheared lattice took 250 (FP64, 2,048 beads) to 410 us (FP32, 6,011), now 17 and 22.
 template <typename R, bool SHEAR>
