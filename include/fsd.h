@@ -205,7 +205,7 @@ fsd_status fsd_autotune_xi(fsd_system* s, double xi_lo, double xi_hi, int reps, 
 
 /* Measured tile shapes of the transform passes: the lines per workgroup of the z and y
  * passes (B, a divisor of the grid side) and the row pairs per workgroup of the x+Green pass
- * (G), and the two-step passes of sides that have them (B or G reported as 0), are timed over
+ * (G), and the two-step passes of sides that have them (their own B and G), are timed over
  * reps back-to-back launches each (fsd_time_kernel) in the system's precision, and the fastest
  * are kept for every later launch of s (captured graphs are
  * rebuilt).  Both stay within 64 KB of LDS per workgroup.  lines_b and green_g (may be
