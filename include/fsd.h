@@ -187,6 +187,10 @@ fsd_status fsd_get_stresslets(fsd_system* s, double* S_agg, double* S_mean);
  * decisions (the serving form); 0 for invalid arguments. */
 size_t fsd_estimate_bytes(const fsd_params* p, int32_t n_bead, int32_t n_agg, double L);
 
+/* The same for a system on the sheared lattice (sheared != 0: its larger grid and spreading plan)
+ * or on the cube. */
+size_t fsd_estimate_bytes_on(const fsd_params* p, int32_t n_bead, int32_t n_agg, double L, int sheared);
+
 /* Text of the last error of s; with s == NULL, of the calling thread's last failed
  * call that takes no system (fsd_fft3d).  Owned by the library. */
 const char* fsd_last_error(const fsd_system* s);
@@ -369,7 +373,7 @@ fsd_status fsd_fft3d_noalloc(int n, int sign, double* d_data, void* hip_stream);
 /* ---- batches of independent systems (many small suspensions sharing the GPU) -------- */
 
 /* A batch holds up to max_slots systems whose device memory counts against
- * mem_budget_bytes (fsd_estimate_bytes of each).  Systems stay owned by the caller
+ * mem_budget_bytes (fsd_estimate_bytes_on of each, for its lattice).  Systems stay owned by the caller
  * and keep their state, neighbour lists and factors resident between steps; give
  * each its own stream (fsd_create with NULL) so their work overlaps on the GPU. */
 typedef struct fsd_batch fsd_batch;

@@ -79,6 +79,7 @@ _sig("fsd_get_velocities", C.c_int, _SYS, _D)
 _sig("fsd_get_info", C.c_int, _SYS, C.POINTER(Info))
 _sig("fsd_get_stresslets", C.c_int, _SYS, _D, _D)
 _sig("fsd_estimate_bytes", C.c_size_t, C.POINTER(Params), C.c_int32, C.c_int32, C.c_double)
+_sig("fsd_estimate_bytes_on", C.c_size_t, C.POINTER(Params), C.c_int32, C.c_int32, C.c_double, C.c_int)
 _sig("fsd_last_error", C.c_char_p, _SYS)
 _sig("fsd_destroy", None, _SYS)
 _sig("fsd_apply_mobility", C.c_int, _SYS, _D, _D, C.c_int, C.c_int)
@@ -157,8 +158,8 @@ def default_params(**kw) -> Params:
     return p
 
 
-def estimate_bytes(params: Params, n_bead: int, n_agg: int, L: float) -> int:
-    return int(lib.fsd_estimate_bytes(C.byref(params), n_bead, n_agg, L))
+def estimate_bytes(params: Params, n_bead: int, n_agg: int, L: float, lees_edwards: bool = False) -> int:
+    return int(lib.fsd_estimate_bytes_on(C.byref(params), n_bead, n_agg, L, 1 if lees_edwards else 0))
 
 
 def philox4x64(k0: int, k1: int, counter, n_blocks: int) -> np.ndarray:

@@ -137,6 +137,10 @@ void launch_displace(int na, const double* com0, const double* quat0, const doub
 // and the periodic image shift (3 x 3 bits, offset by 3).
 struct NeighborWork;
 NeighborWork* neighbor_work_create(int nb);
+size_t neighbor_work_bytes(int nb, double L, double cutoff);  // device bytes it takes at most
+// Upper bound of the temporary storage of a library sort of n pairs of ints (queried for 1 to 3.4e8
+// pairs: 8 bytes a pair beside at most 0.063, 256 bytes up to 1,000)
+inline size_t sort_pairs_bytes(size_t n) { return size_t(8.1 * double(n)) + 4096; }
 void neighbor_work_destroy(NeighborWork* w);
 // Two phases: neighbors_count launches per-row counts and the scan into rowptr
 // and copies the total to pinned memory (read it with neighbors_total once the
@@ -197,6 +201,7 @@ struct SpreadPlan;
 // nullptr if n_grid has no blocks: not a multiple of 4, or of 8 on a sheared lattice
 SpreadPlan* spread_plan_create(int nb, int n_grid, int support, bool sheared);
 bool spread_plan_sheared(const SpreadPlan* sp);
+size_t spread_plan_bytes(int nb, int n_grid, int support, bool sheared);  // device bytes it takes
 void spread_plan_destroy(SpreadPlan* sp);
 hipError_t spread_plan_update(SpreadPlan* sp, const double* pos4, const WaveParams& wp, hipStream_t st);
 template <typename R>

@@ -242,6 +242,16 @@ double pick_xi(const fsd_params& p, int nb, double L) {
   return best;
 }
 
+// on a sheared lattice the grid's modes reach |k| >= (N pi / L) / sqrt(1 + gamma^2) in every
+// direction, so the grid grows by sqrt(5)/2 (|gamma| <= 1/2) to keep the cutoff k_c
+double lattice_margin(bool sheared) { return sheared ? std::sqrt(1.25) : 1.0; }
+
+// points of the Gaussian support along an axis
+int support_of(const fsd_params& p) {
+  const int P = p.support > 0 ? p.support : int(std::ceil(2.0 / M_PI * std::log(1.0 / p.ewald_tol))) + 2;
+  return std::max(4, std::min(P, 21));
+}
+
 }  // namespace
 
 // ==========================================================================================
@@ -610,15 +620,11 @@ void choose_parameters(fsd_system* s) {
   const double lnt = std::sqrt(-std::log(tol));
   const double rc = lnt / xi;
   const double kc = 2.0 * lnt * xi + 1.0 / a;
-  // on a sheared lattice the grid's modes reach |k| >= (N pi / L) / sqrt(1 + gamma^2) in every
-  // direction, so the grid grows by sqrt(5)/2 (|gamma| <= 1/2) to keep the cutoff k_c
-  const double le_margin = s->le ? std::sqrt(1.25) : 1.0;
-  int N = p.grid > 0 ? p.grid : next_smooth(int(std::ceil(kc * L / M_PI * le_margin)));
+  int N = p.grid > 0 ? p.grid : next_smooth(int(std::ceil(kc * L / M_PI * lattice_margin(s->le))));
   if (N > kMaxGrid) throw ApiError(FSD_EINVAL, "spectral grid above 256^3; raise xi or lower the tolerance");
   if (!make_plan(N, s->plan))
     throw ApiError(FSD_EINVAL, "grid size must be a product of powers of 2, 3 and 5");
-  int P = p.support > 0 ? p.support : int(std::ceil(2.0 / M_PI * std::log(1.0 / tol))) + 2;
-  P = std::max(4, std::min(P, 21));
+  const int P = support_of(p);
   if (P > N) throw ApiError(FSD_EINVAL, "Gaussian support exceeds the grid");
   const double h = L / N;
   const double mshape = 0.976 * std::sqrt(M_PI * P);
@@ -2047,29 +2053,35 @@ fsd_status fsd_get_info(const fsd_system* cs, fsd_info* info) {
 }
 
 size_t fsd_estimate_bytes(const fsd_params* p, int32_t nb, int32_t na, double L) {
+  return fsd_estimate_bytes_on(p, nb, na, L, 0);
+}
+
+size_t fsd_estimate_bytes_on(const fsd_params* p, int32_t nb, int32_t na, double L, int sheared) {
   if (!p || nb <= 0 || na <= 0 || !(L > 0)) return 0;
   const double a = p->radius;
   const double xi = pick_xi(*p, nb, L);
   const double lnt = std::sqrt(-std::log(p->ewald_tol));
   const double rc = 1.15 * lnt / xi;
-  int N = p->grid > 0 ? p->grid : next_smooth(int(std::ceil((2.0 * lnt * xi + 1.0 / a) * L / M_PI)));
+  const int N = p->grid > 0 ? p->grid
+                            : next_smooth(int(std::ceil((2.0 * lnt * xi + 1.0 / a) * L / M_PI * lattice_margin(sheared))));
   const double dens = nb / (L * L * L);
   const double nnz = nb * (4.19 * rc * rc * rc * dens * 1.3 + 64);
   const double rl = p->r_lub;
   const double nl = rl > 0 ? nb * (4.19 * rl * rl * rl * dens * 2.0 + 16) : 0;
-  const double n = 6.0 * (nb + na);
+  const size_t n = 6 * (size_t(nb) + na);
   const int m = p->gmres_restart;
-  double bytes = 48.0 * double(N) * N * N + 4.0 * nnz + 44.0 * nl + 8.0 * n * (m + 9) + 200.0 * nb + 400.0 * na +
-                 8.0 * (m + 2) * 1024 + 8.0 * 64 * 38 + 4.0 * 128 * 20 + (1 << 20);
+  // grid and Green's multipliers; pair lists; Krylov basis and six more vectors; beads, bodies
+  double bytes = 48.0 * double(N) * N * N + 54.0 * double(N) * N + 4.0 * nnz + 44.0 * nl + 8.0 * n * (m + 7) +
+                 196.0 * nb + 468.0 * na + 8.0 * std::max(size_t(m + 2) * 1024, size_t(96) * cgs_blocks(n)) +
+                 double(RealPoly<double>::kBytes + RealPoly<float>::kBytes) + (1 << 20);
+  bytes += double(neighbor_work_bytes(nb, L, lnt / xi)) + double(neighbor_work_bytes(nb, L, rl > 0 ? rl : L));
   if (p->kT > 0) {  // Lanczos basis and partials, Brownian vectors
     const double lm = p->lanczos_maxit > 0 ? p->lanczos_maxit : 100;
     bytes += 8.0 * nb * (6.0 * (lm + 1) + 24) + 8.0 * (lm + 2) * 1024;
   }
-  // spreading plan: 3P weights per bead (FP64 and FP32) and up to 27 block
-  // slots per bead (keys and values, sorted copies and the sort's temporary storage)
-  const int P = p->support > 0 ? p->support : int(std::ceil(2.0 / M_PI * std::log(1.0 / p->ewald_tol))) + 2;
-  bytes += double(nb) * (12.0 * 3 * P + 27.0 * 48.0);
-  return size_t(bytes);
+  bytes += double(spread_plan_bytes(nb, N, support_of(*p), sheared != 0));
+  // large allocations come in pieces of 2 MiB, and the two streams hold one each
+  return size_t(bytes * (1.0 + 1.0 / 32)) + (4 << 20);
 }
 
 const char* fsd_last_error(const fsd_system* s) { return s ? s->err.c_str() : g_last_error.c_str(); }
@@ -2711,15 +2723,13 @@ struct fsd_batch {
 };
 
 namespace {
+// the estimate for the lattice the system is on, with the grid it holds (a system switched back to
+// the cube keeps the sheared lattice's)
 size_t system_bytes(const fsd_system* s) {
   fsd_params p = s->p;
-  p.grid = s->wp.n;  // the grid it holds (larger on a sheared lattice than the rule gives)
-  size_t bytes = fsd_estimate_bytes(&p, s->nb, s->na, s->L);
-  if (spread_plan_sheared(s->spread)) {  // P^2 + P weights instead of 3 P, row starts, up to 45 slots
-    const size_t P = size_t(s->wp.support);
-    bytes += size_t(s->nb) * (12 * (P * P + P) + 2 * P + 18 * 48);
-  }
-  return bytes;
+  p.xi = s->wp.xi;
+  p.grid = s->wp.n;
+  return fsd_estimate_bytes_on(&p, s->nb, s->na, s->L, s->le || spread_plan_sheared(s->spread));
 }
 
 // One solve (and optionally an Euler step) for every admitted system.  Each system

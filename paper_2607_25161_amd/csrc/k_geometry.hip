@@ -148,6 +148,16 @@ struct NeighborWork {
   int* total = nullptr;    // pinned host, row count of the last build
 };
 
+namespace {
+int cells_a_side(double L, double reach) { return std::min(int(std::min(L / reach, 1e6)), 1024); }
+}  // namespace
+
+size_t neighbor_work_bytes(int nb, double L, double cutoff) {
+  const int nc = cells_a_side(L, cutoff);
+  return size_t(nb) * (4 * sizeof(int) + sizeof(double4)) + sizeof(int) * (size_t(nb) + 1) + sort_pairs_bytes(nb) +
+         (nc >= 3 ? 2 * sizeof(int) * size_t(nc) * nc * nc : 0);
+}
+
 NeighborWork* neighbor_work_create(int nb) {
   auto* w = new NeighborWork;
   w->nb = nb;
@@ -379,8 +389,7 @@ hipError_t neighbors_count(NeighborWork* w, int nb, const double* pos4v, const i
   const double4* pos = (const double4*)pos4v;
   const double rc2 = cutoff * cutoff;
   const double reach = cutoff * sqrt(1.0 + gam * gam);  // sheared extent of the cutoff sphere
-  int nc = int(L / reach);
-  if (nc > 1024) nc = 1024;
+  const int nc = cells_a_side(L, reach);
   w->nc = nc;
   hipError_t e;
   if (nc >= 3) {

@@ -601,19 +601,54 @@ int pick_block(int N) {
   if (N % 4 == 0) return 4;
   return 0;
 }
+
+// Sizes of a plan (BS == 0: the grid has none), for its creation and for the memory estimate
+struct PlanShape {
+  int BS, nbin, K;
+  int kc, kcx;         // 8^3 blocks: blocks a support can reach along y and z, and along x
+  size_t wlen, slots;  // weights and block slots of a bead
+};
+
+PlanShape plan_shape(int N, int P, bool sheared) {
+  PlanShape h{};
+  h.BS = pick_block(N);
+  if (sheared && h.BS != 8) h.BS = 0;
+  if (h.BS == 0) return h;
+  h.nbin = N / h.BS;
+  h.wlen = sheared ? size_t(P) * P + P : size_t(3) * P;
+  h.K = std::min(1 + (P - 1 + h.BS - 1) / h.BS, h.nbin);
+  if (h.BS == 8) {
+    h.kc = h.K;
+    // the rows of a sheared support start up to ceil((P - 1) / 2) points apart (|strain| <= 1/2)
+    h.kcx = sheared ? std::min(1 + (P + P / 2 - 1 + 7) / 8, h.nbin) : h.kc;
+    h.slots = size_t(h.kcx) * h.kc * h.kc;
+  }
+  return h;
+}
 }  // namespace
 
+size_t spread_plan_bytes(int nb, int N, int P, bool sheared) {
+  const PlanShape h = plan_shape(N, P, sheared);
+  if (h.BS == 0) return 0;
+  // per bead: four sort arrays, the start, the weights in FP64 and FP32, the rows' starts; per slot: the
+  // candidate record, the slot's place, and what spread_plan_create gives the scratch
+  const size_t bead = 4 * sizeof(int) + sizeof(int4) + 12 * h.wlen + (sheared ? 2 * P : 0);
+  const size_t slot = h.BS == 8 ? sizeof(int4) + sizeof(int) + 6 * sizeof(double) : 0;
+  return nb * (bead + slot * h.slots) + sort_pairs_bytes(nb) + 2 * sizeof(int) * size_t(h.nbin) * h.nbin * h.nbin;
+}
+
 SpreadPlan* spread_plan_create(int nb, int N, int P, bool sheared) {
-  const int BS = pick_block(N);
-  if (BS == 0 || (sheared && BS != 8)) return nullptr;
+  const PlanShape h = plan_shape(N, P, sheared);
+  const int BS = h.BS;
+  if (BS == 0) return nullptr;
   auto* sp = new SpreadPlan;
   sp->nb = nb;
   sp->BS = BS;
-  sp->nbin = N / BS;
+  sp->nbin = h.nbin;
   sp->P = P;
   sp->sheared = sheared;
-  sp->wlen = sheared ? P * P + P : 3 * P;
-  sp->K = std::min(1 + (P - 1 + BS - 1) / BS, sp->nbin);
+  sp->wlen = int(h.wlen);
+  sp->K = h.K;
   const int nbins = sp->nbin * sp->nbin * sp->nbin;
   const size_t nw = size_t(sp->wlen) * nb;
   bool ok = hipMalloc(&sp->keys_in, sizeof(int) * nb) == hipSuccess &&
@@ -633,10 +668,9 @@ SpreadPlan* spread_plan_create(int nb, int N, int P, bool sheared) {
          hipMalloc(&sp->bin_end, sizeof(int) * nbins) == hipSuccess;
   }
   if (ok && BS == 8) {
-    sp->kc = std::min(sp->K, sp->nbin);
-    // the rows of a sheared support start up to ceil((P - 1) / 2) points apart (|strain| <= 1/2)
-    sp->kcx = sheared ? std::min(1 + (P + P / 2 - 1 + 7) / 8, sp->nbin) : sp->kc;
-    const size_t slots = size_t(nb) * sp->kcx * sp->kc * sp->kc;
+    sp->kc = h.kc;
+    sp->kcx = h.kcx;
+    const size_t slots = nb * h.slots;
     ok = hipMalloc(&sp->blk_start, sizeof(int) * nbins) == hipSuccess &&
          hipMalloc(&sp->blk_end, sizeof(int) * nbins) == hipSuccess &&
          hipMalloc(&sp->cand, sizeof(int4) * slots) == hipSuccess &&

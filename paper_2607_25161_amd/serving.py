@@ -61,13 +61,11 @@ class LibBackend:
         self.drift = drift
 
     def estimate(self, req: Request) -> int:
-        """Device bytes the request's system will hold.  On the sheared lattice the library
-        grows the grid by sqrt(5)/2 per side; sizing the estimate on a box that much larger
-        bounds that grid from above (the other terms only grow with it)."""
+        """Device bytes the request's system will hold on the backend's lattice: what the batch
+        counts when it admits the system."""
         s = req.suspension
         p = self.F.default_params(**self._kw(s))
-        L = s.L * (1.25 ** 0.5 if self.lees_edwards else 1.0)
-        return self.F.estimate_bytes(p, s.n_bead, s.n_agg, L)
+        return self.F.estimate_bytes(p, s.n_bead, s.n_agg, s.L, self.lees_edwards)
 
     def _kw(self, s):
         kw = dict(eta=s.eta, radius=s.a, xi=s.xi, ewald_tol=s.ewald_tol, grid=s.grid, r_lub=s.r_lub,
