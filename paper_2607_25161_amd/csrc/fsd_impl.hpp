@@ -200,7 +200,6 @@ void launch_wave_fft(R* grid, const FftPlan& plan, const R* twiddle, const WaveP
 struct SpreadPlan;
 // nullptr if n_grid has no blocks: not a multiple of 4, or of 8 on a sheared lattice
 SpreadPlan* spread_plan_create(int nb, int n_grid, int support, bool sheared);
-bool spread_plan_sheared(const SpreadPlan* sp);
 size_t spread_plan_bytes(int nb, int n_grid, int support, bool sheared);  // device bytes it takes
 void spread_plan_destroy(SpreadPlan* sp);
 hipError_t spread_plan_update(SpreadPlan* sp, const double* pos4, const WaveParams& wp, hipStream_t st);

@@ -342,6 +342,7 @@ struct fsd_system {
   double *d_ub = nullptr, *d_fb = nullptr, *d_lan = nullptr, *d_lc = nullptr, *d_u6 = nullptr;
   double *d_lh = nullptr, *d_lpart = nullptr;  // Lanczos coefficients and partial sums
   SpreadPlan* spread = nullptr;  // gather spreading (nullptr: atomic scatter)
+  bool spread_le = false;        // the lattice it was asked for (a side may have a plan on the cube alone)
   std::vector<double> h_tab, h_tab32;  // the smooth part's coefficients (RealPoly), before rounding to R
 
   // per-kernel-class event timing (fsd_set_timing)
@@ -767,9 +768,10 @@ void prepare_begin(fsd_system* s) {
     launch_set_value(s->d_gam, g, s->st);
   }
   s->rp.gam = s->wp.gam = s->le ? s->d_gam : nullptr;
-  if (spread_plan_sheared(s->spread) && !s->le) {  // the lattice was switched back to the cube
+  if (s->spread_le && !s->le) {  // the lattice was switched back to the cube
     spread_plan_destroy(s->spread);
     s->spread = spread_plan_create(s->nb, s->wp.n, s->wp.support, false);
+    s->spread_le = false;
   }
   launch_bead_positions(s->nb, s->na, s->d_body, s->d_xbody, s->d_com, s->d_quat, s->L, g, s->d_r4, s->d_pos4,
                         s->st);
@@ -1800,6 +1802,7 @@ fsd_status fsd_init_aggregates(fsd_system* s, int32_t n_agg, const int32_t* off,
     HIPCHK(hipHostMalloc((void**)&s->h_io, sizeof(double) * s->io_cap));
     s->h_flags[0] = s->h_flags[1] = 0;
     s->spread = spread_plan_create(nb, s->wp.n, s->wp.support, s->le);  // nullptr: scatter
+    s->spread_le = s->le;
     upload_tables(s);
     HIPCHK(hipMemcpy(s->d_offsets, off, sizeof(int) * (n_agg + 1), hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(s->d_body, body.data(), sizeof(int) * nb, hipMemcpyHostToDevice));
@@ -2729,7 +2732,7 @@ size_t system_bytes(const fsd_system* s) {
   fsd_params p = s->p;
   p.xi = s->wp.xi;
   p.grid = s->wp.n;
-  return fsd_estimate_bytes_on(&p, s->nb, s->na, s->L, s->le || spread_plan_sheared(s->spread));
+  return fsd_estimate_bytes_on(&p, s->nb, s->na, s->L, s->spread_le);
 }
 
 // One solve (and optionally an Euler step) for every admitted system.  Each system

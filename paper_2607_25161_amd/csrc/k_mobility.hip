@@ -695,8 +695,6 @@ SpreadPlan* spread_plan_create(int nb, int N, int P, bool sheared) {
   return sp;
 }
 
-bool spread_plan_sheared(const SpreadPlan* sp) { return sp && sp->sheared; }
-
 void spread_plan_destroy(SpreadPlan* sp) {
   if (!sp) return;
   (void)hipFree(sp->keys_in);
