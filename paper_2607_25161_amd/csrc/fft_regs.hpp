@@ -156,56 +156,6 @@ struct Dft<15> : DftPair<3, 5> {};
 template <>
 struct Dft<16> : DftPair<4, 4> {};
 
-// ---- sides with a two-step transform ----------------------------------------------------------
-// RA <= RB, both at most 16 (a thread's registers).  BL: lines of a z or y pass per workgroup in
-// FP32, dividing N^2, as many as 256 threads transform in one go (RB each); FP64 takes half.
-// GP: row pairs of an x+Green workgroup, 6 lines each (even sides).
-template <int N>
-struct Split;
-#define FSD_SPLIT(N_, A_, B_, L_, G_)                    \
-  template <>                                            \
-  struct Split<N_> {                                     \
-    static constexpr int RA = A_, RB = B_, BL = L_, GP = G_; \
-  };
-// the sides that are multiples of 8, as the grid rule takes them
-FSD_SPLIT(8, 2, 4, 64, 10)
-FSD_SPLIT(16, 4, 4, 64, 10)
-FSD_SPLIT(24, 4, 6, 32, 7)
-FSD_SPLIT(32, 4, 8, 32, 5)
-FSD_SPLIT(40, 5, 8, 32, 5)
-FSD_SPLIT(48, 6, 8, 32, 5)
-FSD_SPLIT(64, 8, 8, 32, 4)
-FSD_SPLIT(72, 8, 9, 24, 3)
-FSD_SPLIT(80, 8, 10, 16, 3)
-FSD_SPLIT(96, 8, 12, 16, 2)
-FSD_SPLIT(120, 10, 12, 16, 2)
-FSD_SPLIT(128, 8, 16, 16, 2)
-FSD_SPLIT(144, 12, 12, 16, 1)
-FSD_SPLIT(160, 10, 16, 16, 1)
-FSD_SPLIT(192, 12, 16, 16, 1)
-FSD_SPLIT(240, 15, 16, 16, 1)
-FSD_SPLIT(256, 16, 16, 16, 1)
-// further sides of the 3D transform on its own
-FSD_SPLIT(27, 3, 9, 27, 0)
-FSD_SPLIT(36, 6, 6, 36, 0)
-FSD_SPLIT(45, 5, 9, 25, 0)
-FSD_SPLIT(50, 5, 10, 25, 0)
-FSD_SPLIT(54, 6, 9, 27, 0)
-FSD_SPLIT(60, 6, 10, 24, 0)
-FSD_SPLIT(75, 5, 15, 15, 0)
-FSD_SPLIT(81, 9, 9, 27, 0)
-FSD_SPLIT(90, 9, 10, 20, 0)
-FSD_SPLIT(100, 10, 10, 25, 0)
-FSD_SPLIT(108, 9, 12, 16, 0)
-FSD_SPLIT(135, 9, 15, 15, 0)
-FSD_SPLIT(150, 10, 15, 15, 0)
-FSD_SPLIT(180, 12, 15, 16, 0)
-#undef FSD_SPLIT
-#define FSD_WAVE_SIDES(X) \
-  X(8) X(16) X(24) X(32) X(40) X(48) X(64) X(72) X(80) X(96) X(120) X(128) X(144) X(160) X(192) X(240) X(256)
-#define FSD_OTHER_SIDES(X) \
-  X(27) X(36) X(45) X(50) X(54) X(60) X(75) X(81) X(90) X(100) X(108) X(135) X(150) X(180)
-
 // Exchange in LDS: element e of a line at slot (e mod RA) PAD + e / RA, PAD >= RB odd.  The first
 // step's thread b writes e = b RA + r (slots r PAD + b: neighbours side by side), the second
 // step's reads e = b + r RA (slots b PAD + r: an odd stride) and, in place, may write its outputs
@@ -218,7 +168,7 @@ constexpr int kSlots = Split<N>::RA * kPad<N>;
 template <typename R, int N>
 struct LineTile {
   static constexpr int RA = Split<N>::RA, RB = Split<N>::RB;
-  static constexpr int B = (sizeof(R) == 8 && Split<N>::BL % 2 == 0) ? Split<N>::BL / 2 : Split<N>::BL;
+  static constexpr int B = split_lines<N>(sizeof(R));
   static constexpr int kThreads = (B * RB + 63) / 64 * 64;
   static constexpr size_t kBytes = 2 * sizeof(R) * (size_t(B) * kSlots<N> + N);
   static_assert(RA <= RB && N * N % B == 0 && kThreads <= 256 && kBytes <= 65536, "one pass of 256 threads");

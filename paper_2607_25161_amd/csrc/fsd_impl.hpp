@@ -10,6 +10,8 @@
 #include <tuple>
 #include <utility>
 
+#include "fft_tiles.hpp"
+
 namespace fsd {
 
 // ---- timed launches ---------------------------------------------------------------------
@@ -52,19 +54,6 @@ struct FftPlan {
   unsigned long long rcode;  // the radices again, 4 bits per stage (stage 0 lowest)
 };
 
-// LDS distance, in elements of elem_bytes, between the B lines that one workgroup of a z
-// or y pass transforms.  Loading B consecutive x of a grid row puts neighbouring lanes on
-// different lines, so with a stride of N (a multiple of the 64 banks' width for every even
-// N) they would all hit one bank.  A stride S with S / t odd, t = max(1, E / B) and E the
-// elements per bank row, sends the lanes of one LDS cycle to distinct banks.
-__host__ __device__ inline int fft_line_stride(int N, int B, int elem_bytes) {
-  if (B <= 1) return N;
-  const int E = 256 / elem_bytes, t = E / B > 1 ? E / B : 1;
-  int S = N;
-  while (S % (2 * t) != t) ++S;
-  return S;
-}
-
 // Constants of the wave-space (spectral Ewald) part of the mobility.
 struct WaveParams {
   int n;            // grid points per side
@@ -83,9 +72,7 @@ struct WaveParams {
   // the same multipliers rounded to FP32, 8 per entry: sinc, jv, the solve's and the
   // Brownian root's factors, 1/|k|, then 3 unused (16-byte aligned rows), or nullptr
   const float* gtab32;
-  // transform tiles (0: the two-step passes where the side has them, else the default rules
-  // fft_lines_b / fft_green_rows): lines per workgroup
-  // of the z and y passes, row pairs per workgroup of the x+Green pass
+  // transform tiles that the caller had measured (0: none; see line_tile and green_tile)
   int tile_b, tile_g;
 };
 
@@ -444,18 +431,6 @@ enum BatchKind {
 };
 
 // FFT blocking used by both the single-system and the multi-system launches
-int fft_lines_b(int N, int rbytes);  // lines per workgroup of the z/y passes (rbytes: 8 FP64, 4 FP32)
-int fft_green_rows(int N);           // row slots per workgroup of the x+Green pass
-// the tiles a system's transforms run with (its overrides, else the rules), and whether a
-// tile fits: B divides N, and the LDS of either pass stays within 64 KB
-int lines_b_of(const WaveParams& wp, int rbytes);
-int green_g_of(const WaveParams& wp);
-bool tile_b_fits(int N, int B, int rbytes);
-bool tile_g_fits(int N, int G, int rbytes);
-// whether the system's line passes and its x+Green pass are the two-step ones (a side that has
-// them and no tile of its own)
-bool two_step_lines_of(const WaveParams& wp);
-bool two_step_green_of(const WaveParams& wp);
 // fill the spreading fields of d from a gather plan (d.wp must be set first)
 void spread_plan_desc(const SpreadPlan* sp, BatchDesc& d);
 // per-system block counts of each kind and the dynamic LDS the kinds need (prec: 0 FP64, 1 FP32)

@@ -2367,7 +2367,7 @@ fsd_status fsd_autotune_tiles(fsd_system* s, int reps, int* lines_b, int* green_
     // the y pass stands for both line passes (same body, strides differ)
     s->wp.tile_b = s->wp.tile_g = 0;
     int best_b = 0;
-    double best = two_step_lines_of(s->wp) ? timed(FSD_TIMER_FFT_Y) : 1e300;
+    double best = line_tile(N, 0, rb).two_step ? timed(FSD_TIMER_FFT_Y) : 1e300;
     for (int B : {1, 2, 4, 8, 16, 32, 64}) {
       if (!tile_b_fits(N, B, rb)) continue;
       s->wp.tile_b = B;
@@ -2375,7 +2375,7 @@ fsd_status fsd_autotune_tiles(fsd_system* s, int reps, int* lines_b, int* green_
       if (ms < best) best = ms, best_b = B;
     }
     int best_g = 0;
-    best = two_step_green_of(s->wp) ? timed(FSD_TIMER_GREEN) : 1e300;
+    best = green_tile(N, 0, rb).two_step ? timed(FSD_TIMER_GREEN) : 1e300;
     for (int G : {1, 2, 3, 4, 6, 8}) {
       if (!tile_g_fits(N, G, rb)) continue;
       s->wp.tile_g = G;
@@ -2385,8 +2385,8 @@ fsd_status fsd_autotune_tiles(fsd_system* s, int reps, int* lines_b, int* green_
     s->wp.tile_b = best_b;
     s->wp.tile_g = best_g;
     s->drop_graphs();  // captured launches carry the old shapes
-    if (lines_b) *lines_b = lines_b_of(s->wp, rb);
-    if (green_g) *green_g = green_g_of(s->wp);
+    if (lines_b) *lines_b = line_tile(N, best_b, rb).size;
+    if (green_g) *green_g = green_tile(N, best_g, rb).size;
     return FSD_OK;
   });
 }
@@ -2827,8 +2827,9 @@ BatchDesc make_desc(fsd_system* s, int prec) {
   d.tw64 = s->d_tw64;
   d.tw32 = s->d_tw32;
   d.grid = s->d_grid;
-  d.bl = two_step_lines_of(s->wp) ? 0 : lines_b_of(s->wp, prec ? 4 : 8);
-  d.bg = two_step_green_of(s->wp) ? 0 : green_g_of(s->wp);
+  const FftTile lt = line_tile(d.wp.n, d.wp.tile_b, prec ? 4 : 8), gt = green_tile(d.wp.n, d.wp.tile_g, prec ? 4 : 8);
+  d.bl = lt.two_step ? 0 : lt.size;
+  d.bg = gt.two_step ? 0 : gt.size;
   spread_plan_desc(s->spread, d);
   d.lrow = lub ? s->d_lrow : nullptr;
   d.lcol = s->d_lcol;

@@ -530,15 +530,6 @@ __global__ __launch_bounds__(256) void k_fft_lines(R* __restrict__ grid, size_t 
 // TABLE: the cube, multipliers read from the table by |m|^2; otherwise (the sheared lattice)
 // computed per mode.  Two instantiations keep the per-mode FP64 arithmetic out of the
 // cube's register budget.
-// LDS of the x+Green pass with G row slots and complex values of tb bytes: two buffers of
-// 6 G lines (stride N | 1) and the twiddles, then (16-byte aligned) the 2 G row descriptors
-__host__ __device__ inline size_t xgreen_rows_offset(int N, int G, int tb) {
-  return (size_t(tb) * (12 * size_t(G) * (N | 1) + N) + 15) & ~size_t(15);
-}
-__host__ __device__ inline size_t xgreen_shm(int N, int G, int tb) {
-  return xgreen_rows_offset(N, G, tb) + 2 * size_t(G) * sizeof(int4);
-}
-
 template <typename R, bool TABLE>
 __device__ __forceinline__ void fft_xgreen_body(R* __restrict__ grid, size_t cs, FftPlan plan,
                                                 const R* __restrict__ twiddle, WaveParams wp, int G,
@@ -659,26 +650,6 @@ __global__ __launch_bounds__(256) void k_fft_xgreen(R* __restrict__ grid, size_t
   fft_xgreen_body<R, TABLE>(grid, cs, plan, twiddle, wp, G, skip, blockIdx.x, blockIdx.y, gridDim.x);
 }
 
-// row slots per workgroup of the x+Green pass (measured: 2 is fastest at 64^3 and 128^3)
-int fft_green_rows(int N) { return N >= 256 ? 1 : N >= 64 ? 2 : 256 / N; }
-
-bool tile_b_fits(int N, int B, int rbytes) {
-  return B >= 1 && (B & (B - 1)) == 0 && N % B == 0 &&
-         size_t(2 * rbytes) * (2 * size_t(B) * fft_line_stride(N, B, 2 * rbytes) + N) <= (size_t(64) << 10);
-}
-
-bool tile_g_fits(int N, int G, int rbytes) {
-  return G >= 1 && G <= 16 && xgreen_shm(N, G, 2 * rbytes) <= (size_t(64) << 10);
-}
-
-// lines per workgroup of the coalesced y/z passes: largest B in {16, 8, 4, 2, 1} dividing N
-// whose two LDS buffers and twiddles fit in 64 KB
-int fft_lines_b(int N, int rbytes) {
-  for (int B = 16; B > 1; B /= 2)
-    if (tile_b_fits(N, B, rbytes)) return B;
-  return 1;
-}
-
 // ------------------------------------------------------------------------------------------
 // Two-step passes of the sides in fft_regs.hpp.  What bounds a pass: the grid is read and written
 // once, and with every stage of a line in LDS (four or five exchanges, a barrier each, addresses
@@ -761,41 +732,7 @@ void launch_fft3d_two_step(double* grid, const double* twiddle, int sign, hipStr
   }
 }
 
-// lines per workgroup of the two-step line passes (0: the side has none)
-int two_step_lines(int N, int rbytes) {
-  switch (N) {
-#define X(N_) \
-  case N_: return rbytes == 4 ? LineTile<float, N_>::B : LineTile<double, N_>::B;
-    FSD_WAVE_SIDES(X)
-#undef X
-    default: return 0;
-  }
-}
-int two_step_pairs(int N) {
-  switch (N) {
-#define X(N_) \
-  case N_: return GreenTile<float, N_>::G;
-    FSD_WAVE_SIDES(X)
-#undef X
-    default: return 0;
-  }
-}
 }  // namespace
-
-int lines_b_of(const WaveParams& wp, int rbytes) {
-  if (wp.tile_b > 0 && tile_b_fits(wp.n, wp.tile_b, rbytes)) return wp.tile_b;
-  const int two = two_step_lines(wp.n, rbytes);
-  return two ? two : fft_lines_b(wp.n, rbytes);
-}
-
-int green_g_of(const WaveParams& wp) {
-  if (wp.tile_g > 0 && tile_g_fits(wp.n, wp.tile_g, 8)) return wp.tile_g;
-  const int two = two_step_pairs(wp.n);
-  return two ? two : fft_green_rows(wp.n);
-}
-
-bool two_step_lines_of(const WaveParams& wp) { return wp.tile_b == 0 && two_step_lines(wp.n, 8) > 0; }
-bool two_step_green_of(const WaveParams& wp) { return wp.tile_g == 0 && two_step_pairs(wp.n) > 0; }
 
 template <typename R>
 void launch_fft3d(R* grid, int ncomp, size_t comp_stride, const FftPlan& plan, const R* twiddle, int sign,
@@ -825,7 +762,8 @@ void launch_wave_fft(R* grid, const FftPlan& plan, const R* twiddle, const WaveP
   using T = typename C2<R>::T;
   const int N = plan.n;
   const size_t cs = 2 * size_t(N) * N * N;
-  if (stage == 2 ? two_step_green_of(wp) : two_step_lines_of(wp)) {
+  const FftTile tile = stage == 2 ? green_tile(N, wp.tile_g, sizeof(R)) : line_tile(N, wp.tile_b, sizeof(R));
+  if (tile.two_step) {
     switch (N) {
 #define X(N_) \
   case N_: launch_two_step<R, N_>(grid, twiddle, wp, stage, st, skip); return;
@@ -834,7 +772,7 @@ void launch_wave_fft(R* grid, const FftPlan& plan, const R* twiddle, const WaveP
     }
   }
   if (stage == 2) {
-    const int G = green_g_of(wp);
+    const int G = tile.size;
     const size_t shm = xgreen_shm(N, G, int(sizeof(T)));
     const int nblk = (N * N / 2 + 2 + G - 1) / G;
     if (wp.gtab && !wp.gam)  // the cube: tabulated multipliers
@@ -842,7 +780,7 @@ void launch_wave_fft(R* grid, const FftPlan& plan, const R* twiddle, const WaveP
     else
       launch_k(k_fft_xgreen<R, false>, nblk, kThreads, shm, st, grid, cs, plan, twiddle, wp, G, skip);
   } else {
-    const int B = lines_b_of(wp, sizeof(R));
+    const int B = tile.size;
     const size_t shm = sizeof(T) * (2 * size_t(B) * fft_line_stride(N, B, int(sizeof(T))) + N);
     dim3 g(N * N / B, 3);
     const int sign = stage < 2 ? -1 : +1;
