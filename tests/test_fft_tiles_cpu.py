@@ -44,8 +44,8 @@ def test_run_time_passes_get_tiles_they_can_run(tmp_path):
         if not l2:
             assert B & (B - 1) == 0 and N % B == 0 and lds <= 65536, (N, rb, t, B, lds)
         if not g2:
-            # a measured G keeps to 64 KB; the rule's two row pairs take up to 98 KB of a CU's 160 KB
-            assert 1 <= G <= 64 and gshm <= (65536 if G == t else 163840), (N, rb, t, G, gshm)
+            # the default of two row pairs takes up to 98 KB of a CU's 160 KB
+            assert 1 <= G <= 64 and gshm <= 163840, (N, rb, t, G, gshm)
         if t and not l2 and (t & (t - 1)) == 0 and N % t == 0 and B != t:
             # a measured tile gives way only where it does not fit
             assert 2 * rb * (2 * t * N + N) > 65536 - 2 * rb * 2 * t * 64, (N, rb, t, B)
