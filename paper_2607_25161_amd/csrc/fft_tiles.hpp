@@ -6,59 +6,85 @@
 namespace fsd {
 
 // ---- sides with a two-step transform ----------------------------------------------------------
-// RA <= RB, both at most 16 (a thread's registers).  BL: lines of a z or y pass per workgroup in
-// FP32, dividing N^2, as many as 256 threads transform in one go (RB each); FP64 takes half.
-// GP: row pairs of an x+Green workgroup, 6 lines each (even sides).
+// A side has one when it is a product of two factors RA <= RB <= 16 (a thread's registers) that have a
+// register transform: 2, 3, 4, 5, 6, 8, 9, 10, 12, 15, 16.  Of its products the most even one counts.
+// (125, 162, 200, 216, 243 and 250 have none and keep the run-time passes.)
+constexpr bool reg_factor(int f) {
+  return f == 2 || f == 3 || f == 4 || f == 5 || f == 6 || f == 8 || f == 9 || f == 10 || f == 12 || f == 15 || f == 16;
+}
+constexpr int split_low(int N) {  // RA, or 0
+  int best = 0;
+  for (int f = 2; f * f <= N; ++f)
+    if (N % f == 0 && reg_factor(f) && reg_factor(N / f)) best = f;
+  return best;
+}
+// lines of a z or y pass per workgroup: the most that divide N^2 and that 256 threads (RB a line) transform in
+// one go
+constexpr int split_most_lines(int N) {
+  int best = 1;
+  for (int b = 1; b * (N / split_low(N)) <= 256; ++b)
+    if (N * N % b == 0) best = b;
+  return best;
+}
+
+// BL: lines of a z or y pass per workgroup in FP32; FP64 takes half where that leaves an even number (side
+// 108, 18 lines: 35 us for the 3D transform, with 9 43).  GP: row pairs of an x+Green workgroup, 6 lines each.
 template <int N>
-struct Split;
-#define FSD_SPLIT(N_, A_, B_, L_, G_)                    \
-  template <>                                            \
-  struct Split<N_> {                                     \
-    static constexpr int RA = A_, RB = B_, BL = L_, GP = G_; \
+struct Split {  // transforms of their own only
+  static constexpr int RA = split_low(N), RB = N / RA, BL = split_most_lines(N), GP = 0;
+};
+#define FSD_SPLIT(N_, L_, G_)                                                             \
+  template <>                                                                             \
+  struct Split<N_> {                                                                      \
+    static constexpr int RA = split_low(N_), RB = N_ / RA, BL = L_, GP = G_;               \
   };
-// the sides that are multiples of 8, as the grid rule takes them
-FSD_SPLIT(8, 2, 4, 64, 10)
-FSD_SPLIT(16, 4, 4, 64, 10)
-FSD_SPLIT(24, 4, 6, 32, 7)
-FSD_SPLIT(32, 4, 8, 32, 5)
-FSD_SPLIT(40, 5, 8, 32, 5)
-FSD_SPLIT(48, 6, 8, 32, 5)
-FSD_SPLIT(64, 8, 8, 32, 4)
-FSD_SPLIT(72, 8, 9, 24, 3)
-FSD_SPLIT(80, 8, 10, 16, 3)
-FSD_SPLIT(96, 8, 12, 16, 2)
-FSD_SPLIT(120, 10, 12, 16, 2)
-FSD_SPLIT(128, 8, 16, 16, 2)
-FSD_SPLIT(144, 12, 12, 16, 1)
-FSD_SPLIT(160, 10, 16, 16, 1)
-FSD_SPLIT(192, 12, 16, 16, 1)
-FSD_SPLIT(240, 15, 16, 16, 1)
-FSD_SPLIT(256, 16, 16, 16, 1)
-// further sides of the 3D transform on its own
-FSD_SPLIT(27, 3, 9, 27, 0)
-FSD_SPLIT(36, 6, 6, 36, 0)
-FSD_SPLIT(45, 5, 9, 25, 0)
-FSD_SPLIT(50, 5, 10, 25, 0)
-FSD_SPLIT(54, 6, 9, 27, 0)
-FSD_SPLIT(60, 6, 10, 24, 0)
-FSD_SPLIT(75, 5, 15, 15, 0)
-FSD_SPLIT(81, 9, 9, 27, 0)
-FSD_SPLIT(90, 9, 10, 20, 0)
-FSD_SPLIT(100, 10, 10, 25, 0)
-FSD_SPLIT(108, 9, 12, 16, 0)
-FSD_SPLIT(135, 9, 15, 15, 0)
-FSD_SPLIT(150, 10, 15, 15, 0)
-FSD_SPLIT(180, 12, 15, 16, 0)
+// Sides of the wave-space passes: the multiples of 8, which the grid rule takes.  Their lines are powers of
+// two (24 on side 72), so that a run of lines is whole cache lines.
+FSD_SPLIT(8, 64, 10)
+FSD_SPLIT(16, 64, 10)
+FSD_SPLIT(24, 32, 7)
+FSD_SPLIT(32, 32, 5)
+FSD_SPLIT(40, 32, 5)
+FSD_SPLIT(48, 32, 5)
+FSD_SPLIT(64, 32, 4)
+FSD_SPLIT(72, 24, 3)
+FSD_SPLIT(80, 16, 3)
+FSD_SPLIT(96, 16, 2)
+FSD_SPLIT(120, 16, 2)
+FSD_SPLIT(128, 16, 2)
+FSD_SPLIT(144, 16, 1)
+FSD_SPLIT(160, 16, 1)
+FSD_SPLIT(192, 16, 1)
+FSD_SPLIT(240, 16, 1)
+FSD_SPLIT(256, 16, 1)
 #undef FSD_SPLIT
 #define FSD_WAVE_SIDES(X) \
   X(8) X(16) X(24) X(32) X(40) X(48) X(64) X(72) X(80) X(96) X(120) X(128) X(144) X(160) X(192) X(240) X(256)
-#define FSD_OTHER_SIDES(X) \
-  X(27) X(36) X(45) X(50) X(54) X(60) X(75) X(81) X(90) X(100) X(108) X(135) X(150) X(180)
+#define FSD_OTHER_SIDES(X)                                                                                      \
+  X(4) X(6) X(9) X(10) X(12) X(15) X(18) X(20) X(25) X(27) X(30) X(36) X(45) X(50) X(54) X(60) X(75) X(81) X(90) \
+  X(100) X(108) X(135) X(150) X(180) X(225)
+// the two lists hold every side that splits
+constexpr bool is_listed(int N) {
+  switch (N) {
+#define X(N_) case N_:
+    FSD_WAVE_SIDES(X)
+    FSD_OTHER_SIDES(X)
+#undef X
+    return true;
+  }
+  return false;
+}
+constexpr bool all_listed() {
+  for (int N = 1; N <= 512; ++N)
+    if ((split_low(N) > 0) != is_listed(N)) return false;
+  return true;
+}
+static_assert(all_listed(), "a side of the rule is missing, or one too many");
 
 // lines of a z or y pass per workgroup, values of rbytes
 template <int N>
 constexpr int split_lines(size_t rbytes) {
-  return rbytes == 8 && Split<N>::BL % 2 == 0 ? Split<N>::BL / 2 : Split<N>::BL;
+  return rbytes == 8 && Split<N>::BL % 4 == 0 ? Split<N>::BL / 2 : Split<N>::BL;
 }
 
 // of a two-step wave-space pass: lines (0: the side has none), row pairs of x+Green
