@@ -15,30 +15,32 @@
 namespace fsd {
 
 // ---- timed launches ---------------------------------------------------------------------
-// A timed call site arms a start/stop event pair; the next kernel launched through
-// launch_k takes it, and hipExtLaunchKernel stamps the pair at that kernel's own start
-// and end (events recorded around a launch would also count their marker packets).
+// A timed call site arms start/stop event pairs; the kernels launched through launch_k take one
+// each (a class has up to kTimedLaunches of them), and hipExtLaunchKernel stamps a pair at its
+// kernel's own start and end (events recorded around a launch would also count their marker packets).
+constexpr int kTimedLaunches = 2;
 struct LaunchEvents {
-  hipEvent_t a = nullptr, b = nullptr;
-  bool used = false;
+  hipEvent_t a[kTimedLaunches] = {}, b[kTimedLaunches] = {};
+  int used = 0;
   hipError_t status = hipSuccess;
 };
 extern thread_local LaunchEvents g_launch_events;
 
 template <typename F, typename T, size_t... I>
-hipError_t launch_ext(F k, dim3 grid, dim3 block, uint32_t shm, hipStream_t st, const LaunchEvents& e, T& args,
+hipError_t launch_ext(F k, dim3 grid, dim3 block, uint32_t shm, hipStream_t st, hipEvent_t ea, hipEvent_t eb, T& args,
                       std::index_sequence<I...>) {
   void* ptrs[] = {static_cast<void*>(&std::get<I>(args))...};
-  return hipExtLaunchKernel(reinterpret_cast<const void*>(k), grid, block, ptrs, shm, st, e.a, e.b, 0);
+  return hipExtLaunchKernel(reinterpret_cast<const void*>(k), grid, block, ptrs, shm, st, ea, eb, 0);
 }
 
 template <typename... P, typename... A>
 inline void launch_k(void (*k)(P...), dim3 grid, dim3 block, uint32_t shm, hipStream_t st, A... a) {
   LaunchEvents& e = g_launch_events;
-  if (e.a && !e.used) {
-    e.used = true;
+  if (e.used < kTimedLaunches && e.a[e.used]) {
     std::tuple<P...> args{static_cast<P>(a)...};
-    e.status = launch_ext(k, grid, block, shm, st, e, args, std::index_sequence_for<P...>{});
+    const hipError_t r = launch_ext(k, grid, block, shm, st, e.a[e.used], e.b[e.used], args, std::index_sequence_for<P...>{});
+    if (e.status == hipSuccess) e.status = r;
+    ++e.used;
   } else {
     k<<<grid, block, shm, st>>>(static_cast<P>(a)...);
   }

@@ -347,7 +347,7 @@ struct fsd_system {
 
   // per-kernel-class event timing (fsd_set_timing)
   struct Pending {
-    int cls;
+    int cls, launches;  // 0 launches: a further kernel of the launch before
     double bytes;
     hipEvent_t a, b;
   };
@@ -518,7 +518,7 @@ void harvest_timers(fsd_system* s) {
     float ms = 0;
     HIPCHK(hipEventElapsedTime(&ms, p.a, p.b));
     s->t_ms[p.cls] += ms;
-    s->t_n[p.cls] += 1;
+    s->t_n[p.cls] += p.launches;
     s->t_bytes[p.cls] += p.bytes;
   }
   s->pending.clear();
@@ -527,19 +527,15 @@ void harvest_timers(fsd_system* s) {
 
 hipEvent_t next_event(fsd_system* s) {
   if (s->ev_next == s->ev_pool.size()) {
-    if (s->ev_pool.size() < 4096) {
-      hipEvent_t e;
-      HIPCHK(hipEventCreate(&e));
-      s->ev_pool.push_back(e);
-    } else {
-      harvest_timers(s);
-    }
+    hipEvent_t e;
+    HIPCHK(hipEventCreate(&e));
+    s->ev_pool.push_back(e);
   }
   return s->ev_pool[s->ev_next++];
 }
 
-// Start/stop events of one eager kernel launch when timing is on (stamped by the launch
-// itself, see launch_k), with the launch's algorithmic HBM bytes (the minimum traffic of
+// Start/stop events of the kernels of one eager launch when timing is on (stamped by the launches
+// themselves, see launch_k), with the launch's algorithmic HBM bytes (the minimum traffic of
 // its inputs and outputs).  Launches that take no events (none made, or made inside a
 // capture) record nothing.  (This runtime cannot time kernels inside captured graphs,
 // so timed runs launch eagerly; see run_body.)
@@ -547,19 +543,25 @@ struct Timed {
   fsd_system* s;
   int cls;
   double bytes;
-  hipEvent_t a = nullptr, b = nullptr;
+  bool armed = false;
   Timed(fsd_system* s_, int c, double by) : s(s_), cls(c), bytes(by) {
     if (!s->timing || s->capturing) return;
-    a = next_event(s);
-    b = next_event(s);
-    g_launch_events = LaunchEvents{a, b, false, hipSuccess};
+    if (s->ev_next + 2 * kTimedLaunches > 4096) harvest_timers(s);
+    LaunchEvents e;
+    for (int k = 0; k < kTimedLaunches; ++k) {
+      e.a[k] = next_event(s);
+      e.b[k] = next_event(s);
+    }
+    g_launch_events = e;
+    armed = true;
   }
   ~Timed() noexcept(false) {
-    if (!a) return;
+    if (!armed) return;
     const LaunchEvents e = g_launch_events;
     g_launch_events = LaunchEvents{};
+    s->ev_next -= 2 * size_t(kTimedLaunches - e.used);
     HIPCHK(e.status);
-    if (e.used) s->pending.push_back({cls, bytes, a, b});
+    for (int k = 0; k < e.used; ++k) s->pending.push_back({cls, k == 0, k == 0 ? bytes : 0.0, e.a[k], e.b[k]});
   }
 };
 
