@@ -437,7 +437,6 @@ enum BatchKind {
 void spread_plan_desc(const SpreadPlan* sp, BatchDesc& d);
 // per-system block counts of each kind and the dynamic LDS the kinds need (prec: 0 FP64, 1 FP32)
 int batch_blocks(const BatchDesc& d, int kind, int prec);
-bool interp_by_blocks(int nb, int prec);  // multi-system launches: nb of all systems
 int batch_fft_blocks(const BatchDesc& d, int kind, int prec);
 size_t batch_fft_shm(const BatchDesc& d, int kind, int prec);
 size_t batch_shm(const BatchDesc& d, int kind, int prec);

@@ -18,6 +18,7 @@
 
 #include "fsd.h"
 #include "fsd_impl.hpp"
+#include "interp_choice.hpp"
 #include "tridiag.hpp"
 
 using namespace fsd;
@@ -2913,9 +2914,9 @@ void set_tables(fsd_batch* b, const std::vector<fsd_system*>& cyc, int prec) {
     while (first < ns && held + 0.5 * grid_bytes_of(desc[first], prec) <= per_group);
     g.ns = first - g.first;
     g.off = off.size();
-    int beads = 0;
-    for (int k = g.first; k < first; ++k) beads += desc[k].nb;
-    for (int k = g.first; k < first; ++k) desc[k].by_blocks = interp_by_blocks(beads, prec);
+    InterpChoice choice(false, prec ? 4 : 8);
+    for (int k = g.first; k < first; ++k) choice.add(desc[k].nb, desc[k].wp.n, desc[k].wp.support);
+    for (int k = g.first; k < first; ++k) desc[k].by_blocks = choice.by_blocks();
     for (int kind = 0; kind < BK_COUNT; ++kind) {
       int acc = 0;
       for (int k = g.first; k < first; ++k) {

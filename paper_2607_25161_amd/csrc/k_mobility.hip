@@ -13,6 +13,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "interp_choice.hpp"
 #include "k_common.hpp"
 #include "k_rigid.hpp"
 
@@ -1053,21 +1054,10 @@ __device__ __forceinline__ Acc64 mma4(double a, double b, Acc64 c) {
 __device__ __forceinline__ Acc32 mma4(float a, float b, Acc32 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
-// Up to here four wavefronts share a bead in interpolation: 32 beads at P = 14 take 5.3 us instead of
-// 11.8, 2,048 at P = 11 11.4 instead of 9.7 (FP64)
+// Up to here four wavefronts share a bead in interpolation by beads.  One wavefront / four, in us, FP64 and P = 10,
+// 14, 21: 128 beads 5.9 / 4.1, 9.7 / 5.4, 18.8 / 8.3; 512 beads 5.9 / 5.1, 9.9 / 7.3, 20.2 / 14.2; 800 beads 6.2 / 6.3,
+// 10.7 / 10.3, 21.1 / 22.8 (at P = 5 and 8 equal throughout; FP32 meets at 640 to 800 as well)
 constexpr int kShareBeads = 512;
-// Interpolation by blocks (k_interp_tile) or by beads (k_interp_plan), in us, random beads, P = 14:
-//   beads / grid       3000 / 64   4096 / 64   4096 / 128   8192 / 64   16384 / 64   16384 / 96
-//   FP64, cube        22.8, 29.2  27.4, 36.7   36.2, 81.5  42.0, 63.3   71.4, 119    64.9, 125
-//   FP32, cube        18.5, 17.5  21.4, 22.2   27.5, 37.1  30.7, 39.5   50.3, 73.4   41.8, 78.8
-//   FP64, sheared     32.3, 29.2  39.1, 37.9   42.2, 84.2  60.6, 63.9    103, 120    93.0, 125
-//   FP32, sheared     26.2, 17.2  31.2, 21.7   32.8, 37.4  49.5, 38.6   82.7, 74.9   60.5, 78.2
-// A sheared block stages the 64 weights of a plane per candidate, which in FP32 pays only where a
-// block has few of them.  A batch counts the beads of a launch.
-bool interp_by_blocks(int nb, int N, bool sheared, int bytes) {
-  if (!sheared) return nb >= 4096;
-  return nb >= 8192 && (bytes == 8 || double(N) * N * N >= 50.0 * nb);
-}
 template <typename R>
 struct AccOf {
   using T = Acc64;
@@ -1537,7 +1527,7 @@ __global__ __launch_bounds__(256) void k_interp_plan(int nb, BeadArgs<R> ba, con
   interp_plan_body<R, SHEAR, WPB>(nb, ba, grid, cs, wp, out, skip, body, r4, V, blockIdx.x, gridDim.x);
 }
 
-// Interpolation of large systems, the spreading product turned round: a wavefront holds its two rows
+// Interpolation by blocks (see interp_choice.hpp), the spreading product turned round: a wavefront holds its two rows
 // of the block (16 points of a plane, 8 planes, 6 components) in registers as the A operand, each
 // grid value read once, and takes the candidates that reach them 16 at a time,
 //   T(z, c; b) = sum over (x, y) of G(z, c; x, y) A_b(x, y),
@@ -1718,7 +1708,13 @@ void launch_interp(int nb, const double* pos4, const R* grid, const WaveParams& 
     launch_k(k_interp<R>, nblocks(nb, 4), kThreads, 0, st, nb, (const double4*)pos4, grid, cs, wp, out, skip, body, r, V);
     return;
   }
-  if (sp->BS == 8 && interp_by_blocks(nb, wp.n, sp->sheared, sizeof(R))) {
+  bool by_blocks = false;
+  if (sp->BS == 8 && nb > kShareBeads) {
+    InterpChoice choice(sp->sheared, sizeof(R));
+    choice.add(nb, wp.n, wp.support);
+    by_blocks = choice.by_blocks();
+  }
+  if (by_blocks) {
     const int nblk = sp->nbin * sp->nbin * sp->nbin;
     R* part = static_cast<R*>(sp->scratch);
     if (sp->sheared)
@@ -1825,8 +1821,6 @@ void spread_plan_desc(const SpreadPlan* sp, BatchDesc& d) {
   d.where = ok ? sp->where : nullptr;
   d.places = ok ? sp->scratch : nullptr;
 }
-
-bool interp_by_blocks(int nb, int prec) { return interp_by_blocks(nb, 0, false, prec ? 4 : 8); }
 
 int batch_blocks(const BatchDesc& d, int kind, int prec) {
   switch (kind) {
