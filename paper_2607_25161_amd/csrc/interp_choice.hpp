@@ -10,7 +10,7 @@
 //
 // The constants are least-squares fits of the relative error to 468 measured pairs (1,000 to 40,000 random beads,
 // grids 16 to 128, P = 6 to 21, both lattices (strain 0.3) and precisions).  The rule's choice is the quicker one
-// or within 5% of it in all but 12 of them, at worst 1.28 times it.
+// or within 5% of it in all but 15 of them, at worst 1.28 times it.
 #pragma once
 #include <algorithm>
 #include <cmath>
