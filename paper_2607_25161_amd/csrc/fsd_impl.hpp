@@ -159,7 +159,7 @@ void launch_real_sum(int nb, const double* pos4, const double* lam, const int* r
 template <typename R>
 void launch_spread(int nb, const double* pos4, const double* lam, const WaveParams& wp, R* grid,
                    hipStream_t st, const int* skip = nullptr);
-// Spreading and interpolation on a sheared lattice (wp.gam) without a plan (no 8^3 blocks): grid point
+// Spreading and interpolation on a sheared lattice (wp.gam) without a plan: grid point
 // (i, j, k) sits at sheared coordinates (i, j, k) h, and each grid row j takes the P x-points
 // around its own centre p_x - gam (j h - p_y).  Spreading scatters with atomic adds into a
 // zeroed grid; interpolation adds into out as launch_interp does (with V: + Sigma^T V).
@@ -187,7 +187,7 @@ void launch_wave_fft(R* grid, const FftPlan& plan, const R* twiddle, const WaveP
                      hipStream_t st, const int* skip = nullptr);
 // Gaussian spreading as a gather over beads binned by grid block (no atomics).
 struct SpreadPlan;
-// nullptr if n_grid has no blocks: not a multiple of 4, or of 8 on a sheared lattice
+// nullptr if n_grid has no blocks (not a multiple of 4, or of 8 on a sheared lattice) or too few of them
 SpreadPlan* spread_plan_create(int nb, int n_grid, int support, bool sheared);
 size_t spread_plan_bytes(int nb, int n_grid, int support, bool sheared);  // device bytes it takes
 void spread_plan_destroy(SpreadPlan* sp);

@@ -641,7 +641,12 @@ size_t spread_plan_bytes(int nb, int N, int P, bool sheared) {
 SpreadPlan* spread_plan_create(int nb, int N, int P, bool sheared) {
   const PlanShape h = plan_shape(N, P, sheared);
   const int BS = h.BS;
-  if (BS == 0) return nullptr;
+  // On a sheared lattice the eight blocks of side 16 (and the one of side 8) gather thousands of beads one
+  // after the other; below 11 points a support the scatter is quicker then.  Sheared 16^3, us by gather / scatter,
+  // P = 6: 4,096 beads 194 / 93 (FP32 175 / 79), 16,384 891 / 361; P = 10: 1,000 beads 88 / 106 (79 / 89), 4,096 356 /
+  // 362 (313 / 268), 16,384 1,624 / 1,458 (1,483 / 1,052); P = 14: 4,096 409 / 893.  Side 24: gather, by 1.4 at least.
+  const bool scatter = sheared && N <= 16 && ((P <= 9 && nb >= 512) || (P == 10 && nb >= 2048));
+  if (BS == 0 || scatter) return nullptr;
   auto* sp = new SpreadPlan;
   sp->nb = nb;
   sp->BS = BS;
