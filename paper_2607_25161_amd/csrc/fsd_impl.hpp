@@ -11,6 +11,7 @@
 #include <utility>
 
 #include "fft_tiles.hpp"
+#include "real_poly.hpp"
 
 namespace fsd {
 
@@ -78,30 +79,12 @@ struct WaveParams {
   int tile_b, tile_g;
 };
 
-// The smooth part of the real-space functions as piecewise polynomials on kIntervals equal
-// intervals of [0, r_cut]: five functions of kCoef coefficients each (highest power first, in the
-// offset from the interval's centre over its width), rows kStride values apart (an odd multiple
-// of 16 bytes).  The functions, all even in r: tt I, tt rr / r^2, rr I, rr rr / r^2, rt / r.
-// Their error, in units of the self mobilities, is at most 4e-14 in FP64 and 2e-9 in FP32 for
-// cutoff rules from 1e-5 to 1e-8 (checked against the quadrature in the tests).
-template <typename R>
-struct RealPoly;
-template <>
-struct RealPoly<double> {
-  static constexpr int kIntervals = 64, kCoef = 7, kStride = 38;
-  static constexpr size_t kBytes = sizeof(double) * kIntervals * kStride;
-};
-template <>
-struct RealPoly<float> {
-  static constexpr int kIntervals = 128, kCoef = 4, kStride = 20;
-  static constexpr size_t kBytes = sizeof(float) * kIntervals * kStride;
-};
-
 // Constants of the real-space part.
 struct RealParams {
   double L, a, eta;
   double r_cut;
   double inv_w;     // 1 / r_cut: a distance in units of the range the smooth part covers
+  int fine;         // intervals of the smooth part, in units of RealPoly::kIntervals
   double self_t, self_r;
   const double* gam;  // device scalar: strain of the sheared lattice (nullptr: the cube)
 };

@@ -77,15 +77,15 @@ struct SpreadPlan {
 // ------------------------------------------------------------------------------------------
 
 // The smooth part of a pair, five scalars as piecewise polynomials of the distance (RealPoly):
-// interval q = int(r inv_w), x = r inv_w - q - 1/2, Horner from the highest coefficient.  T points
+// interval q = int(r inv_w) (the last one at most), x = r inv_w - q - 1/2, Horner from the highest coefficient.  T points
 // at the coefficients in LDS, read in 16-byte pieces; rows are an odd number of pieces apart, so
 // that lanes at different distances meet different banks (an even number, 18, left FP64 half of
 // the banks: 163 us instead of 154 at 81,920 beads).
 template <typename R>
-__device__ __forceinline__ void smooth_part(const R* T, R r, R inv_w, R (&f)[5]) {
+__device__ __forceinline__ void smooth_part(const R* T, R r, R inv_w, int last, R (&f)[5]) {
   using P = RealPoly<R>;
   const R u = r * inv_w;
-  const int q = min(int(u), P::kIntervals - 1);  // r < r_cut up to rounding
+  const int q = min(int(u), last);  // r < r_cut up to rounding
   const R x = u - R(q) - R(0.5);
   typedef R V __attribute__((ext_vector_type(16 / sizeof(R))));
   constexpr int L = 16 / sizeof(R);
@@ -109,7 +109,7 @@ __device__ __forceinline__ void smooth_part(const R* T, R r, R inv_w, R (&f)[5])
 // 12 of the 17 loads of a pair: at 15.5 million pairs (81,920 beads) 367 us in FP64 and 230 in
 // FP32, the rate at which a CU looks up cache lines.  As 64 intervals of degree 6 (FP64) or 128
 // of degree 3 (FP32) it is 18 or 10 KB that every workgroup copies to LDS, and is closer to the
-// quadrature than the table was (4e-14 of the self mobility against 1e-13): with 32 lanes a row 140 us in FP64
+// quadrature than the table was (2e-15 of the self mobility against 3e-14): with 32 lanes a row 140 us in FP64
 // (with four wavefronts a SIMD; 154 with the three that its registers would leave) and 112 in FP32,
 // with 16 132 and 108.  A workgroup takes a contiguous chunk of rows, in the plan's spatial order
 // where there is one, so that the copy is paid once per many rows.
@@ -126,8 +126,9 @@ __device__ __forceinline__ void real_sum_body(int nb, const double4* __restrict_
   {
     typedef R V __attribute__((ext_vector_type(16 / sizeof(R))));
     constexpr int NV = P::kIntervals * P::kStride * int(sizeof(R)) / 16;
-    for (int k = threadIdx.x; k < NV; k += kThreads)
-      reinterpret_cast<V*>(T)[k] = reinterpret_cast<const V*>(tab)[k];
+    for (int h = 0; h < rp.fine; ++h)  // NV at a time: a constant count keeps all the loads in flight
+      for (int k = threadIdx.x; k < NV; k += kThreads)
+        reinterpret_cast<V*>(T)[h * NV + k] = reinterpret_cast<const V*>(tab)[h * NV + k];
   }
   __syncthreads();
   constexpr int kGroups = kThreads / LPR;
@@ -137,7 +138,8 @@ __device__ __forceinline__ void real_sum_body(int nb, const double4* __restrict_
   const int r_end = min(nb, (lb + 1) * chunk), lane = threadIdx.x % LPR;
   const R a = R(rp.a), a2 = a * a;
   const R c8 = R(1.0 / (8.0 * M_PI * rp.eta));
-  const R inv_w = R(rp.inv_w) * R(P::kIntervals);
+  const int last = rp.fine * P::kIntervals - 1;
+  const R inv_w = R(rp.inv_w) * R(rp.fine * P::kIntervals);
   const R touch = R(4) * a2;
   const double gam = rp.gam ? *rp.gam : 0.0;
   for (int rl = lb * chunk + int(threadIdx.x) / LPR; rl < r_end; rl += kGroups) {
@@ -175,7 +177,7 @@ __device__ __forceinline__ void real_sum_body(int nb, const double4* __restrict_
         cc = -R(0.5) * mr * (R(1) - R(3.0 / 8.0) * s);
       }
       R f[5];
-      smooth_part<R>(T, r, inv_w, f);
+      smooth_part<R>(T, r, inv_w, last, f);
       tI -= f[0];
       tB -= f[1];
       rI -= f[2];
@@ -249,7 +251,7 @@ void launch_real_sum(int nb, const double* pos4, const double* lam, const int* r
   const int acc = accumulate ? 1 : 0;
   const double4* p = (const double4*)pos4;
 #define FSD_REAL(L_)                                                                                    \
-  launch_k(k_real_sum<R, L_>, real_blocks(nb, L_), kThreads, RealPoly<R>::kBytes, st, nb, p, lam, rowptr, col, table, rp, out, acc, order, skip)
+  launch_k(k_real_sum<R, L_>, real_blocks(nb, L_), kThreads, RealPoly<R>::bytes(rp.fine), st, nb, p, lam, rowptr, col, table, rp, out, acc, order, skip)
   switch (lpr) {
     case 1: FSD_REAL(1); break;
     case 2: FSD_REAL(2); break;
@@ -1320,7 +1322,7 @@ void launch_spread_fused(const SpreadPlan* sp, const double* lam, const WavePara
   const size_t cs = 2 * size_t(wp.n) * wp.n * wp.n;
   const int nblk = sp->nbin * sp->nbin * sp->nbin;
   const size_t shm = std::max(sp->sheared ? SpreadTile<R, true>::kBytes : SpreadTile<R, false>::kBytes,
-                              RealPoly<R>::kBytes);
+                              RealPoly<R>::bytes(ra.rp.fine));
   auto pad8 = [](long long n) { return int((n + 7) / 8 * 8); };
   const int na_blk = pad8((ga.na + 3) / 4), nr_blk = pad8(real_blocks(ra.nb, lpr));
   const int total = na_blk + nr_blk + nblk;
@@ -1854,7 +1856,7 @@ int batch_blocks(const BatchDesc& d, int kind, int prec) {
 size_t batch_shm(const BatchDesc& d, int kind, int prec) {
   switch (kind) {
     case BK_REAL:
-      return prec ? RealPoly<float>::kBytes : RealPoly<double>::kBytes;
+      return prec ? RealPoly<float>::bytes(d.rp.fine) : RealPoly<double>::bytes(d.rp.fine);
     case BK_SPREAD:
       return prec ? SpreadTile<float, false>::kBytes : SpreadTile<double, false>::kBytes;
     case BK_INTERP:
