@@ -2581,7 +2581,9 @@ struct fsd_batch {
   const BatchDesc* desc_of(const Group& g) const { return d_desc + g.first; }
   const int* off_of(const Group& g, int kind) const { return d_off + g.off + size_t(kind) * (g.ns + 1); }
   std::vector<fsd_system*> cyc;  // the systems of the tables, in table order
-  std::vector<char> active;      // cyc[k] still iterating in the current cycle (timing only)
+  // cyc[k] still iterating in the current cycle, by the stop flags of its last segment: a group without such a
+  // system is launched no more until the cycle ends, and timed launches count the bytes of these systems
+  std::vector<char> active;
   // LDS per workgroup allowed to the z/y line passes and to the x+Green pass (0: no cap).
   // A multi-system launch reserves the largest system's LDS for every workgroup, so one
   // system's wide tile lowers the occupancy of all; fsd_batch_autotune_tiles measures these.
