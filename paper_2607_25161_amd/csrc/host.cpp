@@ -2818,6 +2818,7 @@ void set_tables(fsd_batch* b, const std::vector<fsd_system*>& cyc, int prec) {
                     std::memcmp(desc.data(), b->h_desc.data(), sizeof(BatchDesc) * ns) == 0;
   if (same) return;
   ++b->table_version;  // captured segments hold the old block counts and LDS sizes
+  b->nsys = 0;         // no tables until these are uploaded: a failure below must not leave the old ones as current
   if (ns > b->cap) {
     if (b->d_desc) HIPCHK(hipFree(b->d_desc));
     b->d_desc = nullptr;
