@@ -3,30 +3,9 @@
 // in each of RA threads.
 #pragma once
 #include "k_common.hpp"
+#include "turn_consts.hpp"
 
 namespace fsd {
-
-// ---- compile-time trigonometry -------------------------------------------------------------
-// cos(2 pi m / n) for 0 <= m / n, folded to the first eighth of the circle and summed as a series
-constexpr double series_cos(double x) {
-  double t = 1.0, s = 1.0;
-  for (int k = 1; k < 12; ++k) s += t *= -x * x / ((2 * k - 1) * (2 * k));
-  return s;
-}
-constexpr double series_sin(double x) {
-  double t = x, s = x;
-  for (int k = 1; k < 12; ++k) s += t *= -x * x / ((2 * k) * (2 * k + 1));
-  return s;
-}
-constexpr double kTwoPi = 6.28318530717958647692;
-constexpr double cos_turn(long m, long n) {
-  m %= n;
-  if (2 * m > n) m = n - m;                                    // cos(2 pi - t) = cos t
-  if (4 * m > n) return -cos_turn(n - 2 * m, 2 * n);           // cos t = -cos(pi - t)
-  if (8 * m > n) return series_sin(kTwoPi * (n - 4 * m) / (4.0 * n));  // cos t = sin(pi / 2 - t)
-  return series_cos(kTwoPi * m / double(n));
-}
-constexpr double sin_turn(long m, long n) { return cos_turn(4 * m + 3 * n, 4 * n); }  // sin t = cos(t - pi / 2)
 
 template <int I, int N, typename Fn>
 __device__ __forceinline__ void unroll_for(Fn&& f) {
@@ -141,18 +120,49 @@ struct DftPair {
     });
   }
 };
+// N = A B without a common factor: no twiddles between the two steps when the input is taken in the order
+// B n1 + A n2 and the output, k mod A and k mod B, is put together by the remainders (Good's mapping).  With it
+// and the nearest constants the rms error of a 3D transform is 2.4, 3.2, 2.9, 3.0 and 3.4e-16 on sides 24, 36, 48,
+// 96 and 144, with twiddles between the steps and constants summed in FP64 2.8, 4.3, 3.7, 3.9 and 4.4e-16; times
+// are the same but for x+Green on sides 192 (FP64 137 -> 145 us) and 240 (FP32 181 -> 185).
+constexpr int inverse_mod(int a, int m) {
+  for (int x = 1; x < m; ++x)
+    if (a * x % m == 1) return x;
+  return 0;
+}
+template <int A, int B>
+struct DftCoprime {
+  template <typename T>
+  static __device__ __forceinline__ void run(T (&v)[A * B]) {
+    constexpr int N = A * B, ea = B * inverse_mod(B % A, A), eb = A * inverse_mod(A % B, B);
+    T w[B][A];
+    unroll_for<0, B>([&](auto n2) {
+#pragma unroll
+      for (int n1 = 0; n1 < A; ++n1) w[n2][n1] = v[(B * n1 + A * n2) % N];
+      Dft<A>::run(w[n2]);
+    });
+    unroll_for<0, A>([&](auto k1) {
+      T u[B];
+#pragma unroll
+      for (int n2 = 0; n2 < B; ++n2) u[n2] = w[n2][k1];
+      Dft<B>::run(u);
+#pragma unroll
+      for (int k2 = 0; k2 < B; ++k2) v[(ea * k1 + eb * k2) % N] = u[k2];
+    });
+  }
+};
 template <>
-struct Dft<6> : DftPair<2, 3> {};
+struct Dft<6> : DftCoprime<2, 3> {};
 template <>
 struct Dft<8> : DftPair<2, 4> {};
 template <>
 struct Dft<9> : DftPair<3, 3> {};
 template <>
-struct Dft<10> : DftPair<2, 5> {};
+struct Dft<10> : DftCoprime<2, 5> {};
 template <>
-struct Dft<12> : DftPair<3, 4> {};
+struct Dft<12> : DftCoprime<3, 4> {};
 template <>
-struct Dft<15> : DftPair<3, 5> {};
+struct Dft<15> : DftCoprime<5, 3> {};
 template <>
 struct Dft<16> : DftPair<4, 4> {};
 

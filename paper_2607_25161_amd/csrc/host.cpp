@@ -698,7 +698,9 @@ void prepare_end(fsd_system* s) {
   const double avg = s->nb ? double(s->nnz) / s->nb : 0.0;
   // Lanes a row for six passes; fewer lanes where there are rows enough for the chip (81,920 beads,
   // 16 lanes instead of 32: first launch 232 -> 224 us, FP32 162 -> 159), about one pass where there
-  // are few (32 beads, 32 lanes instead of 8: 6.6 -> 4.7 us)
+  // are few (32 beads, 32 lanes instead of 8: 6.6 -> 4.7 us).  At the lines, FP64, cutoffs of 4, 8 and 11 a: 512 and
+  // 513 beads 7.5 and 8.9, 5.7 and 7.0, 6.4 and 7.0 us; 16,000 and 16,400 beads 111 and 113, 48 and 47, 56 and 54 us (the
+  // pair sum in a launch of its own 7 and 10, 14 and 16, 27 and 27).
   const double passes = s->nb >= 16384 ? 12.0 : s->nb <= 512 ? 1.5 : 6.0;
   int l = 1;
   while (l < 64 && l * passes < avg) l *= 2;
