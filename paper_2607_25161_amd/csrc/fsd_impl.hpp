@@ -83,7 +83,7 @@ struct WaveParams {
 struct RealParams {
   double L, a, eta;
   double r_cut;
-  double inv_w;     // 1 / r_cut: a distance in units of the range the smooth part covers
+  double inv_w;     // poly_inverse_range: a distance in units of the range the smooth part covers
   int fine;         // intervals of the smooth part, in units of RealPoly::kIntervals
   double self_t, self_r;
   const double* gam;  // device scalar: strain of the sheared lattice (nullptr: the cube)

@@ -554,13 +554,15 @@ void choose_parameters(fsd_system* s) {
   const double reach = rcut * (s->le ? std::sqrt(1.25) : 1.0);
   if (reach >= 3.0 * L) throw ApiError(FSD_EINVAL, "real-space cutoff exceeds three box lengths; raise xi");
   r.r_cut = rcut;
-  r.inv_w = 1.0 / rcut;
-  SmoothPart sp(a, p.eta, xi, rcut);
+  // the polynomials cover a little more than the cutoff, a range whose inverse is an FP32 number
+  r.inv_w = poly_inverse_range(rcut);
   r.fine = poly_fine(xi, rcut);
-  s->h_tab = smooth_poly<double>(sp, rcut, r.fine);
-  s->h_tab32 = smooth_poly<float>(sp, rcut, r.fine);
+  // in units of 1 / (8 pi eta), as the kernel's free-space functions
+  const SmoothPart sp(a, 1.0 / (8.0 * M_PI), xi, 1.0 / r.inv_w);
+  s->h_tab = smooth_poly<double>(sp, 1.0 / r.inv_w, r.fine);
+  s->h_tab32 = smooth_poly<float>(sp, 1.0 / r.inv_w, r.fine);
   double s0[5];
-  sp.eval(0.0, s0);
+  SmoothPart(a, p.eta, xi, rcut).eval(0.0, s0);
   r.self_t = mt - s0[0];
   r.self_r = mr - s0[2];
   s->drag_t = 6.0 * M_PI * p.eta * a;
@@ -2057,7 +2059,8 @@ fsd_status fsd_real_functions(fsd_system* s, int n, const double* r, double* out
     const int intervals = s->rp.fine * P::kIntervals;
     const double u = r[q] * s->rp.inv_w * intervals;
     const int it = std::min(int(u), intervals - 1);
-    const double scale[5] = {1.0, r[q] * r[q], 1.0, r[q] * r[q], r[q]};
+    const double c8 = 1.0 / (8.0 * M_PI * s->p.eta);
+    const double scale[5] = {c8, c8 * r[q] * r[q], c8, c8 * r[q] * r[q], c8 * r[q]};
     for (int k = 0; k < 5; ++k) {
       const double* cf = &s->h_tab[size_t(it) * P::kStride + k * P::kCoef];
       double sv = cf[0];

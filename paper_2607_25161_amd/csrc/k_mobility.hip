@@ -76,13 +76,14 @@ struct SpreadPlan {
 // real-space pair sum: one group of LPR lanes per bead row
 // ------------------------------------------------------------------------------------------
 
-// The smooth part of a pair, five scalars as piecewise polynomials of the distance (RealPoly):
-// interval q = int(r inv_w) (the last one at most), x = r inv_w - q - 1/2, Horner from the highest coefficient.  T points
-// at the coefficients in LDS, read in 16-byte pieces; rows are an odd number of pieces apart, so
-// that lanes at different distances meet different banks (an even number, 18, left FP64 half of
+// Takes the smooth part of a pair, five scalars as piecewise polynomials of the distance (RealPoly), from
+// its free-space functions v: interval q = int(r inv_w) (the last one at most), x = r inv_w - q - 1/2, Horner
+// from the highest coefficient, the constant one straight from v (both are close there, so their difference has
+// little rounding).  T points at the coefficients in LDS, read in 16-byte pieces; rows are an odd number of pieces
+// apart, so that lanes at different distances meet different banks (an even number, 18, left FP64 half of
 // the banks: 163 us instead of 154 at 81,920 beads).
 template <typename R>
-__device__ __forceinline__ void smooth_part(const R* T, R r, R inv_w, int last, R (&f)[5]) {
+__device__ __forceinline__ void less_smooth_part(const R* T, R r, R inv_w, int last, R (&v)[5]) {
   using P = RealPoly<R>;
   const R u = r * inv_w;
   const int q = min(int(u), last);  // r < r_cut up to rounding
@@ -93,13 +94,29 @@ __device__ __forceinline__ void smooth_part(const R* T, R r, R inv_w, int last, 
   V c[(5 * P::kCoef + L - 1) / L];
 #pragma unroll
   for (int k = 0; k < int(sizeof(c) / sizeof(V)); ++k) c[k] = row[k];
+  const auto at = [&](int i) { return c[i / L][i % L]; };
 #pragma unroll
   for (int k = 0; k < 5; ++k) {
-    R v = c[(k * P::kCoef) / L][(k * P::kCoef) % L];
+    R p = at(k * P::kCoef);
 #pragma unroll
-    for (int m = 1; m < P::kCoef; ++m) v = v * x + c[(k * P::kCoef + m) / L][(k * P::kCoef + m) % L];
-    f[k] = v;
+    for (int m = 1; m < P::kCoef - 1; ++m) p = p * x + at(k * P::kCoef + m);
+    v[k] = (v[k] - at(k * P::kCoef + P::kCoef - 1)) - p * x;
   }
+}
+
+// 1 / sqrt(r2) and sqrt(r2).  In FP32 to the last place: the hardware's estimate is off by up to one, and it enters
+// the functions three times over.  The FP32 sum against the FP64 one, 300 to 30,000 beads: off by 2.5 to 2.9e-7 of its
+// size with the plain estimate, c8 and the interval factor rounded and multiplied in, and the smooth part rounded
+// before it is subtracted; by 1.4 to 1.5e-7 as it is (1.75 to 2.1e-7 with square roots, divisions and a table).
+__device__ __forceinline__ void root(float r2, float& r, float& ir) {
+  ir = rsqrtf(r2);
+  r = r2 * ir;
+  r = __builtin_fmaf(__builtin_fmaf(-r, r, r2), 0.5f * ir, r);
+  ir = __builtin_fmaf(ir, __builtin_fmaf(-r, ir, 1.0f), ir);
+}
+__device__ __forceinline__ void root(double r2, double& r, double& ir) {
+  ir = rsqrt(r2);
+  r = r2 * ir;
 }
 
 // Out of the pair's separation vector d itself, with no unit vector and no division:
@@ -159,30 +176,27 @@ __device__ __forceinline__ void real_sum_body(int nb, const double4* __restrict_
       const R dy = R(dyd);
       const R dz = R(pi.z - pj.z + (int((c >> 28) & 7u) - 3) * rp.L);
       const R r2 = dx * dx + dy * dy + dz * dz;
-      const R ir = rsqrt(r2), ir2 = ir * ir, ir3 = ir * ir2, r = r2 * ir;
+      R r, ir;
+      root(r2, r, ir);
+      const R ir2 = ir * ir, ir3 = ir * ir2;
       // free-space force-torque RPY; C, tB and rB are the rt, tt and rr functions over r, r^2, r^2
-      R tI, tB, rI, rB, cc;
-      if (r2 >= touch) {
-        tI = c8 * ir * (R(1) + R(2.0 / 3.0) * a2 * ir2);
-        tB = c8 * ir3 * (R(1) - R(2) * a2 * ir2);
-        rI = R(-0.5) * c8 * ir3;
-        rB = R(1.5) * c8 * ir3 * ir2;
-        cc = -c8 * ir3;
-      } else {  // overlapping spheres
-        const R s = r / a, mt = c8 / a * R(4.0 / 3.0), mr = c8 / (a * a2);
-        tI = mt * (R(1) - R(9.0 / 32.0) * s);
-        tB = mt * R(3.0 / 32.0) * s * ir2;
-        rI = mr * (R(1) - R(27.0 / 32.0) * s + R(5.0 / 64.0) * s * s * s);
-        rB = mr * (R(9.0 / 32.0) * s - R(3.0 / 64.0) * s * s * s) * ir2;
-        cc = -R(0.5) * mr * (R(1) - R(3.0 / 8.0) * s);
-      }
       R f[5];
-      smooth_part<R>(T, r, inv_w, last, f);
-      tI -= f[0];
-      tB -= f[1];
-      rI -= f[2];
-      rB -= f[3];
-      cc -= f[4];
+      if (r2 >= touch) {
+        f[0] = ir * (R(1) + R(2.0 / 3.0) * a2 * ir2);
+        f[1] = ir3 * (R(1) - R(2) * a2 * ir2);
+        f[2] = R(-0.5) * ir3;
+        f[3] = R(1.5) * ir3 * ir2;
+        f[4] = -ir3;
+      } else {  // overlapping spheres
+        const R s = r / a, mt = R(4.0 / 3.0) / a, mr = R(1) / (a * a2);
+        f[0] = mt * (R(1) - R(9.0 / 32.0) * s);
+        f[1] = mt * R(3.0 / 32.0) * s * ir2;
+        f[2] = mr * (R(1) - R(27.0 / 32.0) * s + R(5.0 / 64.0) * s * s * s);
+        f[3] = mr * (R(9.0 / 32.0) * s - R(3.0 / 64.0) * s * s * s) * ir2;
+        f[4] = -R(0.5) * mr * (R(1) - R(3.0 / 8.0) * s);
+      }
+      less_smooth_part<R>(T, r, inv_w, last, f);
+      const R tI = f[0], tB = f[1], rI = f[2], rB = f[3], cc = f[4];
       const R fd = tB * (dx * fx + dy * fy + dz * fz), td = rB * (dx * tx + dy * ty + dz * tz);
       u0 += tI * fx + fd * dx + cc * (dy * tz - dz * ty);
       u1 += tI * fy + fd * dy + cc * (dz * tx - dx * tz);
@@ -212,11 +226,11 @@ __device__ __forceinline__ void real_sum_body(int nb, const double4* __restrict_
       const double* li = lam + 6 * size_t(row) + h;
       double* o = out + 6 * size_t(row) + h;
       const double self = up ? rp.self_r : rp.self_t;
-      double v[6] = {double(u0) + self * li[0], double(u1) + self * li[1], double(u2) + self * li[2], 0, 0, 0};
+      double v[6] = {c8 * u0 + self * li[0], c8 * u1 + self * li[1], c8 * u2 + self * li[2], 0, 0, 0};
       if (LPR == 1) {
-        v[3] = double(w0) + rp.self_r * li[3];
-        v[4] = double(w1) + rp.self_r * li[4];
-        v[5] = double(w2) + rp.self_r * li[5];
+        v[3] = c8 * w0 + rp.self_r * li[3];
+        v[4] = c8 * w1 + rp.self_r * li[4];
+        v[5] = c8 * w2 + rp.self_r * li[5];
       }
       for (int k = 0; k < (LPR == 1 ? 6 : 3); ++k) o[k] = accumulate ? o[k] + v[k] : v[k];
     }

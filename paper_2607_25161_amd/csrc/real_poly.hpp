@@ -1,13 +1,14 @@
 // Layout of the smooth part of the real-space functions, for the kernels and the host.
 #pragma once
+#include <cmath>
 #include <cstddef>
 
 namespace fsd {
 
-// The smooth part as piecewise polynomials on fine kIntervals equal intervals of [0, r_cut]: five
+// The smooth part as piecewise polynomials on fine kIntervals equal intervals of [0, 1 / poly_inverse_range]: five
 // functions of kCoef coefficients each (highest power first, in the offset from the interval's centre
 // over its width), rows kStride values apart (an odd multiple of 16 bytes).  The functions, all even
-// in r: tt I, tt rr / r^2, rr I, rr rr / r^2, rt / r.
+// in r and in units of 1 / (8 pi eta): tt I, tt rr / r^2, rr I, rr rr / r^2, rt / r.
 template <typename R>
 struct RealPoly;
 template <>
@@ -28,5 +29,12 @@ struct RealPoly<float> {
 // at 25; with the base intervals they would be 2e-12 at 14.5.  In FP32 the fit alone is off by at most 7e-9 and
 // its rounded form by 1.3e-7 (1.9e-7): the values reach about one self mobility.
 inline int poly_fine(double xi, double rcut) { return xi * rcut > 7.0 ? 2 : 1; }
+
+// The inverse of the range that the polynomials cover: the largest FP32 number up to 1 / rcut, so that a
+// distance in intervals has no systematic error in FP32 (a rounded factor moves every pair the same way)
+inline double poly_inverse_range(double rcut) {
+  const float f = float(1.0 / rcut);
+  return double(f) * rcut > 1.0 ? double(std::nextafter(f, 0.0f)) : double(f);
+}
 
 }  // namespace fsd
