@@ -81,7 +81,9 @@ struct WaveParams {
 
 // Constants of the real-space part.
 struct RealParams {
-  double L, a, eta;
+  double L, a;
+  double c8;        // 1 / (8 pi eta), the unit of the kernel's pair functions
+  double mt, mr;    // 4 / (3 a) and 1 / a^3: the self mobilities in that unit
   double r_cut;
   double inv_w;     // poly_inverse_range: a distance in units of the range the smooth part covers
   int fine;         // intervals of the smooth part, in units of RealPoly::kIntervals

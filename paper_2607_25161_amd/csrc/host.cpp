@@ -531,7 +531,9 @@ void choose_parameters(fsd_system* s) {
   RealParams& r = s->rp;
   r.L = L;
   r.a = a;
-  r.eta = p.eta;
+  r.c8 = 1.0 / (8.0 * M_PI * p.eta);
+  r.mt = 4.0 / (3.0 * a);
+  r.mr = 1.0 / (a * a * a);
   // Real-space cutoff: the rule sqrt(-ln tol)/xi is the floor; the polynomial
   // prefactors of the split leave the pair functions above tol there, so the
   // cutoff grows until every function is below tol times the self-mobility.
@@ -2059,7 +2061,7 @@ fsd_status fsd_real_functions(fsd_system* s, int n, const double* r, double* out
     const int intervals = s->rp.fine * P::kIntervals;
     const double u = r[q] * s->rp.inv_w * intervals;
     const int it = std::min(int(u), intervals - 1);
-    const double c8 = 1.0 / (8.0 * M_PI * s->p.eta);
+    const double c8 = s->rp.c8;
     const double scale[5] = {c8, c8 * r[q] * r[q], c8, c8 * r[q] * r[q], c8 * r[q]};
     for (int k = 0; k < 5; ++k) {
       const double* cf = &s->h_tab[size_t(it) * P::kStride + k * P::kCoef];

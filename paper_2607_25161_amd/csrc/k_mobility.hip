@@ -153,8 +153,9 @@ __device__ __forceinline__ void real_sum_body(int nb, const double4* __restrict_
   if (chunk > kGroups) chunk = (chunk + kGroups - 1) / kGroups * kGroups;  // whole passes
   const int lb = order ? xcd_remap(bx, nblk) : bx;  // with an order, each XCD takes one contiguous range
   const int r_end = min(nb, (lb + 1) * chunk), lane = threadIdx.x % LPR;
-  const R a = R(rp.a), a2 = a * a;
-  const R c8 = R(1.0 / (8.0 * M_PI * rp.eta));
+  // the functions are in units of c8 = 1 / (8 pi eta), which multiplies the sums in FP64
+  const R a = R(rp.a), a2 = a * a, mt = R(rp.mt), mr = R(rp.mr);
+  const double c8 = rp.c8;
   const int last = rp.fine * P::kIntervals - 1;
   const R inv_w = R(rp.inv_w) * R(rp.fine * P::kIntervals);
   const R touch = R(4) * a2;
@@ -188,7 +189,7 @@ __device__ __forceinline__ void real_sum_body(int nb, const double4* __restrict_
         f[3] = R(1.5) * ir3 * ir2;
         f[4] = -ir3;
       } else {  // overlapping spheres
-        const R s = r / a, mt = R(4.0 / 3.0) / a, mr = R(1) / (a * a2);
+        const R s = r / a;
         f[0] = mt * (R(1) - R(9.0 / 32.0) * s);
         f[1] = mt * R(3.0 / 32.0) * s * ir2;
         f[2] = mr * (R(1) - R(27.0 / 32.0) * s + R(5.0 / 64.0) * s * s * s);
